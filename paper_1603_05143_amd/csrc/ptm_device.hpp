@@ -121,7 +121,17 @@ __host__ __device__ inline int orient2_sign_exact(const double *p, const double 
     return exp_sign(x);
 }
 
-PTM_HD int sgn_diff(double a, double b) { return a > b ? 1 : (a < b ? -1 : 0); }
+typedef __int128 i128;
+typedef unsigned __int128 u128;
+
+// the same in integers (coordinates below 2^60): sign of det[[p_i, p_j, 1], [q_i, q_j, 1], [r_i, r_j, 1]]
+PTM_HD int orient2_sign_exact(const int64_t *p, const int64_t *q, const int64_t *r, int i, int j) {
+    const i128 x = (i128)(q[i] - p[i]) * (r[j] - p[j]), y = (i128)(q[j] - p[j]) * (r[i] - p[i]);
+    return x > y ? 1 : (x < y ? -1 : 0);
+}
+
+template <typename T>
+PTM_HD int sgn_diff(T a, T b) { return a > b ? 1 : (a < b ? -1 : 0); }
 
 // Simulation of Simplicity for the 4x4 orientation determinant.  Rows sorted
 // by increasing rank r0 < r1 < r2 < r3; rank r's coordinate j is perturbed by
@@ -129,12 +139,9 @@ PTM_HD int sgn_diff(double a, double b) { return a > b ? 1 : (a < b ? -1 : 0); }
 // before y before x.  The perturbed determinant is a polynomial in eps whose
 // coefficients are signed minors; in order of decreasing size the
 // non-vanishing candidates are listed below as (sign, minor).  Returns the
-// sign of det L_sorted(eps).
-#ifdef __HIP_DEVICE_COMPILE__
-__attribute__((noinline))
-#endif
-__host__ __device__ inline int sos_lambda4_sorted(const double *p0, const double *p1, const double *p2,
-                                           const double *p3) {
+// sign of det L_sorted(eps).  T: double (expansions) or int64_t (fixed point).
+template <typename T>
+PTM_HD int sos_lambda4_sorted(const T *p0, const T *p1, const T *p2, const T *p3) {
     int s;
     // eps(r0,z): +det[x y 1] of rows 1,2,3
     if ((s = orient2_sign_exact(p1, p2, p3, 0, 1))) return s;
@@ -173,7 +180,8 @@ __host__ __device__ inline int sos_lambda4_sorted(const double *p0, const double
 }
 
 // orientation of (a,b,c,d) := det[b-a; c-a; d-a] (> 0: d on the side the
-// normal (b-a)x(c-a) points to), exactly, with SoS by the ranks ra..rd
+// normal (b-a)x(c-a) points to), exactly, with SoS by the ranks ra..rd, on
+// expansions: any finite input
 #ifdef __HIP_DEVICE_COMPILE__
 __attribute__((noinline))
 #endif
@@ -194,39 +202,135 @@ __host__ __device__ inline int orient_exact_sos(const double *a, const double *b
     return -parity * sos_lambda4_sorted(p[0], p[1], p[2], p[3]);
 }
 
-// Semi-static filter for det[b-a; c-a; d-a] in FP64 with exact inputs.
-// Returns the sign, or 0 when the error bound does not decide it.  The
-// evaluation uses differences against d (det[a-d; b-d; c-d] = -orient) and
-// the bound 10 u x permanent (u = 2^-53) covers the 3 input differences, 2 products,
-// 1 subtraction, 1 product and 2 additions of each term.
-PTM_HD int orient_filter64(const double *a, const double *b, const double *c, const double *d) {
-    double adx = a[0] - d[0], ady = a[1] - d[1], adz = a[2] - d[2];
-    double bdx = b[0] - d[0], bdy = b[1] - d[1], bdz = b[2] - d[2];
-    double cdx = c[0] - d[0], cdy = c[1] - d[1], cdz = c[2] - d[2];
-    double m1 = bdx * cdy, m2 = cdx * bdy;
-    double m3 = cdx * ady, m4 = adx * cdy;
-    double m5 = adx * bdy, m6 = bdx * ady;
-    double det = adz * (m1 - m2) + bdz * (m3 - m4) + cdz * (m5 - m6);
-    double perm = (fabs(m1) + fabs(m2)) * fabs(adz) + (fabs(m3) + fabs(m4)) * fabs(bdz) +
-                  (fabs(m5) + fabs(m6)) * fabs(cdz);
-    double bound = 1.1102230246251565e-15 * perm;  // 10 unit roundoffs of perm
-    if (det > bound) return -1;
-    if (det < -bound) return 1;
-    return 0;
+#ifdef __HIP_DEVICE_COMPILE__
+__attribute__((noinline))
+#endif
+__host__ __device__ inline int det3_sign_exact(const double *a, const double *b, const double *c) {
+    Expansion x;
+    x.n = 0;
+    exp_add_det3(x, a, b, c, 1.0);
+    return exp_sign(x);
 }
 
-// det[a; b; c] (raw coordinates) filter; 0 if undecided
-PTM_HD int det3_filter64(const double *a, const double *b, const double *c) {
-    double m1 = b[1] * c[2], m2 = b[2] * c[1];
-    double m3 = b[2] * c[0], m4 = b[0] * c[2];
-    double m5 = b[0] * c[1], m6 = b[1] * c[0];
-    double det = a[0] * (m1 - m2) + a[1] * (m3 - m4) + a[2] * (m5 - m6);
-    double perm = fabs(a[0]) * (fabs(m1) + fabs(m2)) + fabs(a[1]) * (fabs(m3) + fabs(m4)) +
-                  fabs(a[2]) * (fabs(m5) + fabs(m6));
-    double bound = 8.8817841970012523e-16 * perm;  // 8 unit roundoffs
-    if (det > bound) return 1;
-    if (det < -bound) return -1;
-    return 0;
+// ----------------------------------------------------------- fixed point
+// The exact predicates in integers.  Neighbour vectors are differences of
+// positions that share a magnitude, so their coordinates are multiples of
+// one small power of two: scaled by the power of two that brings the largest
+// below 2^60 they are integers, and the determinants are integers of at most
+// 186 bits (differences below 2^61, 2x2 minors below 2^123).  Points that do
+// not fit (a coordinate 2^60 times finer than the largest) take the
+// expansions above, which need per-lane arrays of 112 components in scratch
+// memory and tens of thousands of instructions per predicate.  A noise-free
+// crystal needs exact predicates in every atom (coplanar facet corners): with
+// expansions a frame of 99,991 such atoms took 16.0 ms, 14.0 of them in the
+// hull kernel, with integers 2.1 ms.
+// power of two that brings |x| <= m (finite) below 2^60
+PTM_HD int fixed_shift(double m) {
+    int e = 0;
+    (void)frexp(m, &e);  // m < 2^e
+    return 60 - e;
+}
+// x * 2^shift as an integer; ok is cleared if it is none
+PTM_HD int64_t to_fixed(double x, int shift, bool &ok) {
+    const double t = ldexp(x, shift);
+    ok = ok && trunc(t) == t && (t != 0.0 || x == 0.0);
+    return (int64_t)t;
+}
+
+// acc += m * u, 192-bit two's complement (hi, mid, lo), |m| < 2^124, |u| < 2^62
+struct Acc192 {
+    uint64_t lo, mid, hi;
+};
+PTM_HD void acc_add(Acc192 &acc, i128 m, int64_t u) {
+    const bool neg = (m < 0) != (u < 0);
+    const u128 mm = m < 0 ? (u128)0 - (u128)m : (u128)m;
+    const uint64_t uu = u < 0 ? 0ull - (uint64_t)u : (uint64_t)u;
+    const u128 p0 = (u128)(uint64_t)mm * uu, p1 = (u128)(uint64_t)(mm >> 64) * uu;
+    const u128 t = (p0 >> 64) + (uint64_t)p1;
+    const uint64_t flip = neg ? ~0ull : 0ull;
+    const uint64_t a0 = (uint64_t)p0 ^ flip, a1 = (uint64_t)t ^ flip;
+    const uint64_t a2 = ((uint64_t)(p1 >> 64) + (uint64_t)(t >> 64)) ^ flip;
+    const u128 s0 = (u128)acc.lo + a0 + (neg ? 1u : 0u);
+    const u128 s1 = (u128)acc.mid + a1 + (uint64_t)(s0 >> 64);
+    acc.lo = (uint64_t)s0;
+    acc.mid = (uint64_t)s1;
+    acc.hi += a2 + (uint64_t)(s1 >> 64);
+}
+PTM_HD int acc_sign(const Acc192 &acc) {
+    if ((int64_t)acc.hi < 0) return -1;
+    return (acc.hi | acc.mid | acc.lo) ? 1 : 0;
+}
+
+// sign of det[u; v; w], entries below 2^61
+PTM_HD int det3_sign_fixed(const int64_t *u, const int64_t *v, const int64_t *w) {
+    Acc192 acc = {0, 0, 0};
+    acc_add(acc, (i128)v[1] * w[2] - (i128)v[2] * w[1], u[0]);
+    acc_add(acc, (i128)v[2] * w[0] - (i128)v[0] * w[2], u[1]);
+    acc_add(acc, (i128)v[0] * w[1] - (i128)v[1] * w[0], u[2]);
+    return acc_sign(acc);
+}
+
+// orient_exact_sos in fixed point; 2 if the points do not fit.  Scalar
+// arguments (a call passes them in registers); ranks: ra | rb << 8 | rc << 16
+// | rd << 24.
+#ifdef __HIP_DEVICE_COMPILE__
+__attribute__((noinline))
+#endif
+__host__ __device__ inline int orient_fixed_sos(double ax, double ay, double az, double bx, double by, double bz,
+                                                double cx, double cy, double cz, double dx, double dy, double dz,
+                                                uint32_t ranks) {
+    const double m = fmax(fmax(fmax(fmax(fabs(ax), fabs(ay)), fmax(fabs(az), fabs(bx))),
+                               fmax(fmax(fabs(by), fabs(bz)), fmax(fabs(cx), fabs(cy)))),
+                          fmax(fmax(fabs(cz), fabs(dx)), fmax(fabs(dy), fabs(dz))));
+    const int sh = fixed_shift(m);
+    bool ok = m > 0.0 && m < INFINITY;
+    int64_t P[4][3] = {{to_fixed(ax, sh, ok), to_fixed(ay, sh, ok), to_fixed(az, sh, ok)},
+                       {to_fixed(bx, sh, ok), to_fixed(by, sh, ok), to_fixed(bz, sh, ok)},
+                       {to_fixed(cx, sh, ok), to_fixed(cy, sh, ok), to_fixed(cz, sh, ok)},
+                       {to_fixed(dx, sh, ok), to_fixed(dy, sh, ok), to_fixed(dz, sh, ok)}};
+    if (!ok) return 2;
+    int64_t U[3][3];
+    for (int i = 0; i < 3; i++)
+        for (int k = 0; k < 3; k++) U[i][k] = P[i + 1][k] - P[0][k];
+    const int s = det3_sign_fixed(U[0], U[1], U[2]);
+    if (s) return s;
+    // sort by rank with exchanges of the points themselves, so that they stay in registers
+    int r[4];
+    for (int i = 0; i < 4; i++) r[i] = (int)((ranks >> (8 * i)) & 0xFF);
+    int parity = 1;
+#pragma unroll
+    for (int i = 0; i < 3; i++)
+#pragma unroll
+        for (int j = 0; j < 3 - i; j++) {
+            const bool sw = r[j] > r[j + 1];
+            const int t = r[j];
+            r[j] = sw ? r[j + 1] : t;
+            r[j + 1] = sw ? t : r[j + 1];
+#pragma unroll
+            for (int k = 0; k < 3; k++) {
+                const int64_t x = P[j][k];
+                P[j][k] = sw ? P[j + 1][k] : x;
+                P[j + 1][k] = sw ? x : P[j + 1][k];
+            }
+            parity = sw ? -parity : parity;
+        }
+    return -parity * sos_lambda4_sorted<int64_t>(P[0], P[1], P[2], P[3]);
+}
+
+// det3_sign_exact in fixed point; 2 if the points do not fit
+#ifdef __HIP_DEVICE_COMPILE__
+__attribute__((noinline))
+#endif
+__host__ __device__ inline int det3_fixed(double ax, double ay, double az, double bx, double by, double bz, double cx,
+                                          double cy, double cz) {
+    const double m = fmax(fmax(fmax(fabs(ax), fabs(ay)), fmax(fabs(az), fabs(bx))),
+                          fmax(fmax(fabs(by), fabs(bz)), fmax(fmax(fabs(cx), fabs(cy)), fabs(cz))));
+    const int sh = fixed_shift(m);
+    bool ok = m > 0.0 && m < INFINITY;
+    const int64_t u[3] = {to_fixed(ax, sh, ok), to_fixed(ay, sh, ok), to_fixed(az, sh, ok)};
+    const int64_t v[3] = {to_fixed(bx, sh, ok), to_fixed(by, sh, ok), to_fixed(bz, sh, ok)};
+    const int64_t w[3] = {to_fixed(cx, sh, ok), to_fixed(cy, sh, ok), to_fixed(cz, sh, ok)};
+    return ok ? det3_sign_fixed(u, v, w) : 2;
 }
 
 // Static error bounds.  For a point set whose coordinates are at most m in
@@ -308,8 +412,8 @@ PTM_HD int det3_filter_f32in(const float *a, const float *b, const float *c, dou
     return 0;
 }
 
-// FP64 filters with a static bound (same evaluation as orient_filter64 /
-// det3_filter64, without the per-test permanent)
+// FP64 filters with a static bound: det[a-d; b-d; c-d] = -det[b-a; c-a; d-a]
+// and det[a; b; c]; 0 when the bound does not decide the sign
 PTM_HD int orient_filter64b(const double *a, const double *b, const double *c, const double *d, double bound) {
     // fused multiply-adds round once where a product and a sum round twice,
     // so the error bound of the unfused evaluation covers them
@@ -334,41 +438,22 @@ PTM_HD int det3_filter64b(const double *a, const double *b, const double *c, dou
     return 0;
 }
 
-#ifdef __HIP_DEVICE_COMPILE__
-__attribute__((noinline))
-#endif
-__host__ __device__ inline int det3_sign_exact(const double *a, const double *b, const double *c) {
-    Expansion x;
-    x.n = 0;
-    exp_add_det3(x, a, b, c, 1.0);
-    return exp_sign(x);
-}
-
-PTM_HD int orient_sos64(const double *a, const double *b, const double *c, const double *d, int ra, int rb,
-                        int rc, int rd) {
-    int s = orient_filter64(a, b, c, d);
-    if (s) return s;
-    return orient_exact_sos(a, b, c, d, ra, rb, rc, rd);
-}
-
-PTM_HD int det3_sign64(const double *a, const double *b, const double *c) {
-    int s = det3_filter64(a, b, c);
-    if (s) return s;
-    return det3_sign_exact(a, b, c);
-}
-
-// the same with a static filter bound (f64_orient_bound / f64_det3_bound)
+// FP64 filter with a static bound (f64_orient_bound / f64_det3_bound), then
+// exact arithmetic (fixed point, or expansions for points that do not fit)
 PTM_HD int orient_sos64b(const double *a, const double *b, const double *c, const double *d, int ra, int rb,
                          int rc, int rd, double bound) {
     int s = orient_filter64b(a, b, c, d, bound);
     if (s) return s;
-    return orient_exact_sos(a, b, c, d, ra, rb, rc, rd);
+    s = orient_fixed_sos(a[0], a[1], a[2], b[0], b[1], b[2], c[0], c[1], c[2], d[0], d[1], d[2],
+                         (uint32_t)ra | ((uint32_t)rb << 8) | ((uint32_t)rc << 16) | ((uint32_t)rd << 24));
+    return s != 2 ? s : orient_exact_sos(a, b, c, d, ra, rb, rc, rd);
 }
 
 PTM_HD int det3_sign64b(const double *a, const double *b, const double *c, double bound) {
     int s = det3_filter64b(a, b, c, bound);
     if (s) return s;
-    return det3_sign_exact(a, b, c);
+    s = det3_fixed(a[0], a[1], a[2], b[0], b[1], b[2], c[0], c[1], c[2]);
+    return s != 2 ? s : det3_sign_exact(a, b, c);
 }
 
 // ------------------------------------------------------------------- QCP

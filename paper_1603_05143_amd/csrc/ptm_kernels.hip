@@ -903,8 +903,10 @@ __device__ inline bool vhull_insert(const VLane &L, int p, uint32_t &live) {
     uint32_t vis = 0;
     const float bf = (float)L.bo;
     // two facets per step: both filters' loads are issued together.  A facet
-    // is visible when its FP32 determinant lies below -bound; the rare one
-    // within the bound (or NaN) takes the exact path.
+    // is visible when its FP32 determinant lies below -bound; those within
+    // the bound (or NaN) take the exact path after the loop (a wave then pays
+    // for the most any lane has, not for every step in which some lane has one).
+    uint32_t und = 0;
     for (uint32_t m = live; m;) {
         const int f0 = __builtin_ctz(m);
         m &= m - 1;
@@ -920,10 +922,14 @@ __device__ inline bool vhull_insert(const VLane &L, int p, uint32_t &live) {
         L.load(vv(w1, 1), b1);
         L.load(vv(w1, 2), c1);
         const float d0 = orient_det_f32in(a0, b0, c0, pp), d1 = orient_det_f32in(a1, b1, c1, pp);
-        bool v0 = d0 < -bf, v1 = d1 < -bf;
-        if (!(fabsf(d0) > bf)) v0 = L.orient_exact(vv(w0, 0), vv(w0, 1), vv(w0, 2), p) > 0;
-        if (two && !(fabsf(d1) > bf)) v1 = L.orient_exact(vv(w1, 0), vv(w1, 1), vv(w1, 2), p) > 0;
-        vis |= (v0 ? 1u << f0 : 0u) | (two && v1 ? 1u << f1 : 0u);
+        // (f1 is f0 again when there is no second)
+        vis |= (d0 < -bf ? 1u << f0 : 0u) | (d1 < -bf ? 1u << f1 : 0u);
+        und |= (!(fabsf(d0) > bf) ? 1u << f0 : 0u) | (!(fabsf(d1) > bf) ? 1u << f1 : 0u);
+    }
+    for (; und; und &= und - 1) {
+        const int f = __builtin_ctz(und);
+        const uint32_t w = S.F[f][t];
+        if (L.orient_exact(vv(w, 0), vv(w, 1), vv(w, 2), p) > 0) vis |= 1u << f;
     }
     if (!vis) return true;
     // horizon edges (a -> b) of the visible facets whose neighbour g is not
@@ -1371,7 +1377,11 @@ __device__ int lane_insert(const Lane &L, int p, uint32_t &cv) {
     const float bf = (float)L.bo;
     // two facets per step (nf is even): both filters' loads are issued
     // together.  A facet is visible when its FP32 determinant lies below
-    // -bound; the rare one within the bound (or NaN) takes the exact path.
+    // -bound; those within the bound (or NaN) take the exact path after the
+    // loop: a wave then pays for the most any lane has, not for every step in
+    // which some lane has one (noise-free crystals: coplanar quadruples in
+    // every atom), and the exact path's code stands in one place.
+    uint32_t und = 0;
     for (int f = 0; f < nf; f += 2) {
         const uint32_t w0 = S.F[f][t], w1 = S.F[f + 1][t];
         float a0[3], b0[3], c0[3], a1[3], b1[3], c1[3];
@@ -1382,10 +1392,13 @@ __device__ int lane_insert(const Lane &L, int p, uint32_t &cv) {
         L.load(fv(w1, 1), b1);
         L.load(fv(w1, 2), c1);
         const float d0 = orient_det_f32in(a0, b0, c0, pp), d1 = orient_det_f32in(a1, b1, c1, pp);
-        bool v0 = d0 < -bf, v1 = d1 < -bf;
-        if (!(fabsf(d0) > bf)) v0 = lane_orient_exact(L, fv(w0, 0), fv(w0, 1), fv(w0, 2), p) > 0;
-        if (!(fabsf(d1) > bf)) v1 = lane_orient_exact(L, fv(w1, 0), fv(w1, 1), fv(w1, 2), p) > 0;
-        vis |= (v0 ? 1u << f : 0u) | (v1 ? 2u << f : 0u);
+        vis |= (d0 < -bf ? 1u << f : 0u) | (d1 < -bf ? 2u << f : 0u);
+        und |= (!(fabsf(d0) > bf) ? 1u << f : 0u) | (!(fabsf(d1) > bf) ? 2u << f : 0u);
+    }
+    for (; und; und &= und - 1) {
+        const int f = __builtin_ctz(und);
+        const uint32_t w = S.F[f][t];
+        if (lane_orient_exact(L, fv(w, 0), fv(w, 1), fv(w, 2), p) > 0) vis |= 1u << f;
     }
     if (vis == 0) return 0;  // p inside: never a vertex
     const int nvis = __builtin_popcount(vis);
@@ -1457,7 +1470,8 @@ __device__ int lane_insert(const Lane &L, int p, uint32_t &cv) {
 __device__ inline int lane_centre_inside(const Lane &L, int K, uint32_t &cv) {
     const uint32_t all = (1u << (2 * K - 4)) - 1;
     const float bd = (float)L.bd;
-    // two facets per step, as in the insertion
+    // two facets per step and the undecided ones afterwards, as in the insertion
+    uint32_t und = 0;
     for (uint32_t m = all & ~cv; m;) {
         const int f0 = __builtin_ctz(m);
         m &= m - 1;
@@ -1474,8 +1488,11 @@ __device__ inline int lane_centre_inside(const Lane &L, int K, uint32_t &cv) {
         // outside below -bound; within the bound (or NaN) the exact path decides
         const float e0 = det3_f32in(a0, b0, c0), e1 = det3_f32in(a1, b1, c1);
         if (e0 < -bd || e1 < -bd) return 0;
-        if (!(e0 > bd) && lane_det3_exact(L, fv(w0, 0), fv(w0, 1), fv(w0, 2)) <= 0) return 0;
-        if (!(e1 > bd) && lane_det3_exact(L, fv(w1, 0), fv(w1, 1), fv(w1, 2)) <= 0) return 0;
+        und |= (!(e0 > bd) ? 1u << f0 : 0u) | (!(e1 > bd) ? 1u << f1 : 0u);
+    }
+    for (; und; und &= und - 1) {
+        const uint32_t w = L.S.F[__builtin_ctz(und)][L.t];
+        if (lane_det3_exact(L, fv(w, 0), fv(w, 1), fv(w, 2)) <= 0) return 0;
     }
     cv |= all;
     return 1;
