@@ -88,6 +88,8 @@ bool FrameScratch::reserve(int64_t n, int64_t cells, bool topo, std::string &err
     nbr_rel = (double *)take(8 * (size_t)n * KMAX * 3);
     code = (int32_t *)take(4 * (size_t)n * NGRP);
     ord = (uint64_t *)take(8 * (size_t)n * NGRP);
+    static_assert(sizeof(int4) <= sizeof(uint64_t) * NGRP, "the fixed-point positions fit in ord");
+    sfix = (int4 *)ord;  // read by the k-NN kernels, before the hull kernel writes ord
     part = (double *)take(8 * 7 * (size_t)nb);
     sv_part = (double *)take(8 * 7 * (size_t)serve_bounds_items(n));
     sv_bsum = (int32_t *)take(4 * (size_t)(serve_scan_items(n) + 1));
@@ -166,6 +168,7 @@ Grid make_grid(const double box[3], const double mn[3], const double mx[3], int6
         hmax = std::fmax(hmax, g.h[a]);
     }
     g.margin = 1e-9 * hmax;
+    set_fixed_scale(g, ext, mn, mx);
     g.canonical = 1;
     for (int a = 0; a < 3; a++)
         if (g.periodic[a] && !(mn[a] >= 0.0 && mx[a] < box[a])) g.canonical = 0;
@@ -191,16 +194,16 @@ ptm_status enqueue_frame(ptm_ctx *ctx, FrameScratch &S, const FrameJob &J, hipSt
     const int32_t *box_fail = S.count + cells + 3;
     launch_bin_count(J.pos, n, g, S.cell_of, S.slot_of, S.count, st);
     launch_cell_starts(S.count, cells, S.sv_bsum, S.start, st);
-    launch_bin_scatter(J.pos, n, S.cell_of, S.slot_of, S.start, S.spos, S.sid, st);
+    launch_bin_scatter(J.pos, n, g, S.cell_of, S.slot_of, S.start, S.spos, S.sfix, S.sid, st);
     if ((ps = mark(PTM_STAGE_KNN)) != PTM_OK) return ps;
     // slot_of is free once the atoms are scattered: it holds the leftover list
     if (J.topo) {
         // the 18 Euclidean neighbours, then their topological order (Sec. 3)
-        launch_knn(n, g, VK, S.spos, S.sid, S.start, S.id18, S.rel18, S.slot_of, S.count + cells + 1,
+        launch_knn(n, g, VK, S.spos, S.sfix, S.sid, S.start, S.id18, S.rel18, S.slot_of, S.count + cells + 1,
                    S.count + cells + 3, st);
         launch_voronoi(n, S.rel18, S.id18, S.vf, S.vlive, S.nbr_rel, S.nbr_id, box_fail, st);
     } else {
-        launch_knn(n, g, KMAX, S.spos, S.sid, S.start, S.nbr_id, S.nbr_rel, S.slot_of, S.count + cells + 1,
+        launch_knn(n, g, KMAX, S.spos, S.sfix, S.sid, S.start, S.nbr_id, S.nbr_rel, S.slot_of, S.count + cells + 1,
                    S.count + cells + 3, st);
     }
     if ((ps = mark(PTM_STAGE_TOPO)) != PTM_OK) return ps;

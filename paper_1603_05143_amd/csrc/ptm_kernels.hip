@@ -51,6 +51,18 @@ __device__ inline int cell_coord(double x, const Grid &g, int d) {
     return c;
 }
 
+// Place of the x-row of cells (cy, cz) in the sorted order: rows go tile by
+// tile of 8 x 8, z within y tiles within z tiles, so that the rows an atom's
+// search reads (two to each side) and the atoms next to it in y and z are
+// close in the sorted order.  Plane after plane, the five planes of a search
+// are 20 MB in a frame of 352^3 cells, five times an XCD's L2, and were
+// fetched again for every plane; a tile and its margin are 1.6 MB.
+__device__ inline int cell_row(const Grid &g, int cy, int cz) {
+    const int ty = cy & ~7, tz = cz & ~7;
+    const int wy = min(8, g.nc[1] - ty), wz = min(8, g.nc[2] - tz);
+    return tz * g.nc[1] + ty * wz + (cz - tz) * wy + (cy - ty);
+}
+
 __device__ inline double wrapped(double x, const Grid &g, int d) {
     return g.periodic[d] ? x - g.L[d] * floor(x * g.invL[d]) : x - g.lo[d];
 }
@@ -99,7 +111,7 @@ __global__ void k_bin_count(const double *__restrict__ pos, int64_t n, Grid g, i
     int cx = cell_coord(pos[3 * i + 0], g, 0);
     int cy = cell_coord(pos[3 * i + 1], g, 1);
     int cz = cell_coord(pos[3 * i + 2], g, 2);
-    int c = (cz * g.nc[1] + cy) * g.nc[0] + cx;
+    int c = cell_row(g, cy, cz) * g.nc[0] + cx;
     cell_of[i] = c;
     slot_of[i] = atomicAdd(&count[c], 1);
 }
@@ -215,16 +227,24 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan_cells(const int32_t *__re
     }
 }
 
-__global__ void k_bin_scatter(const double *__restrict__ pos, int64_t n, const int32_t *__restrict__ cell_of,
+// Coordinate x on the grid's fixed-point scale: 2^32 per periodic box length
+// (so that 32-bit differences wrap to the minimum image by themselves), 2^30
+// per extent of an open axis.
+__device__ inline int32_t fixed_coord(double x, const Grid &g, int d) {
+    return (int32_t)(uint32_t)fmin(fmax(wrapped(x, g, d) * g.fix[d], 0.0), 4294967295.0);
+}
+
+__global__ void k_bin_scatter(const double *__restrict__ pos, int64_t n, Grid g, const int32_t *__restrict__ cell_of,
                               const int32_t *__restrict__ slot_of, const int32_t *__restrict__ start,
-                              double *__restrict__ spos,
-                              int32_t *__restrict__ sid) {
+                              double *__restrict__ spos, int4 *__restrict__ sfix, int32_t *__restrict__ sid) {
     int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i >= n) return;
     int64_t p = (int64_t)start[cell_of[i]] + slot_of[i];
-    spos[3 * (int64_t)p] = pos[3 * i + 0];
-    spos[3 * (int64_t)p + 1] = pos[3 * i + 1];
-    spos[3 * (int64_t)p + 2] = pos[3 * i + 2];
+    const double x = pos[3 * i + 0], y = pos[3 * i + 1], z = pos[3 * i + 2];
+    spos[3 * (int64_t)p] = x;
+    spos[3 * (int64_t)p + 1] = y;
+    spos[3 * (int64_t)p + 2] = z;
+    sfix[p] = make_int4(fixed_coord(x, g, 0), fixed_coord(y, g, 1), fixed_coord(z, g, 2), (int32_t)i);
     sid[p] = (int32_t)i;
 }
 
@@ -240,29 +260,6 @@ __device__ inline double min_image(double d, const Grid &g, int a) {
     return d;
 }
 
-// insert (d2, j) -- with j's position q in the sorted arrays -- into the
-// list (kd, kj, kq) of length KN, ascending by (d2, j)
-template <int KN>
-__device__ inline void topk_insert(double (&kd)[KN], int32_t (&kj)[KN], int32_t (&kq)[KN], double d2, int32_t j,
-                                   int32_t q) {
-    bool done = false;
-#pragma unroll
-    for (int m = KN - 1; m > 0; m--) {
-        bool lt = !done && (d2 < kd[m - 1] || (d2 == kd[m - 1] && j < kj[m - 1]));
-        if (!done) {
-            kd[m] = lt ? kd[m - 1] : d2;
-            kj[m] = lt ? kj[m - 1] : j;
-            kq[m] = lt ? kq[m - 1] : q;
-        }
-        done = done || !lt;
-    }
-    if (!done) {
-        kd[0] = d2;
-        kj[0] = j;
-        kq[0] = q;
-    }
-}
-
 __device__ inline void shell_range(const Grid &g, int a, int s, int &lo, int &hi) {
     if (g.periodic[a]) {
         int half = (g.nc[a] - 1) / 2;
@@ -274,30 +271,13 @@ __device__ inline void shell_range(const Grid &g, int a, int s, int &lo, int &hi
     }
 }
 
-// scan the atoms of cell c into the top-K list
-template <int KN>
-__device__ inline void scan_cell(int c, const Grid &g, double xi, double yi, double zi, int32_t i,
-                                 const double *__restrict__ spos, const int32_t *__restrict__ sid,
-                                 const int32_t *__restrict__ start, double (&kd)[KN], int32_t (&kj)[KN],
-                                 int32_t (&kq)[KN], int &found) {
-    int q1 = start[c + 1];
-    for (int q = start[c]; q < q1; q++) {
-        int32_t j = sid[q];
-        if (j == i) continue;
-        double dx = min_image(spos[3 * (int64_t)q] - xi, g, 0);
-        double dy = min_image(spos[3 * (int64_t)q + 1] - yi, g, 1);
-        double dz = min_image(spos[3 * (int64_t)q + 2] - zi, g, 2);
-        double xx = dx * dx, yy = dy * dy, zz = dz * dz;
-        double d2 = (xx + yy) + zz;
-        found++;
-        if (d2 < kd[KN - 1] || (d2 == kd[KN - 1] && j < kj[KN - 1])) topk_insert<KN>(kd, kj, kq, d2, j, q);
-    }
-}
-
-// Is the block of offsets [lo, hi] per axis a certificate for the current
-// K-th distance?  all = the block covers every cell.
-__device__ inline bool certified(const Grid &g, const int (&cc)[3], const double (&u)[3], const int (&lo)[3],
-                                 const int (&hi)[3], int found, int KN, double kth, bool &all) {
+// Radius around the atom that the block of cells with offsets [lo, hi] per
+// axis covers, less the margin (<= 0 if none; +inf, and all, when the block
+// holds every cell): an atom outside the block is at least that far away, so
+// K atoms strictly closer are a certificate that the block holds the K
+// nearest.
+__device__ inline double block_reach(const Grid &g, const int (&cc)[3], const double (&u)[3], const int (&lo)[3],
+                                     const int (&hi)[3], bool &all) {
     double dmin = INFINITY;
     all = true;
     for (int a = 0; a < 3; a++) {
@@ -312,9 +292,7 @@ __device__ inline bool certified(const Grid &g, const int (&cc)[3], const double
         if (!sat_hi) dmin = fmin(dmin, (cc[a] + hi[a] + 1) * g.h[a] - u[a]);
         all = all && sat_lo && sat_hi;
     }
-    if (all) return true;
-    dmin -= g.margin;
-    return found >= KN && dmin > 0 && kth < dmin * dmin;
+    return dmin - g.margin;
 }
 
 // Sec. 5 samples are periodic.  Every image of an atom other than its
@@ -333,74 +311,15 @@ __device__ inline bool shell_exceeds_box(const Grid &g, int cnt, int K, double k
     return periodic && (cnt < K || bad);
 }
 
-// Write the K nearest neighbours of sorted atom p: ids and
-// minimum-image vectors in the component-major layout the hull kernels read.
-// spos[3q .. 3q+2] is a copy of pos[3 sid[q] ..], so the vectors are those of the input.
-template <int KN>
-__device__ inline void write_knn(int64_t n, int64_t p, int cnt, const int32_t (&kq)[KN], const Grid &g,
-                                 double xi, double yi, double zi, const double *__restrict__ spos,
-                                 const int32_t *__restrict__ sid, int32_t *__restrict__ nbr_id,
-                                 double *__restrict__ nbr_rel) {
-#pragma unroll
-    for (int m = 0; m < KN; m++) {
-        int32_t j = -1;
-        double r0 = 0, r1 = 0, r2 = 0;
-        if (m < cnt) {
-            int32_t q = kq[m];
-            j = sid[q];
-            r0 = min_image(spos[3 * (int64_t)q] - xi, g, 0);
-            r1 = min_image(spos[3 * (int64_t)q + 1] - yi, g, 1);
-            r2 = min_image(spos[3 * (int64_t)q + 2] - zi, g, 2);
-        }
-        nbr_id[(int64_t)m * n + p] = j;
-        nbr_rel[((int64_t)m * 3 + 0) * n + p] = r0;
-        nbr_rel[((int64_t)m * 3 + 1) * n + p] = r1;
-        nbr_rel[((int64_t)m * 3 + 2) * n + p] = r2;
-    }
+// LDS written by some lanes of a wave and then read by others of the same
+// wave: a wave's LDS instructions complete in issue order, so the only
+// requirement is that the compiler keeps them on their side of this point.
+__device__ inline void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Packed search key of a candidate: high word = FP32 rounding of d^2 (its
-// bit pattern, offset by 2^20 so that the word read as the high half of an
-// FP64 number is a normal, finite value), low word = sorted index q.  Keys
-// compare as FP64 numbers in the order (round(d^2), q); rounding to nearest
-// is monotone, so round(a) < round(b) implies a < b.
-__device__ inline double pack_key(double d2, int32_t q) {
-    uint32_t hi = __float_as_uint(__double2float_rn(d2)) + 0x00100000u;
-    return __hiloint2double((int)hi, q);
-}
-__device__ inline uint32_t key_hi(double k) { return (uint32_t)__double2hiint(k); }
-__device__ inline int32_t key_q(double k) { return __double2loint(k); }
-// upper bound of every d^2 whose rounding gives the key's high word
-// (relative error 2^-24 of a normal float, absolute 2^-150 of a subnormal)
-__device__ inline double key_d2_upper(double k) {
-    return (double)__uint_as_float(key_hi(k) - 0x00100000u) * (1.0 + 0x1p-22) + 0x1p-148;
-}
-
-// One step of the insertion: (a, t) <- (min(a, t), max(a, t)).  Written as
-// two VALU instructions that update a in place: the keys are finite, normal
-// FP64 numbers (no NaN, no denormal), for which the instructions return one
-// of their operands unchanged, and keeping each list entry in one register
-// avoids copies of the whole list on every loop iteration.
-__device__ inline void minmax_step(double &a, double &t) {
-    double hi;
-    asm("v_max_f64 %0, %1, %2\n\tv_min_f64 %1, %1, %2" : "=&v"(hi), "+v"(a) : "v"(t));
-    t = hi;
-}
-
-
-// Fast search: the 5x5x5 block of cells around the atom, walked as 25
-// x-rows nearest-first.  A row of cells is one contiguous range of the
-// sorted atoms (two if it wraps), and each lane walks its ranges in one flat
-// loop, so a wave pays about the per-lane candidate count rather than the
-// per-cell maximum.  The running list holds the 15 smallest packed keys,
-// kept by a branch-free min/max insertion.  Once 14 keys are known, rows and
-// the x-extent of each row are trimmed to an upper bound of the current 14th
-// distance.  The result is accepted when it is provably the exact ordered
-// (d^2, id) list: the high words of the 15 keys strictly increase (then the
-// rounded order is the exact order and no atom outside ties with the 14th)
-// and the exact 14th distance is certified by the block.  Other atoms are
-// appended to a list for k_knn_exact.  Requires every periodic axis to have
-// at least 5 cells (no axis wraps onto itself within the block).
 // Workgroups are dispatched to the 8 XCDs round-robin, and each XCD has its
 // own L2.  With a grid padded to a multiple of 8, this bijection gives every
 // XCD one contiguous range of blocks, so that blocks sharing cells (and
@@ -412,328 +331,515 @@ __device__ inline int64_t xcd_block(int64_t i, int64_t nblocks_padded) {
 }
 inline int64_t xcd_pad(int64_t nblocks) { return (nblocks + NXCD - 1) / NXCD * NXCD; }
 
+// Fast search, one lane per atom: the 5x5x5 block of cells around it, as 25
+// x-rows nearest-first (a row of cells is one contiguous range of the sorted
+// atoms, two if it wraps).
+//
+// What bounds it: vector instructions (busy 73 % of the time on a 0.92 M-atom
+// frame), and in frames beyond the caches the latency of its loads (47 % busy
+// at 31.7 M atoms).  Candidates are read as 16-byte records of fixed-point
+// coordinates, whose 32-bit differences are minimum images without any shift
+// and which are converted to FP32 (half the cost of an FP64 operation); FP64
+// positions are read for the neighbours found only, where 24-byte FP64
+// records of every candidate had to come before.  31.7 M atoms: 13.4 ms with
+// FP64 records, 64-bit keys and rows plane after plane; 12.2 with this search;
+// 10.3 with it and the tiled order of rows (cell_row).  0.92 M atoms: 345 ->
+// 285 us.
+//
+// A candidate is ranked by one 32-bit key: the upper 21 bits are d^2 on a
+// linear grid (buckets of 1 / (2^21 - 16) of the squared radius the block
+// certifies, farther atoms in the last bucket), the lower 11 name the
+// candidate (range of atoms, offset in it).  The list keeps the 19 smallest
+// keys: inserting t into a sorted list is a[m] = median(a[m - 1], a[m], t),
+// one independent instruction per entry, where the pair (min, max) on 64-bit
+// keys that it replaces took two dependent ones per entry, on two registers
+// each.
+//
+// The ranges come first, in loops over rows that are uniform over the wave
+// (their offsets are scalars): nine inner rows, their atoms, then the sixteen
+// outer rows and the cells that the Kth distance found so far leaves, and
+// their atoms.  Each lane then walks its own list of ranges, kept in LDS, two
+// atoms per step, so that a wave pays about the per-lane atom count.
+//
+// Two atoms whose buckets differ by `apart` or more are in the exact order
+// (the rounding of the coordinates, of d^2 and of the buckets is covered).
+// Where neighbouring entries are closer, the exact (d^2, id) of the entries
+// decides; that covers exact ties inside the list too (the 12 + 6 neighbours
+// of a perfect FCC or HCP crystal end at entry 18).  The atoms left to
+// k_knn_exact are those whose Kth neighbour the block does not certify, whose
+// ties run past the list, or whose ranges do not fit the codes.  Requires
+// every periodic axis to have at least 5 cells (no axis wraps onto itself
+// within the block).
+constexpr int KNN_LIST = 19;    // list entries (both neighbour counts)
+constexpr int KNN_RANGES = 30;  // ranges of one atom (a 5-bit code), kept for the decoding
+constexpr int KNN_PENDING = 18; // ranges of one pass: nine rows that may wrap
+constexpr int KNN_OFF_BITS = 6; // offset within a range
+constexpr int KNN_CODE_BITS = 11;
+constexpr uint32_t KNN_BUCKETS = (1u << (32 - KNN_CODE_BITS)) - 16;
+static_assert(KNN_RANGES << KNN_OFF_BITS <= 1 << KNN_CODE_BITS, "range and offset fit the code");
+
+// W lanes: 138 bytes each (35,328 per block of 256: four blocks per CU)
+template <int W>
+struct KnnRanges {
+    uint32_t q0[KNN_RANGES][W];   // first atom
+    uint8_t cnt[KNN_PENDING][W];  // atoms
+};
+
+// the coordinates of sorted atom q's record (12 bytes: the id, unused, would
+// hold a register that the load in flight forbids to reuse)
+typedef int32_t int3v __attribute__((ext_vector_type(3)));
+__device__ inline int3v fixed_xyz(const int4 *__restrict__ sfix, int64_t q) {
+    return *reinterpret_cast<const int3v *>(sfix + q);
+}
+
+__device__ inline uint32_t med3_u32(uint32_t a, uint32_t b, uint32_t c) {
+    uint32_t r;
+    asm("v_med3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
 // NK = 14 neighbours (Euclidean ordering), or 18 (the input of the
-// topological ordering); the list holds NK + 1 keys, the last one certifies
-// the boundary.  One atom (lane); false: not certified, nothing written
-// (the exact search must take it).
-template <int NK>
-__device__ inline bool knn_fast_atom(int64_t p, int64_t n, const Grid &g, const double *__restrict__ spos,
-                                     const int32_t *__restrict__ sid, const int32_t *__restrict__ start,
-                                     int32_t *__restrict__ nbr_id, double *__restrict__ nbr_rel,
-                                     int32_t *__restrict__ box_fail) {
-    constexpr int KN = NK + 1;
+// topological ordering).  One atom (lane t of the W in S); false: left to the
+// exact search, nothing written.
+template <int NK, int W>
+__device__ inline bool knn_fast_atom(KnnRanges<W> &S, int t, int64_t p, int64_t n, const Grid &g,
+                                     const double *__restrict__ spos, const int4 *__restrict__ sfix,
+                                     const int32_t *__restrict__ start, int32_t *__restrict__ nbr_id,
+                                     double *__restrict__ nbr_rel, int32_t *__restrict__ box_fail) {
     const double xi = spos[3 * (int64_t)p], yi = spos[3 * (int64_t)p + 1], zi = spos[3 * (int64_t)p + 2];
     const double xs[3] = {xi, yi, zi};
+    const int4 own = sfix[p];
     int cc[3];
     double u[3];
     for (int a = 0; a < 3; a++) {
         cc[a] = cell_coord(xs[a], g, a);
         u[a] = wrapped(xs[a], g, a);
     }
-    const double INF = __longlong_as_double(0x7ff0000000000000ll);
-    double key[KN];
+    // squared radius within which the block is complete (bounded by the
+    // block's own extent when it holds every cell), and the bucket width
+    double rcap2;
+    {
+        const int lo[3] = {-2, -2, -2}, hi[3] = {2, 2, 2};
+        bool all;
+        const double reach = block_reach(g, cc, u, lo, hi, all);
+        const double ext2 = 9.0 * ((g.h[0] * g.h[0] + g.h[1] * g.h[1]) + g.h[2] * g.h[2]) * 1.001;
+        if (!(reach > 0)) return false;
+        rcap2 = all ? ext2 : fmin(reach * reach, ext2);
+        if (!(rcap2 > 1e-30 && rcap2 < 1e30)) return false;  // (beyond what FP32 resolves)
+    }
+    const double bucket = rcap2 / (double)KNN_BUCKETS;
+    // A bucket is off by the coordinates' rounding (fix_err in a difference
+    // vector, 2 r fix_err in d^2 = r^2 <= rcap2) and by FP32 (conversion,
+    // factor and product of each difference, twice in its square, then three
+    // roundings: 9 2^-24 of at most 2^21 buckets).  apart = one more than
+    // twice that, rounded up.
+    const double err = 2.1 * sqrt(rcap2) * g.fix_err / bucket + 1.15;
+    if (!(err < 256.0)) return false;  // a grid so long that its fixed point is too coarse
+    const int apart = 2 + (int)(2.0 * err);
+    // per-axis steps in units of a bucket's square root
+    const double root = 1.0 / sqrt(bucket);
+    const float wx = (float)(root / g.fix[0]), wy = (float)(root / g.fix[1]), wz = (float)(root / g.fix[2]);
+    // offset within the own cell, and the squared gaps to the cells at -2, -1,
+    // +1, +2 of x (less the margin and, in FP32, 4e-6 cells)
+    float f[3], h[3], slack[3];
+    for (int a = 0; a < 3; a++) {
+        f[a] = (float)(u[a] - cc[a] * g.h[a]);
+        h[a] = (float)g.h[a];
+        slack[a] = (float)g.margin + 4e-6f * h[a];
+    }
+    auto sqgap = [&](int a, float e) {
+        e = fmaxf(e - slack[a], 0.0f);
+        return e * e;
+    };
+    const float gx_m2 = sqgap(0, f[0] + h[0]), gx_m1 = sqgap(0, f[0]);
+    const float gx_p1 = sqgap(0, h[0] - f[0]), gx_p2 = sqgap(0, 2.0f * h[0] - f[0]);
+    const int nx = g.nc[0];
+
+    uint32_t key[KNN_LIST];
 #pragma unroll
-    for (int m = 0; m < KN; m++) key[m] = INF;
-    // known minimum-image shifts: every periodic coordinate in [0, L) and at
-    // least 7 cells per periodic axis, so a wrapped row is exactly one box
-    // length away and the shifted difference equals the minimum image
-    bool shifted = g.canonical != 0;
-    for (int a = 0; a < 3; a++) shifted = shifted && (!g.periodic[a] || g.nc[a] >= 7);
+    for (int m = 0; m < KNN_LIST; m++) key[m] = ~0u;
+    int nrange = 0;         // ranges kept so far
+    bool overflow = false;  // a range or offset that does not fit the codes
+    float cap = (float)rcap2 * 1.000001f;  // squared radius still to search
     // (dy + 2) + 5 (dz + 2) of the 25 rows by increasing dy^2 + dz^2, 5 bits each
     const uint64_t rows_lo = 0x013952440D13B56Cull;  // rows 0..11
     const uint64_t rows_hi = 0x0250171D4334BCB6ull;  // rows 12..23
-    const int row_last = 24;                          // row 24: (dy, dz) = (2, 2)
-    const int nx = g.nc[0];
-    int r = 0, q = 0, qend = 0, seg2_lo = 0, seg2_hi = -1;
-    double shx = 0, shy = 0, shz = 0, shx2 = 0;
-    int cyz = 0;
-    // Each iteration first moves to the next segment if the current one is
-    // exhausted, then takes at most one candidate; the insertion runs on
-    // every iteration (an empty step inserts +inf), and the loop exits only
-    // after it, so the list stays in the same registers across the loop.
-    bool more = true;
-    do {
-        if (q >= qend) {
-            if (seg2_lo <= seg2_hi) {  // second (wrapped) part of the row
-                q = start[cyz + seg2_lo];
-                qend = start[cyz + seg2_hi + 1];
-                shx = shx2;
-                seg2_hi = -1;
-            } else if (r < 25) {
-                int code = r < 12 ? (int)((rows_lo >> (5 * r)) & 31)
-                                  : (r < 24 ? (int)((rows_hi >> (5 * (r - 12))) & 31) : row_last);
-                r++;
-                int dz = code / 5 - 2, dy = code - 5 * (code / 5) - 2;
-                int cy = cc[1] + dy, cz = cc[2] + dz;
-                bool skip = false;
-                shy = shz = 0;
-                if (g.periodic[1]) {
-                    if (cy < 0) { cy += g.nc[1]; shy = g.L[1]; }
-                    else if (cy >= g.nc[1]) { cy -= g.nc[1]; shy = -g.L[1]; }
-                } else {
-                    skip = cy < 0 || cy >= g.nc[1];
-                }
-                if (g.periodic[2]) {
-                    if (cz < 0) { cz += g.nc[2]; shz = g.L[2]; }
-                    else if (cz >= g.nc[2]) { cz -= g.nc[2]; shz = -g.L[2]; }
-                } else {
-                    skip = skip || cz < 0 || cz >= g.nc[2];
-                }
-                int xlo = -2, xhi = 2;
-                if (!skip && key[NK - 1] != INF) {
-                    double ly = (cc[1] + dy) * g.h[1] - u[1], hy = ly + g.h[1];
-                    double lz = (cc[2] + dz) * g.h[2] - u[2], hz = lz + g.h[2];
-                    double gy = ly > 0 ? ly : (hy < 0 ? -hy : 0.0);
-                    double gz = lz > 0 ? lz : (hz < 0 ? -hz : 0.0);
-                    gy = gy > g.margin ? gy - g.margin : 0.0;
-                    gz = gz > g.margin ? gz - g.margin : 0.0;
-                    double rem = key_d2_upper(key[NK - 1]) - (gy * gy + gz * gz);
-                    if (rem < 0) {
-                        skip = true;
-                    } else {
-                        // cells whose x-gap less the margin exceeds sqrt(rem)
-                        // cannot hold a better neighbour (compared squared)
-                        const double x0 = u[0] - cc[0] * g.h[0];  // offset of the atom inside its cell
-                        auto beyond = [&](double gap) {
-                            const double e = gap - g.margin;
-                            return e > 0 && e * e > rem;
-                        };
-                        while (xlo < 0 && beyond((-xlo - 1) * g.h[0] + x0)) xlo++;
-                        while (xhi > 0 && beyond((xhi - 1) * g.h[0] + (g.h[0] - x0))) xhi--;
-                    }
-                }
-                cyz = (cz * g.nc[1] + cy) * nx;
-                int a0 = cc[0] + xlo, a1 = cc[0] + xhi;
-                seg2_hi = -1;
-                if (g.periodic[0]) {
-                    if (a0 < 0) {  // wrapped part [a0 + nx, nx - 1] lies one box length up
-                        seg2_lo = a0 + nx;
-                        seg2_hi = nx - 1;
-                        shx2 = g.L[0];
-                        a0 = 0;
-                    } else if (a1 >= nx) {
-                        seg2_lo = 0;
-                        seg2_hi = a1 - nx;
-                        shx2 = -g.L[0];
-                        a1 = nx - 1;
-                    }
-                } else {
-                    a0 = max(a0, 0);
-                    a1 = min(a1, nx - 1);
-                    skip = skip || a0 > a1;
-                }
-                if (skip) {
-                    q = qend = 0;
-                    seg2_hi = -1;
-                } else {
-                    q = start[cyz + a0];
-                    qend = start[cyz + a1 + 1];
-                }
-                shx = 0;
-            } else {
-                more = false;
+#pragma unroll 1
+    for (int pass = 0; pass < 2; pass++) {
+        const int r0 = pass ? 9 : 0, r1 = pass ? 25 : 9;
+        const int base = nrange;
+        int npend = 0;
+        auto add = [&](int c0, int c1) {
+            const int32_t q0 = start[c0], cnt = start[c1 + 1] - q0;
+            if (cnt <= 0) return;
+            if (cnt >= (1 << KNN_OFF_BITS) || nrange == KNN_RANGES || npend == KNN_PENDING) {
+                overflow = true;
+                return;
+            }
+            S.q0[nrange++][t] = (uint32_t)q0;
+            S.cnt[npend++][t] = (uint8_t)cnt;
+        };
+        for (int r = r0; r < r1; r++) {
+            const int code = r < 12 ? (int)((rows_lo >> (5 * r)) & 31)
+                                    : (r < 24 ? (int)((rows_hi >> (5 * (r - 12))) & 31) : 24);
+            const int dz = code / 5 - 2, dy = code - 5 * (code / 5) - 2;
+            int cy = cc[1] + dy, cz = cc[2] + dz;
+            const bool out = (!g.periodic[1] && (cy < 0 || cy >= g.nc[1])) ||
+                             (!g.periodic[2] && (cz < 0 || cz >= g.nc[2]));
+            cy = cy < 0 ? cy + g.nc[1] : (cy >= g.nc[1] ? cy - g.nc[1] : cy);
+            cz = cz < 0 ? cz + g.nc[2] : (cz >= g.nc[2] ? cz - g.nc[2] : cz);
+            const float gy2 = dy == 0 ? 0.0f : sqgap(1, dy > 0 ? (float)dy * h[1] - f[1] : f[1] - (float)(dy + 1) * h[1]);
+            const float gz2 = dz == 0 ? 0.0f : sqgap(2, dz > 0 ? (float)dz * h[2] - f[2] : f[2] - (float)(dz + 1) * h[2]);
+            const float rem = cap - (gy2 + gz2);
+            if (out || rem < 0) continue;
+            // cells whose x-gap exceeds what is left cannot hold a better neighbour
+            const int a0 = cc[0] - (gx_m1 <= rem) - (gx_m2 <= rem), a1 = cc[0] + (gx_p1 <= rem) + (gx_p2 <= rem);
+            const int cyz = cell_row(g, cy, cz) * nx;
+            add(cyz + max(a0, 0), cyz + min(a1, nx - 1));
+            if (g.periodic[0]) {  // the part across the box edge
+                if (a0 < 0) add(cyz + a0 + nx, cyz + nx - 1);
+                else if (a1 >= nx) add(cyz, cyz + a1 - nx);
             }
         }
-        // up to two candidates per step: their loads are independent, so the
-        // second one's latency hides behind the first's
-        double t = INF, t2 = INF;
-        if (q < qend) {
-            const bool two = q + 1 < qend;
-            const int q2 = two ? q + 1 : q;  // (a repeated, in-bounds load when there is no second)
-            const double ax = spos[3 * (int64_t)q], ay = spos[3 * (int64_t)q + 1], az = spos[3 * (int64_t)q + 2];
-            const double bx = spos[3 * (int64_t)q2], by = spos[3 * (int64_t)q2 + 1], bz = spos[3 * (int64_t)q2 + 2];
-            double dx, dy, dz, ex, ey, ez;
-            if (shifted) {
-                dx = (ax - xi) - shx;
-                dy = (ay - yi) - shy;
-                dz = (az - zi) - shz;
-                ex = (bx - xi) - shx;
-                ey = (by - yi) - shy;
-                ez = (bz - zi) - shz;
-            } else {
-                dx = min_image(ax - xi, g, 0);
-                dy = min_image(ay - yi, g, 1);
-                dz = min_image(az - zi, g, 2);
-                ex = min_image(bx - xi, g, 0);
-                ey = min_image(by - yi, g, 1);
-                ez = min_image(bz - zi, g, 2);
+        // the atoms of the ranges, two per step; the next step's are loaded
+        // before this one's are used
+        int k = 0, q = 0, qend = 0;
+        uint32_t code = 0;  // code of atom q less q
+        auto fetch = [&](int3v &A, int3v &B, uint32_t &ca, uint32_t &cb) {
+            const bool any = q < qend || k < npend;
+            if (q >= qend && k < npend) {
+                q = (int)S.q0[base + k][t];
+                qend = q + (int)S.cnt[k][t];
+                code = ((uint32_t)(base + k) << KNN_OFF_BITS) - (uint32_t)q;
+                k++;
             }
-            const double xx = dx * dx, yy = dy * dy, zz = dz * dz;
-            const double d2 = (xx + yy) + zz;
-            const double xx2 = ex * ex, yy2 = ey * ey, zz2 = ez * ez;
-            const double e2 = (xx2 + yy2) + zz2;
-            if (q != (int)p) t = pack_key(d2, q);
-            if (two && q2 != (int)p) t2 = pack_key(e2, q2);
-            q += two ? 2 : 1;
-        }
-        // the two insertions interleaved, the second one step behind the
-        // first (step m of the second reads key[m] after step m of the
-        // first): two independent dependency chains instead of one of twice
-        // the length, with the result of inserting t, then t2
-        minmax_step(key[0], t);
+            // loads without a branch (the atom itself where there is none),
+            // so that they can stay in flight
+            const bool one = q < qend, two = q + 1 < qend;
+            const int qa = one ? q : (int)p, qb = two ? q + 1 : (int)p;
+            A = fixed_xyz(sfix, qa);
+            B = fixed_xyz(sfix, qb);
+            ca = qa == (int)p ? ~0u : code + (uint32_t)qa;
+            cb = qb == (int)p ? ~0u : code + (uint32_t)qb;
+            q += 2;
+            return any;
+        };
+        auto rank = [&](const int3v &A, const int3v &B, uint32_t ca, uint32_t cb) {
+            const float dx = (float)(int32_t)((uint32_t)A.x - (uint32_t)own.x) * wx;
+            const float dy = (float)(int32_t)((uint32_t)A.y - (uint32_t)own.y) * wy;
+            const float dz = (float)(int32_t)((uint32_t)A.z - (uint32_t)own.z) * wz;
+            const float ex = (float)(int32_t)((uint32_t)B.x - (uint32_t)own.x) * wx;
+            const float ey = (float)(int32_t)((uint32_t)B.y - (uint32_t)own.y) * wy;
+            const float ez = (float)(int32_t)((uint32_t)B.z - (uint32_t)own.z) * wz;
+            const float d2 = fmaf(dz, dz, fmaf(dy, dy, dx * dx)), e2 = fmaf(ez, ez, fmaf(ey, ey, ex * ex));
+            const uint32_t b1 = (uint32_t)fminf(d2, (float)(KNN_BUCKETS + 8));
+            const uint32_t b2 = (uint32_t)fminf(e2, (float)(KNN_BUCKETS + 8));
+            const uint32_t t1 = ca == ~0u ? ~0u : (b1 << KNN_CODE_BITS) + ca;
+            const uint32_t t2 = cb == ~0u ? ~0u : (b2 << KNN_CODE_BITS) + cb;
 #pragma unroll
-        for (int m = 1; m < KN; m++) {
-            minmax_step(key[m], t);
-            minmax_step(key[m - 1], t2);
-        }
-        minmax_step(key[KN - 1], t2);
-    } while (more);
-    bool ok = key[NK - 1] != INF;
+            for (int m = KNN_LIST - 1; m > 0; m--) key[m] = med3_u32(key[m - 1], key[m], t1);
+            key[0] = min(key[0], t1);
 #pragma unroll
-    for (int m = 0; m < KN - 1; m++) ok = ok && key_hi(key[m]) < key_hi(key[m + 1]);
-    int32_t kq[NK];
-#pragma unroll
-    for (int m = 0; m < NK; m++) kq[m] = key_q(key[m]);
-    if (ok) {
-        // certified on the key's upper bound of the K-th distance, so the
-        // K-th neighbour's position is read only when the box check needs
-        // the exact distance
-        const double kth_up = key_d2_upper(key[NK - 1]);
-        int lo[3] = {-2, -2, -2}, hi[3] = {2, 2, 2};
-        bool all;
-        ok = certified(g, cc, u, lo, hi, NK, NK, kth_up, all);
-        if (ok && shell_exceeds_box(g, NK, NK, kth_up)) {
-            const int32_t q13 = kq[NK - 1];
-            const double ex = min_image(spos[3 * (int64_t)q13] - xi, g, 0);
-            const double ey = min_image(spos[3 * (int64_t)q13 + 1] - yi, g, 1);
-            const double ez = min_image(spos[3 * (int64_t)q13 + 2] - zi, g, 2);
-            if (shell_exceeds_box(g, NK, NK, (ex * ex + ey * ey) + ez * ez)) atomicOr(box_fail, 1);
+            for (int m = KNN_LIST - 1; m > 0; m--) key[m] = med3_u32(key[m - 1], key[m], t2);
+            key[0] = min(key[0], t2);
+        };
+        // two steps per turn, each step's loads issued before the step
+        // before it is ranked (the barriers keep the compiler from moving
+        // them down to their use)
+        int3v A0, B0, A1, B1;
+        uint32_t ca0, cb0, ca1, cb1;
+        bool more = fetch(A0, B0, ca0, cb0);
+        while (more) {
+            more = fetch(A1, B1, ca1, cb1);
+            __builtin_amdgcn_sched_barrier(0);
+            rank(A0, B0, ca0, cb0);
+            if (!more) break;
+            more = fetch(A0, B0, ca0, cb0);
+            __builtin_amdgcn_sched_barrier(0);
+            rank(A1, B1, ca1, cb1);
         }
+        // an upper bound of the Kth distance found so far
+        cap = fminf(cap, (float)((key[NK - 1] >> KNN_CODE_BITS) + (uint32_t)apart) * ((float)bucket * 1.000001f));
     }
-    if (!ok) return false;
-    write_knn<NK>(n, p, NK, kq, g, xi, yi, zi, spos, sid, nbr_id, nbr_rel);
+    if (overflow) return false;
+
+    auto bk = [&](int m) { return (int)(key[m] >> KNN_CODE_BITS); };
+    // entries to put in order: past NK as long as the next one could come before the last
+    int cnt = NK;
+#pragma unroll
+    for (int m = NK; m < KNN_LIST; m++)
+        if (cnt == m && bk(m) - bk(m - 1) < apart) cnt = m + 1;
+    bool close = cnt > NK;
+#pragma unroll
+    for (int m = 1; m < NK; m++) close = close || bk(m) - bk(m - 1) < apart;
+    int last = bk(NK - 1);  // bucket of the last entry that matters
+#pragma unroll
+    for (int m = NK; m < KNN_LIST; m++) last = m < cnt ? bk(m) : last;
+    if (cnt == KNN_LIST || last + apart >= (int)KNN_BUCKETS) return false;
+
+    int32_t kq[KNN_LIST];
+#pragma unroll
+    for (int m = 0; m < KNN_LIST; m++) {
+        const uint32_t code = key[m] & ((1u << KNN_CODE_BITS) - 1);
+        kq[m] = m < cnt ? (int32_t)(S.q0[code >> KNN_OFF_BITS][t] + (code & ((1u << KNN_OFF_BITS) - 1))) : 0;
+    }
+    if (close) {
+        // exact (d^2, id) order of the first cnt entries: odd-even exchanges
+        // until none is left to make
+        double ed[KNN_LIST];
+        int32_t ej[KNN_LIST];
+#pragma unroll
+        for (int m = 0; m < KNN_LIST; m++) {
+            ed[m] = INFINITY;
+            ej[m] = 0x7fffffff;
+            if (m < cnt) {
+                const int64_t q = kq[m];
+                const double dx = min_image(spos[3 * q] - xi, g, 0), dy = min_image(spos[3 * q + 1] - yi, g, 1);
+                const double dz = min_image(spos[3 * q + 2] - zi, g, 2);
+                ed[m] = (dx * dx + dy * dy) + dz * dz;
+                ej[m] = sfix[q].w;
+            }
+        }
+        bool moved;
+        do {
+            moved = false;
+#pragma unroll
+            for (int o = 1; o >= 0; o--)
+#pragma unroll
+                for (int m = o; m + 1 < KNN_LIST; m += 2) {
+                    const bool sw = ed[m + 1] < ed[m] || (ed[m + 1] == ed[m] && ej[m + 1] < ej[m]);
+                    const double td = ed[m];
+                    const int32_t tj = ej[m], tq = kq[m];
+                    ed[m] = sw ? ed[m + 1] : td;
+                    ej[m] = sw ? ej[m + 1] : tj;
+                    kq[m] = sw ? kq[m + 1] : tq;
+                    ed[m + 1] = sw ? td : ed[m + 1];
+                    ej[m + 1] = sw ? tj : ej[m + 1];
+                    kq[m + 1] = sw ? tq : kq[m + 1];
+                    moved = moved || sw;
+                }
+        } while (moved);
+    }
+    // the exact Kth distance only where its upper bound does not pass the box check
+    if (shell_exceeds_box(g, NK, NK, (double)(bk(NK - 1) + apart) * bucket)) {
+        const int64_t qk = kq[NK - 1];
+        const double ex = min_image(spos[3 * qk] - xi, g, 0);
+        const double ey = min_image(spos[3 * qk + 1] - yi, g, 1);
+        const double ez = min_image(spos[3 * qk + 2] - zi, g, 2);
+        if (shell_exceeds_box(g, NK, NK, (ex * ex + ey * ey) + ez * ez)) atomicOr(box_fail, 1);
+    }
+    // Ids and minimum-image vectors in the component-major layout the hull
+    // kernels read (spos[3q .. 3q+2] is a copy of the input's position, so the
+    // vectors are those of the input).  With every periodic coordinate in [0,
+    // L) and at least 7 cells per axis, atoms of a block that does not wrap
+    // lie less than half a box length apart and need no shift.
+    bool plain = g.canonical != 0;
+    for (int a = 0; a < 3; a++)
+        plain = plain && (!g.periodic[a] || (g.nc[a] >= 7 && cc[a] >= 2 && cc[a] + 2 < g.nc[a]));
+    const bool shifts = __ballot(!plain) != 0;
+#pragma unroll
+    for (int m = 0; m < NK; m++) {
+        const int64_t q = kq[m];
+        double dx = spos[3 * q] - xi, dy = spos[3 * q + 1] - yi, dz = spos[3 * q + 2] - zi;
+        if (shifts) {
+            dx = min_image(dx, g, 0);
+            dy = min_image(dy, g, 1);
+            dz = min_image(dz, g, 2);
+        }
+        nbr_id[(int64_t)m * n + p] = sfix[q].w;
+        nbr_rel[((int64_t)m * 3 + 0) * n + p] = dx;
+        nbr_rel[((int64_t)m * 3 + 1) * n + p] = dy;
+        nbr_rel[((int64_t)m * 3 + 2) * n + p] = dz;
+    }
     return true;
 }
 
 template <int NK>
-__global__ void __launch_bounds__(256) k_knn_fast(int64_t n, Grid g, const double *__restrict__ spos,
-                                                  const int32_t *__restrict__ sid, const int32_t *__restrict__ start,
+__global__ void __launch_bounds__(256, 4) k_knn_fast(int64_t n, Grid g, const double *__restrict__ spos,
+                                                  const int4 *__restrict__ sfix, const int32_t *__restrict__ start,
                                                   int32_t *__restrict__ nbr_id, double *__restrict__ nbr_rel,
                                                   int32_t *__restrict__ todo, int32_t *__restrict__ todo_count,
                                                   int32_t *__restrict__ box_fail) {
+    __shared__ KnnRanges<256> S;
     int64_t p = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
     if (p >= n) return;
-    if (!knn_fast_atom<NK>(p, n, g, spos, sid, start, nbr_id, nbr_rel, box_fail))
+    if (!knn_fast_atom<NK, 256>(S, (int)threadIdx.x, p, n, g, spos, sfix, start, nbr_id, nbr_rel, box_fail))
         todo[atomicAdd(todo_count, 1)] = (int32_t)p;
 }
 
 // Exact search for the atoms the fast search left (or all atoms when todo
-// is NULL), one wavefront per atom.  The lanes share the cells of the block
-// of shells 0..2 (then of each further shell) and keep private lists
-// ordered by the exact key (d^2, id); a 14-round wave-wide merge of the list
-// heads gives the atom's ordered neighbours, and the shells grow until the
-// searched block certifies the 14th distance.  A wave per atom keeps the
-// latency of a few left-over atoms short: each lane scans one or two cells.
+// is NULL), one wavefront per atom.  Shells of cells are added until the
+// atoms strictly closer than the block's certified radius are K or more: only
+// those can be among the K nearest.  A lane takes a row of cells, an
+// exclusive scan of the rows' atom counts numbers the block's atoms, and each
+// lane then finds its atoms' rows by bisection, so that all positions of the
+// block are in flight at once.  The atoms within the radius go to a list in
+// LDS; when it fills up it is cut to the K best, whose last then bounds the
+// rest.  An atom's place in the order is the number of list entries before it
+// by (d^2, id).  (Private sorted lists per lane merged by K rounds of
+// wave-wide minima took 207 us where this takes 86 on the 0.92 M-atom
+// polycrystal.)
+constexpr int KNN_CAND = 256;  // list entries
+struct KnnWave {
+    double d2[KNN_CAND];
+    int32_t id[KNN_CAND], q[KNN_CAND];
+    int32_t pre[64], qa[64], la[64], qb[64];
+};
+
+// sorts the first count entries of the list's K best to its front (whole
+// wave); returns the entries left
+template <int K>
+__device__ inline int knn_cut(KnnWave &S, int count) {
+    const int lane = threadIdx.x & 63;
+    double d[KNN_CAND / 64];
+    int32_t j[KNN_CAND / 64], q[KNN_CAND / 64], rank[KNN_CAND / 64];
+    wave_lds_sync();
+#pragma unroll
+    for (int b = 0; b < KNN_CAND / 64; b++) {
+        rank[b] = K;
+        const int e = 64 * b + lane;
+        if (64 * b >= count) continue;
+        d[b] = e < count ? S.d2[e] : INFINITY;
+        j[b] = e < count ? S.id[e] : 0x7fffffff;
+        q[b] = e < count ? S.q[e] : 0;
+        int before = 0;
+        for (int c = 0; c < count; c++) {
+            const double dc = S.d2[c];
+            before += dc < d[b] || (dc == d[b] && S.id[c] < j[b]);
+        }
+        rank[b] = e < count ? before : K;
+    }
+    wave_lds_sync();
+#pragma unroll
+    for (int b = 0; b < KNN_CAND / 64; b++)
+        if (rank[b] < K) {
+            S.d2[rank[b]] = d[b];
+            S.id[rank[b]] = j[b];
+            S.q[rank[b]] = q[b];
+        }
+    wave_lds_sync();
+    return min(count, K);
+}
+
 // One atom p (wave-uniform) by the whole wave.
 template <int NK>
-__device__ void knn_exact_atom(int64_t p, int64_t n, const Grid &g, const double *__restrict__ spos,
+__device__ void knn_exact_atom(KnnWave &S, int64_t p, int64_t n, const Grid &g, const double *__restrict__ spos,
                                const int32_t *__restrict__ sid, const int32_t *__restrict__ start,
                                int32_t *__restrict__ nbr_id, double *__restrict__ nbr_rel,
                                int32_t *__restrict__ box_fail) {
-    constexpr int KN = NK;
     const int lane = threadIdx.x & 63;
-    {
-        const double xi = spos[3 * (int64_t)p], yi = spos[3 * (int64_t)p + 1], zi = spos[3 * (int64_t)p + 2];
-        const int32_t i = sid[p];
-        const double xs[3] = {xi, yi, zi};
-        int cc[3];
-        double u[3];
-        for (int a = 0; a < 3; a++) {
-            cc[a] = cell_coord(xs[a], g, a);
-            u[a] = wrapped(xs[a], g, a);
-        }
-        double kd[KN];
-        int32_t kj[KN], kq[KN];
-#pragma unroll
-        for (int m = 0; m < KN; m++) { kd[m] = INFINITY; kj[m] = 0x7fffffff; kq[m] = 0; }
-        int found = 0;
-        // merged result: lane m < KN holds entry m
-        double rd = INFINITY;
-        int32_t rj = -1, rq = 0;
-        int total = 0;
-        double kth = INFINITY;
-        int plo[3] = {1, 1, 1}, phi[3] = {0, 0, 0};  // block already searched (empty)
-        for (int s = 2;; s++) {
-            int lo[3], hi[3], ext[3];
-            for (int a = 0; a < 3; a++) {
-                shell_range(g, a, s, lo[a], hi[a]);
-                ext[a] = hi[a] - lo[a] + 1;
-            }
-            const int ncell = ext[0] * ext[1] * ext[2];
-            for (int c = lane; c < ncell; c += 64) {
-                int ox = lo[0] + c % ext[0];
-                int oy = lo[1] + (c / ext[0]) % ext[1];
-                int oz = lo[2] + c / (ext[0] * ext[1]);
-                bool inner = ox >= plo[0] && ox <= phi[0] && oy >= plo[1] && oy <= phi[1] && oz >= plo[2] &&
-                             oz <= phi[2];
-                if (inner) continue;
-                int cx = cc[0] + ox, cy = cc[1] + oy, cz = cc[2] + oz;
-                if (g.periodic[0]) cx = (cx % g.nc[0] + g.nc[0]) % g.nc[0];
-                else if (cx < 0 || cx >= g.nc[0]) continue;
-                if (g.periodic[1]) cy = (cy % g.nc[1] + g.nc[1]) % g.nc[1];
-                else if (cy < 0 || cy >= g.nc[1]) continue;
-                if (g.periodic[2]) cz = (cz % g.nc[2] + g.nc[2]) % g.nc[2];
-                else if (cz < 0 || cz >= g.nc[2]) continue;
-                scan_cell<KN>((cz * g.nc[1] + cy) * g.nc[0] + cx, g, xi, yi, zi, i, spos, sid, start, kd, kj,
-                              kq, found);
-            }
-            // wave-wide merge of the list heads, smallest (d^2, id) first
-            total = found;
-            for (int off = 32; off > 0; off >>= 1) total += __shfl_xor(total, off);
-#pragma unroll 1
-            for (int m = 0; m < KN; m++) {
-                double bd = kd[0];
-                int32_t bj = kj[0];
-                for (int off = 32; off > 0; off >>= 1) {
-                    double od = __shfl_xor(bd, off);
-                    int32_t oj = __shfl_xor(bj, off);
-                    if (od < bd || (od == bd && oj < bj)) { bd = od; bj = oj; }
-                }
-                if (bd == INFINITY) break;  // every list is empty
-                bool mine = kd[0] == bd && kj[0] == bj;
-                uint64_t who = __ballot(mine);
-                int src = __ffsll((unsigned long long)who) - 1;
-                int32_t bq = __shfl(kq[0], src);
-                if (lane == m) { rd = bd; rj = bj; rq = bq; }
-                if (mine) {  // pop the head
-#pragma unroll
-                    for (int t = 0; t < KN - 1; t++) { kd[t] = kd[t + 1]; kj[t] = kj[t + 1]; kq[t] = kq[t + 1]; }
-                    kd[KN - 1] = INFINITY;
-                    kj[KN - 1] = 0x7fffffff;
-                }
-            }
-            kth = __shfl(rd, KN - 1);
-            bool all;
-            bool done = certified(g, cc, u, lo, hi, total, KN, kth, all);
-            for (int a = 0; a < 3; a++) { plo[a] = lo[a]; phi[a] = hi[a]; }
-            if (done) break;
-            // the merged entries seed lane 0's list for the next shell
-#pragma unroll
-            for (int m = 0; m < KN; m++) {
-                double d = __shfl(rd, m);
-                int32_t j = __shfl(rj, m), q = __shfl(rq, m);
-                kd[m] = lane == 0 && j >= 0 ? d : INFINITY;
-                kj[m] = lane == 0 && j >= 0 ? j : 0x7fffffff;
-                kq[m] = q;
-            }
-            found = lane == 0 ? total : 0;
-        }
-        const int cnt = total < KN ? total : KN;
-        if (lane == 0 && shell_exceeds_box(g, cnt, KN, kth)) atomicOr(box_fail, 1);
-        if (lane < KN) {
-            int32_t j = lane < cnt ? rj : -1;
-            double r0 = 0, r1 = 0, r2 = 0;
-            if (lane < cnt) {
-                r0 = min_image(spos[3 * (int64_t)rq] - xi, g, 0);
-                r1 = min_image(spos[3 * (int64_t)rq + 1] - yi, g, 1);
-                r2 = min_image(spos[3 * (int64_t)rq + 2] - zi, g, 2);
-            }
-            nbr_id[(int64_t)lane * n + p] = j;
-            nbr_rel[((int64_t)lane * 3 + 0) * n + p] = r0;
-            nbr_rel[((int64_t)lane * 3 + 1) * n + p] = r1;
-            nbr_rel[((int64_t)lane * 3 + 2) * n + p] = r2;
-        }
+    const double xi = spos[3 * (int64_t)p], yi = spos[3 * (int64_t)p + 1], zi = spos[3 * (int64_t)p + 2];
+    const double xs[3] = {xi, yi, zi};
+    const int nx = g.nc[0];
+    int cc[3];
+    double u[3];
+    for (int a = 0; a < 3; a++) {
+        cc[a] = cell_coord(xs[a], g, a);
+        u[a] = wrapped(xs[a], g, a);
     }
+    int count = 0;
+    for (int s = 2;; s++) {
+        int lo[3], hi[3];
+        for (int a = 0; a < 3; a++) shell_range(g, a, s, lo[a], hi[a]);
+        bool all;
+        const double reach = block_reach(g, cc, u, lo, hi, all);
+        // kept: d^2 < thr, or d^2 <= thr once the list was cut
+        double thr = all ? INFINITY : (reach > 0 ? reach * reach : 0.0);
+        bool cut = all;
+        count = 0;
+        const int ey = hi[1] - lo[1] + 1, rows = ey * (hi[2] - lo[2] + 1);
+        for (int r0 = 0; r0 < rows; r0 += 64) {
+            int qa = 0, la = 0, qb = 0, lb = 0;
+            const int r = r0 + lane;
+            if (r < rows) {
+                int cy = cc[1] + lo[1] + r % ey, cz = cc[2] + lo[2] + r / ey;
+                bool in = true;
+                if (g.periodic[1]) cy = (cy % g.nc[1] + g.nc[1]) % g.nc[1];
+                else in = cy >= 0 && cy < g.nc[1];
+                if (g.periodic[2]) cz = (cz % g.nc[2] + g.nc[2]) % g.nc[2];
+                else in = in && cz >= 0 && cz < g.nc[2];
+                if (in) {
+                    const int cyz = cell_row(g, cy, cz) * nx;
+                    const int a0 = cc[0] + lo[0], a1 = cc[0] + hi[0];
+                    const int i0 = max(a0, 0), i1 = min(a1, nx - 1);
+                    qa = start[cyz + i0];
+                    la = start[cyz + i1 + 1] - qa;
+                    if (g.periodic[0] && (a0 < 0 || a1 >= nx)) {
+                        const int w0 = a0 < 0 ? a0 + nx : 0, w1 = a0 < 0 ? nx - 1 : a1 - nx;
+                        qb = start[cyz + w0];
+                        lb = start[cyz + w1 + 1] - qb;
+                    }
+                }
+            }
+            int incl = la + lb;
+            for (int d = 1; d < 64; d <<= 1) {
+                const int y = __shfl_up(incl, d);
+                if (lane >= d) incl += y;
+            }
+            const int total = __shfl(incl, 63);
+            S.pre[lane] = incl - (la + lb);
+            S.qa[lane] = qa;
+            S.la[lane] = la;
+            S.qb[lane] = qb;
+            wave_lds_sync();
+            for (int b = 0; b < total; b += 64) {
+                const int i = b + lane;
+                bool keep = false;
+                double d2 = 0;
+                int32_t q = 0;
+                if (i < total) {
+                    // the last row whose first atom is not past i (rows
+                    // without atoms share their number with the next)
+                    int row = 0;
+#pragma unroll
+                    for (int w = 32; w > 0; w >>= 1)
+                        if (S.pre[row + w] <= i) row += w;
+                    const int o = i - S.pre[row], l = S.la[row];
+                    q = o < l ? S.qa[row] + o : S.qb[row] + (o - l);
+                    const double dx = min_image(spos[3 * (int64_t)q] - xi, g, 0);
+                    const double dy = min_image(spos[3 * (int64_t)q + 1] - yi, g, 1);
+                    const double dz = min_image(spos[3 * (int64_t)q + 2] - zi, g, 2);
+                    d2 = (dx * dx + dy * dy) + dz * dz;
+                    keep = q != (int32_t)p && (d2 < thr || (cut && d2 == thr));
+                }
+                const uint64_t who = __ballot(keep);
+                if (keep) {
+                    const int at = count + __popcll(who & ((1ull << lane) - 1));
+                    S.d2[at] = d2;
+                    S.id[at] = sid[q];
+                    S.q[at] = q;
+                }
+                count += __popcll(who);
+                if (count > KNN_CAND - 64) {
+                    count = knn_cut<NK>(S, count);
+                    if (count == NK) {
+                        thr = S.d2[NK - 1];
+                        cut = true;
+                    }
+                }
+            }
+            wave_lds_sync();
+        }
+        if (count >= NK || all) break;
+    }
+    const int cnt = knn_cut<NK>(S, count);
+    if (lane == 0 && shell_exceeds_box(g, cnt, NK, cnt == NK ? S.d2[NK - 1] : INFINITY)) atomicOr(box_fail, 1);
+    if (lane < NK) {
+        int32_t j = -1;
+        double r0 = 0, r1 = 0, r2 = 0;
+        if (lane < cnt) {
+            j = S.id[lane];
+            const int64_t q = S.q[lane];
+            r0 = min_image(spos[3 * q] - xi, g, 0);
+            r1 = min_image(spos[3 * q + 1] - yi, g, 1);
+            r2 = min_image(spos[3 * q + 2] - zi, g, 2);
+        }
+        nbr_id[(int64_t)lane * n + p] = j;
+        nbr_rel[((int64_t)lane * 3 + 0) * n + p] = r0;
+        nbr_rel[((int64_t)lane * 3 + 1) * n + p] = r1;
+        nbr_rel[((int64_t)lane * 3 + 2) * n + p] = r2;
+    }
+    wave_lds_sync();  // the list is free for the wave's next atom
 }
 
 template <int NK>
@@ -743,10 +849,12 @@ __global__ void __launch_bounds__(256) k_knn_exact(int64_t n, Grid g, const doub
                                                    const int32_t *__restrict__ todo,
                                                    const int32_t *__restrict__ todo_count,
                                                    int32_t *__restrict__ box_fail) {
+    __shared__ KnnWave S[4];
     const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x >> 6);
     const int64_t cnt_todo = todo ? (int64_t)*todo_count : n;
     for (int64_t w = blockIdx.x * (int64_t)(blockDim.x >> 6) + (threadIdx.x >> 6); w < cnt_todo; w += nwaves)
-        knn_exact_atom<NK>(todo ? (int64_t)todo[w] : w, n, g, spos, sid, start, nbr_id, nbr_rel, box_fail);
+        knn_exact_atom<NK>(S[threadIdx.x >> 6], todo ? (int64_t)todo[w] : w, n, g, spos, sid, start, nbr_id, nbr_rel,
+                           box_fail);
 }
 
 // ------------------------------------------------- topological ordering
@@ -2175,15 +2283,6 @@ struct MatchLds {
     MatchWork<RT, NW> work;
 };
 
-// LDS written by some lanes of a wave and then read by others of the same
-// wave: a wave's LDS instructions complete in issue order, so the only
-// requirement is that the compiler keeps them on their side of this point.
-__device__ inline void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // one job: the candidate with tv of the atom at p, K neighbours, barycentre cb
 template <typename RT>
 __device__ inline void eval_job(int K, const double *__restrict__ nbr_rel, int64_t n, int64_t p,
@@ -2780,10 +2879,10 @@ void launch_cell_starts(const int32_t *count, int64_t cells, int32_t *bsum, int3
     hipLaunchKernelGGL(k_scan_cells, dim3((unsigned)items), dim3(SCAN_THREADS), 0, st, count, cells,
                        (const int32_t *)bsum, start);
 }
-void launch_bin_scatter(const double *pos, int64_t n, const int32_t *cell_of, const int32_t *slot_of,
-                        const int32_t *start, double *spos, int32_t *sid, hipStream_t st) {
-    hipLaunchKernelGGL(k_bin_scatter, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, pos, n, cell_of, slot_of,
-                       start, spos, sid);
+void launch_bin_scatter(const double *pos, int64_t n, const Grid &g, const int32_t *cell_of, const int32_t *slot_of,
+                        const int32_t *start, double *spos, int4 *sfix, int32_t *sid, hipStream_t st) {
+    hipLaunchKernelGGL(k_bin_scatter, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, pos, n, g, cell_of,
+                       slot_of, start, spos, sfix, sid);
 }
 bool knn_fast_applies(const Grid &g) {
     for (int a = 0; a < 3; a++)
@@ -2791,16 +2890,15 @@ bool knn_fast_applies(const Grid &g) {
     return true;
 }
 template <int NK>
-static void launch_knn_nk(int64_t n, const Grid &g, const double *spos,
+static void launch_knn_nk(int64_t n, const Grid &g, const double *spos, const int4 *sfix,
                           const int32_t *sid, const int32_t *start, int32_t *nbr_id, double *nbr_rel,
                           int32_t *todo, int32_t *todo_count, int32_t *box_fail, hipStream_t st) {
     int64_t blocks = (n + 255) / 256;
     if (knn_fast_applies(g)) {
-        hipLaunchKernelGGL(k_knn_fast<NK>, dim3((unsigned)xcd_pad(blocks)), dim3(256), 0, st, n, g, spos, sid,
+        hipLaunchKernelGGL(k_knn_fast<NK>, dim3((unsigned)xcd_pad(blocks)), dim3(256), 0, st, n, g, spos, sfix,
                            start, nbr_id, nbr_rel, todo, todo_count, box_fail);
-        // the atoms left over are few; 512 blocks of four waves (two per SIMD,
-        // what its registers allow) stride over them
-        hipLaunchKernelGGL(k_knn_exact<NK>, dim3((unsigned)std::min<int64_t>(blocks, 512)), dim3(256), 0, st, n, g,
+        // the atoms left over are few; at most 1024 blocks of four waves stride over them
+        hipLaunchKernelGGL(k_knn_exact<NK>, dim3((unsigned)std::min<int64_t>((n + 15) / 16, 1024)), dim3(256), 0, st, n, g,
                            spos, sid, start, nbr_id, nbr_rel, (const int32_t *)todo,
                            (const int32_t *)todo_count, box_fail);
     } else {
@@ -2809,13 +2907,13 @@ static void launch_knn_nk(int64_t n, const Grid &g, const double *spos,
                            (const int32_t *)nullptr, box_fail);
     }
 }
-void launch_knn(int64_t n, const Grid &g, int nk, const double *spos,
+void launch_knn(int64_t n, const Grid &g, int nk, const double *spos, const int4 *sfix,
                 const int32_t *sid, const int32_t *start, int32_t *nbr_id, double *nbr_rel, int32_t *todo,
                 int32_t *todo_count, int32_t *box_fail, hipStream_t st) {
     if (nk == VK)
-        launch_knn_nk<VK>(n, g, spos, sid, start, nbr_id, nbr_rel, todo, todo_count, box_fail, st);
+        launch_knn_nk<VK>(n, g, spos, sfix, sid, start, nbr_id, nbr_rel, todo, todo_count, box_fail, st);
     else
-        launch_knn_nk<KMAX>(n, g, spos, sid, start, nbr_id, nbr_rel, todo, todo_count, box_fail, st);
+        launch_knn_nk<KMAX>(n, g, spos, sfix, sid, start, nbr_id, nbr_rel, todo, todo_count, box_fail, st);
 }
 void launch_voronoi(int64_t n, const double *rel18, const int32_t *id18, uint32_t *vf, uint32_t *vlive,
                     double *nbr_rel, int32_t *nbr_id, const int32_t *box_fail, hipStream_t st) {
@@ -2907,6 +3005,7 @@ __device__ inline Grid make_grid_dev(const double (&box)[3], const double (&mn)[
         hmax = fmax(hmax, g.h[a]);
     }
     g.margin = 1e-9 * hmax;
+    set_fixed_scale(g, ext, mn, mx);
     g.canonical = 1;
     for (int a = 0; a < 3; a++)
         if (g.periodic[a] && !(mn[a] >= 0.0 && mx[a] < box[a])) g.canonical = 0;
@@ -2956,13 +3055,17 @@ __device__ inline long long wave_excl_scan(long long v, long long &total) {
 
 template <typename RT>
 union ServeWork {
+    KnnRanges<64> ranges;
+    KnnWave knn;
     TopoShared topo;
     MatchWork<RT, 1> mw;
 };
 
 // k-NN stage item: the fast search lane by lane, the exact one for what it
-// leaves, a wave per atom (a call of its own: its registers apart)
-__device__ __noinline__ void serve_knn(ServeSlot &S, int64_t r) {
+// leaves, a wave per atom (a call of its own: its registers apart; its LDS as
+// LDS pointers, see serve_match)
+__device__ __noinline__ void serve_knn(__attribute__((address_space(3))) KnnRanges<64> *Rp,
+                                       __attribute__((address_space(3))) KnnWave *Wp, ServeSlot &S, int64_t r) {
     const int lane = threadIdx.x & 63;
     // the grid and the arrays in registers: the searches' stores cannot
     // alias them
@@ -2970,6 +3073,7 @@ __device__ __noinline__ void serve_knn(ServeSlot &S, int64_t r) {
     const int64_t n = S.r.n;
     const bool fast = S.fast;
     const double *spos = S.r.spos;
+    const int4 *sfix = S.r.sfix;
     const int32_t *sid = S.r.sid, *start = S.r.count;
     int32_t *nbr_id = S.r.nbr_id;
     double *nbr_rel = S.r.nbr_rel;
@@ -2978,12 +3082,15 @@ __device__ __noinline__ void serve_knn(ServeSlot &S, int64_t r) {
     for (int64_t sub = b; sub < e; sub += 64) {
         const int64_t p = sub + lane;
         bool ok = true;
-        if (p < e) ok = fast && knn_fast_atom<KMAX>(p, n, g, spos, sid, start, nbr_id, nbr_rel, box_fail);
+        if (p < e)
+            ok = fast && knn_fast_atom<KMAX, 64>(*(KnnRanges<64> *)Rp, lane, p, n, g, spos, sfix, start, nbr_id,
+                                                 nbr_rel, box_fail);
+        wave_lds_sync();  // the two searches share their LDS
         uint64_t left = __ballot(!ok);
         while (left) {
             const int l = __builtin_ctzll(left);
             left &= left - 1;
-            knn_exact_atom<KMAX>(sub + l, n, g, spos, sid, start, nbr_id, nbr_rel, box_fail);
+            knn_exact_atom<KMAX>(*(KnnWave *)Wp, sub + l, n, g, spos, sid, start, nbr_id, nbr_rel, box_fail);
         }
     }
 }
@@ -3114,7 +3221,7 @@ __device__ void serve_item(const MatchShared &M, const TablesView &Tl, MatchOut 
             const int cx = cell_coord(R.pos[3 * i + 0], g, 0);
             const int cy = cell_coord(R.pos[3 * i + 1], g, 1);
             const int cz = cell_coord(R.pos[3 * i + 2], g, 2);
-            const int c = (cz * g.nc[1] + cy) * g.nc[0] + cx;
+            const int c = cell_row(g, cy, cz) * g.nc[0] + cx;
             R.cell_of[i] = c;
             R.slot_of[i] = atomicAdd(&R.count[c], 1);
         }
@@ -3158,13 +3265,16 @@ __device__ void serve_item(const MatchShared &M, const TablesView &Tl, MatchOut 
         for (int64_t i = b + lane; i < e; i += 64) {
             const int32_t c = R.cell_of[i];
             const int64_t p = (int64_t)R.start[c] + R.bsum[c / SERVE_SCAN_CELLS] + R.slot_of[i];
-            R.spos[3 * (int64_t)p] = R.pos[3 * i + 0];
-            R.spos[3 * (int64_t)p + 1] = R.pos[3 * i + 1];
-            R.spos[3 * (int64_t)p + 2] = R.pos[3 * i + 2];
+            const double x = R.pos[3 * i + 0], y = R.pos[3 * i + 1], z = R.pos[3 * i + 2];
+            R.spos[3 * (int64_t)p] = x;
+            R.spos[3 * (int64_t)p + 1] = y;
+            R.spos[3 * (int64_t)p + 2] = z;
+            R.sfix[p] = make_int4(fixed_coord(x, S.g, 0), fixed_coord(y, S.g, 1), fixed_coord(z, S.g, 2), (int32_t)i);
             R.sid[p] = (int32_t)i;
         }
     } else if (ph == PH_KNN) {
-        serve_knn(S, r);
+        serve_knn((__attribute__((address_space(3))) KnnRanges<64> *)&U.ranges,
+                  (__attribute__((address_space(3))) KnnWave *)&U.knn, S, r);
     } else {  // PH_MATCH
         serve_match<RT>((__attribute__((address_space(3))) MatchShared *)&M,
                         (__attribute__((address_space(3))) TablesView *)&Tl,

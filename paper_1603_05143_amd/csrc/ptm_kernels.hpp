@@ -19,8 +19,25 @@ struct Grid {
     double h[3];      // cell edge
     double inv_h[3];  // cells per unit length
     double margin;    // safety margin of the neighbour-search certificate
+    double fix[3];    // fixed-point steps per unit length (fixed_coord)
+    double fix_err;   // error bound of a difference vector in these steps
     int canonical;    // every periodic coordinate already lies in [0, L)
 };
+
+// Fixed-point scale of the axes: 2^32 steps per periodic box length, 2^30 per
+// extent of an open axis (1 if it has none).  fix_err: what a difference
+// vector is off at most, one step per axis and the rounding of the wrapped
+// coordinates (2^-50 of the largest coordinate mn .. mx).
+__host__ __device__ inline void set_fixed_scale(Grid &g, const double (&ext)[3], const double *mn,
+                                                const double *mx) {
+    double e2 = 0;
+    for (int a = 0; a < 3; a++) {
+        g.fix[a] = (g.periodic[a] ? 4294967296.0 : 1073741824.0) / (ext[a] > 0 ? ext[a] : 1.0);
+        const double e = 1.0 / g.fix[a] + 0x1p-50 * fmax(fabs(mn[a]), fabs(mx[a]));
+        e2 += e * e;
+    }
+    g.fix_err = sqrt(e2);
+}
 
 struct MatchOut {
     int8_t *type;
@@ -44,8 +61,9 @@ void launch_bin_count(const double *pos, int64_t n, const Grid &g, int32_t *cell
 // start[0 .. cells] = exclusive scan of count[0 .. cells - 1] (start[cells]
 // = the total); bsum: scan_items(cells) words of scratch
 void launch_cell_starts(const int32_t *count, int64_t cells, int32_t *bsum, int32_t *start, hipStream_t st);
-void launch_bin_scatter(const double *pos, int64_t n, const int32_t *cell_of, const int32_t *slot_of,
-                        const int32_t *start, double *spos, int32_t *sid, hipStream_t st);
+// (sfix: per sorted atom its fixed-point coordinates and its id)
+void launch_bin_scatter(const double *pos, int64_t n, const Grid &g, const int32_t *cell_of, const int32_t *slot_of,
+                        const int32_t *start, double *spos, int4 *sfix, int32_t *sid, hipStream_t st);
 // k-NN: fast block search, then the exact shell search for the atoms it
 // leaves in todo (n entries) / *todo_count (zeroed by the caller).
 bool knn_fast_applies(const Grid &g);
@@ -54,7 +72,7 @@ bool knn_fast_applies(const Grid &g);
 // (zeroed by the caller) is set when the frame has a periodic axis and some
 // atom's nk-th neighbour is not strictly closer than half a periodic length
 // (or it has fewer than nk neighbours); every later stage then does nothing.
-void launch_knn(int64_t n, const Grid &g, int nk, const double *spos,
+void launch_knn(int64_t n, const Grid &g, int nk, const double *spos, const int4 *sfix,
                 const int32_t *sid, const int32_t *start, int32_t *nbr_id, double *nbr_rel, int32_t *todo,
                 int32_t *todo_count, int32_t *box_fail, hipStream_t st);
 // topological order (Sec. 3) of the 18 neighbours in rel18 / id18: the first
@@ -117,6 +135,7 @@ struct ServeRequest {
     int32_t *knn_out;
     int32_t *cell_of, *slot_of, *sid, *count, *start;
     double *spos;
+    int4 *sfix;
     int32_t *nbr_id;
     double *nbr_rel;
     int32_t *code;

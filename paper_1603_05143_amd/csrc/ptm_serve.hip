@@ -381,6 +381,7 @@ static ptm_status persistent_submit(ptm_ctx *ctx, const double *positions, const
     R.count = S.count;
     R.start = S.start;
     R.spos = S.spos;
+    R.sfix = S.sfix;
     R.nbr_id = S.nbr_id;
     R.nbr_rel = S.nbr_rel;
     R.code = S.code;
