@@ -106,6 +106,9 @@ void FrameScratch::release() {
     bytes = 0;
 }
 
+// the most cells make_grid chooses for n atoms
+static int64_t max_cells(int64_t n) { return 4 * n + 4096; }
+
 int bounds_blocks(int64_t n) {
     int64_t b = (n + 255) / 256;
     if (b > 1024) b = 1024;
@@ -175,8 +178,12 @@ Grid make_grid(const double box[3], const double mn[3], const double mx[3], int6
     return g;
 }
 
-// Enqueue the whole pipeline for one frame whose bounds are known.
-ptm_status enqueue_frame(ptm_ctx *ctx, FrameScratch &S, const FrameJob &J, hipStream_t st, bool prof) {
+// Enqueue the whole pipeline for one frame: with its grid known (J.grid), or
+// from the bounds on with the grid made on the device (J.dgrid; the cell
+// arrays are then laid out for the largest grid).  host_flag (nullable,
+// pinned) receives the box flag.
+ptm_status enqueue_frame(ptm_ctx *ctx, FrameScratch &S, const FrameJob &J, hipStream_t st, bool prof,
+                         int32_t *host_flag) {
     const int64_t n = J.n;
     auto mark = [&](int e) -> ptm_status {
         if (prof) PTM_HIP(ctx, hipEventRecord(ctx->prof_ev[e], st));
@@ -185,25 +192,37 @@ ptm_status enqueue_frame(ptm_ctx *ctx, FrameScratch &S, const FrameJob &J, hipSt
     ptm_status ps;
     const Grid &g = J.grid;
     if ((ps = mark(PTM_STAGE_BIN)) != PTM_OK) return ps;
-    int64_t cells = (int64_t)g.nc[0] * g.nc[1] * g.nc[2];
+    const int64_t cells = J.dgrid ? max_cells(n) : (int64_t)g.nc[0] * g.nc[1] * g.nc[2];
     // count[cells + 1] and count[cells + 2] count the atoms the fast k-NN
     // search leaves over and those the full rule decides; count[cells + 3]
-    // is the box flag (set by the k-NN kernels, read by every later stage);
-    // job_counter() the candidates superposed
-    launch_zero(S.count, cells + FRAME_COUNTERS, st);
-    const int32_t *box_fail = S.count + cells + 3;
-    launch_bin_count(J.pos, n, g, S.cell_of, S.slot_of, S.count, st);
-    launch_cell_starts(S.count, cells, S.sv_bsum, S.start, st);
-    launch_bin_scatter(J.pos, n, g, S.cell_of, S.slot_of, S.start, S.spos, S.sfix, S.sid, st);
+    // is the box flag (set by the bounds and k-NN kernels, read by every later
+    // stage); job_counter() the candidates superposed
+    int32_t *box_fail = S.count + cells + 3;
+    GridArg A{J.dgrid, g};
+    const int kn = J.topo ? VK : KMAX;
+    GridState *G = ctx->grid_state;
+    if (J.dgrid && n <= SETUP_SMALL_ATOMS) {
+        launch_setup_small(J.pos, n, J.box, kn, G, S.count, cells, S.cell_of, S.slot_of, S.start, S.spos, S.sfix,
+                           S.sid, box_fail, st);
+    } else {
+        if (J.dgrid)
+            launch_bounds_grid(J.pos, n, J.box, kn, S.count, cells, S.part, bounds_blocks(n), G,
+                               box_fail, st);
+        else
+            launch_zero(S.count, cells + FRAME_COUNTERS, st);
+        launch_bin_count(J.pos, n, A, S.cell_of, S.slot_of, S.count, box_fail, st);
+        launch_cell_starts(S.count, cells, A, S.sv_bsum, S.start, st);
+        launch_bin_scatter(J.pos, n, A, S.cell_of, S.slot_of, S.start, S.spos, S.sfix, S.sid, box_fail, st);
+    }
     if ((ps = mark(PTM_STAGE_KNN)) != PTM_OK) return ps;
     // slot_of is free once the atoms are scattered: it holds the leftover list
     if (J.topo) {
         // the 18 Euclidean neighbours, then their topological order (Sec. 3)
-        launch_knn(n, g, VK, S.spos, S.sfix, S.sid, S.start, S.id18, S.rel18, S.slot_of, S.count + cells + 1,
+        launch_knn(n, A, VK, S.spos, S.sfix, S.sid, S.start, S.id18, S.rel18, S.slot_of, S.count + cells + 1,
                    S.count + cells + 3, st);
         launch_voronoi(n, S.rel18, S.id18, S.vf, S.vlive, S.nbr_rel, S.nbr_id, box_fail, st);
     } else {
-        launch_knn(n, g, KMAX, S.spos, S.sfix, S.sid, S.start, S.nbr_id, S.nbr_rel, S.slot_of, S.count + cells + 1,
+        launch_knn(n, A, KMAX, S.spos, S.sfix, S.sid, S.start, S.nbr_id, S.nbr_rel, S.slot_of, S.count + cells + 1,
                    S.count + cells + 3, st);
     }
     if ((ps = mark(PTM_STAGE_TOPO)) != PTM_OK) return ps;
@@ -220,7 +239,7 @@ ptm_status enqueue_frame(ptm_ctx *ctx, FrameScratch &S, const FrameJob &J, hipSt
     // topological ordering starts with it)
     launch_match(n, S.nbr_rel, S.nbr_id, S.sid, J.species, ctx->view, S.code, S.ord, m, J.cutoff,
                  (ctx->flags & PTM_F_FULL_RULE) != 0, O, S.count + cells + 2, job_counter(S.count, cells),
-                 J.topo ? S.id18 : S.nbr_id, J.out.knn, box_fail, f32, st);
+                 J.topo ? S.id18 : S.nbr_id, J.out.knn, box_fail, host_flag, f32, st);
     if ((ps = mark(PTM_NSTAGES)) != PTM_OK) return ps;
     PTM_HIP(ctx, hipGetLastError());
     return PTM_OK;
@@ -321,6 +340,11 @@ hipError_t noalloc_scratch_of(int device, void **ptr) {
     return hipSuccess;
 }
 
+// Frames up to this take their grid from the device: one wait instead of two
+// and two launches fewer, against cell arrays laid out for the largest grid
+// (21 bytes per atom more).  Beyond, the wait is under 2 % of the frame.
+constexpr int64_t DEVICE_GRID_ATOMS = 2000000;
+
 // One frame through the pipeline with the scratch S (the context's own,
 // grown on demand, or a fixed buffer when noalloc: then nothing is
 // allocated and a frame that does not fit is PTM_E_TOO_LARGE).
@@ -345,12 +369,37 @@ ptm_status classify_frame(ptm_ctx *ctx, FrameScratch &S, bool noalloc, const dou
         if (S.reserve(n_atoms, cells, J.topo, ctx->err)) return PTM_OK;
         return noalloc ? PTM_E_TOO_LARGE : PTM_E_NOMEM;
     };
+    const bool prof = (ctx->flags & PTM_F_PROFILE) != 0;
+    ctx->prof_valid = false;
+    // Up to DEVICE_GRID_ATOMS atoms the grid is made on the device and the host
+    // waits once, at the end (stage timing wants the bounds apart, and a
+    // budget may hold the frame's own grid but not the largest one).
+    if (n_atoms <= DEVICE_GRID_ATOMS && !prof &&
+        !(ctx->budget && frame_bytes(n_atoms, max_cells(n_atoms), bounds_blocks(n_atoms), J.topo) > ctx->budget)) {
+        if ((st = reserve(max_cells(n_atoms))) != PTM_OK) return st;
+        J.dgrid = ctx->grid_state;
+        for (int a = 0; a < 3; a++) J.box[a] = box[a];
+        *ctx->pinned = 0;
+        if ((st = enqueue_frame(ctx, S, J, ctx->stream, false, ctx->pinned)) != PTM_OK) return st;
+        PTM_HIP(ctx, hipStreamSynchronize(ctx->stream));
+        if (*ctx->pinned == FRAME_NONFINITE) {
+            ctx->err = "non-finite coordinate";
+            return PTM_E_INVALID;
+        }
+        if (*ctx->pinned) {
+            ctx->err = box_message(J.topo);
+            return PTM_E_BOX;
+        }
+        if (H.active) {  // (host outputs are copied only now: nothing is written on an error)
+            if ((st = stage_out(ctx, out, n_atoms, J, H, ctx->stream)) != PTM_OK) return st;
+            PTM_HIP(ctx, hipStreamSynchronize(ctx->stream));
+        }
+        return PTM_OK;
+    }
     // bounds first (needs scratch for the partials): reserve with a tiny grid
     if ((st = reserve(1)) != PTM_OK) return st;
     double mn[3], mx[3];
     bool bad = false;
-    const bool prof = (ctx->flags & PTM_F_PROFILE) != 0;
-    ctx->prof_valid = false;
     if (prof) PTM_HIP(ctx, hipEventRecord(ctx->prof_ev[PTM_STAGE_BOUNDS], ctx->stream));
     st = frame_bounds(ctx, S, J.pos, n_atoms, mn, mx, bad, ctx->stream);
     if (st != PTM_OK) return st;
@@ -365,12 +414,11 @@ ptm_status classify_frame(ptm_ctx *ctx, FrameScratch &S, bool noalloc, const dou
         return PTM_E_NOMEM;
     }
     if ((st = reserve(cells)) != PTM_OK) return st;
-    st = enqueue_frame(ctx, S, J, ctx->stream, prof);
-    if (st != PTM_OK) return st;
-    // the box flag comes back with the frame; host outputs are copied only
-    // once it is known to be clear (nothing is written on an error)
     *ctx->pinned = 0;
-    PTM_HIP(ctx, hipMemcpyAsync(ctx->pinned, box_flag(S, J.grid), 4, hipMemcpyDeviceToHost, ctx->stream));
+    st = enqueue_frame(ctx, S, J, ctx->stream, prof, ctx->pinned);  // (the box flag comes back with the frame)
+    if (st != PTM_OK) return st;
+    // host outputs are copied only once the box flag is known to be clear
+    // (nothing is written on an error)
     if (H.active) {
         PTM_HIP(ctx, hipStreamSynchronize(ctx->stream));
         if (*ctx->pinned) {
@@ -483,6 +531,16 @@ ptm_status ptm_create(const ptm_config *cfg, ptm_ctx **out) {
         return PTM_E_NOMEM;
     }
     ctx->pinned_bounds = (double *)((char *)ctx->pinned + 256);
+    if (hipMalloc((void **)&ctx->grid_state, sizeof(GridState)) != hipSuccess) {
+        (void)hipGetLastError();
+        ctx->grid_state = nullptr;
+        ptm_destroy(ctx);
+        return PTM_E_NOMEM;
+    }
+    if (hipMemset(ctx->grid_state, 0, sizeof(GridState)) != hipSuccess) {
+        ptm_destroy(ctx);
+        return PTM_E_DEVICE;
+    }
     if (noalloc_scratch_of(ctx->device, &ctx->noalloc_scratch) != hipSuccess) {
         ptm_destroy(ctx);
         return PTM_E_DEVICE;
@@ -516,6 +574,7 @@ void ptm_destroy(ptm_ctx *ctx) {
     ctx->staging.release();
     for (void *p : ctx->table_buffers) (void)hipFree(p);
     if (ctx->aux) (void)hipFree(ctx->aux);
+    if (ctx->grid_state) (void)hipFree(ctx->grid_state);
     for (int e = 0; e <= PTM_NSTAGES; e++)
         if (ctx->prof_ev[e]) (void)hipEventDestroy(ctx->prof_ev[e]);
     if (ctx->own_stream && ctx->stream) (void)hipStreamDestroy(ctx->stream);

@@ -65,7 +65,9 @@ struct FrameJob {
     uint32_t mask = 0;
     bool topo = false;  // topological neighbour ordering
     double cutoff = 0;
-    Grid grid;
+    Grid grid;        // (host) grid, unless dgrid
+    const GridState *dgrid = nullptr;  // grid on the device: bounds and binning are part of the frame's launches
+    double box[3] = {0, 0, 0};
     ptm_outputs out;  // device pointers
 };
 
@@ -99,7 +101,7 @@ inline int32_t *box_flag(const FrameScratch &S, const Grid &g) {
 int bounds_blocks(int64_t n);
 Grid make_grid(const double box[3], const double mn[3], const double mx[3], int64_t n, int kn);
 ptm_status enqueue_frame(struct ::ptm_ctx *ctx, FrameScratch &S, const FrameJob &J, hipStream_t st,
-                         bool prof = false);
+                         bool prof = false, int32_t *host_flag = nullptr);
 ptm_status frame_bounds(struct ::ptm_ctx *ctx, FrameScratch &S, const double *pos, int64_t n, double mn[3],
                         double mx[3], bool &bad, hipStream_t st);
 const char *box_message(bool topo);
@@ -134,6 +136,7 @@ struct ptm_ctx {
     uint32_t flags = 0;
     int32_t *pinned = nullptr;      // pinned host word: the box flag of the last ptm_classify
     double *pinned_bounds = nullptr;  // pinned host space: per-block bounds of the frame being set up
+    ptm::GridState *grid_state = nullptr;  // device: the grid of the frame in progress on the context's stream
     void *noalloc_scratch = nullptr;  // this device's static scratch array (ptm_classify_noalloc)
     ptm::HostTables host;
     std::vector<void *> table_buffers;

@@ -67,47 +67,210 @@ __device__ inline double wrapped(double x, const Grid &g, int d) {
     return g.periodic[d] ? x - g.L[d] * floor(x * g.invL[d]) : x - g.lo[d];
 }
 
+__device__ inline Grid make_grid_dev(const double (&box)[3], const double (&mn)[3], const double (&mx)[3], int64_t n,
+                                     int kn) {
+    // the host's make_grid (ptm_api.hip), same arithmetic
+    Grid g;
+    double ext[3], vol = 1.0;
+    int flat = 0;
+    for (int a = 0; a < 3; a++) {
+        g.periodic[a] = box[a] > 0;
+        ext[a] = g.periodic[a] ? box[a] : fmax(mx[a] - mn[a], 0.0);
+        if (ext[a] > 0) vol *= ext[a];
+        else flat++;
+    }
+    double h;
+    if (flat == 0 && vol > 0) {
+        const double rho = (double)n / vol;
+        h = 0.6 * cbrt((double)kn / (4.1887902047863905 * rho));
+    } else {
+        h = 1.0;
+        for (int a = 0; a < 3; a++) h = fmax(h, ext[a] / 16.0);
+    }
+    for (int iter = 0; iter < 200; iter++) {
+        double cells = 1;
+        for (int a = 0; a < 3; a++) {
+            int nc;
+            if (g.periodic[a]) nc = (int)fmin(floor(ext[a] / h), (double)(1 << 20));
+            else nc = ext[a] > 0 ? (int)fmin(floor(ext[a] / h), (double)(1 << 20)) : 1;
+            if (g.periodic[a] && nc < 3) nc = 3;
+            if (nc < 1) nc = 1;
+            g.nc[a] = nc;
+            cells *= nc;
+        }
+        if (cells <= (double)(1 << 30) && cells <= 4.0 * (double)n + 4096.0) break;
+        h *= 1.25;
+    }
+    double hmax = 0;
+    for (int a = 0; a < 3; a++) {
+        if (g.periodic[a]) {
+            g.L[a] = box[a];
+            g.invL[a] = 1.0 / box[a];
+            g.lo[a] = 0.0;
+            g.h[a] = box[a] / g.nc[a];
+            g.inv_h[a] = g.nc[a] / box[a];
+        } else {
+            g.L[a] = 0.0;
+            g.invL[a] = 0.0;
+            g.lo[a] = mn[a];
+            g.h[a] = ext[a] > 0 ? ext[a] / g.nc[a] : 1.0;
+            g.inv_h[a] = ext[a] > 0 ? g.nc[a] / ext[a] : 1.0;
+        }
+        hmax = fmax(hmax, g.h[a]);
+    }
+    g.margin = 1e-9 * hmax;
+    set_fixed_scale(g, ext, mn, mx);
+    g.canonical = 1;
+    for (int a = 0; a < 3; a++)
+        if (g.periodic[a] && !(mn[a] >= 0.0 && mx[a] < box[a])) g.canonical = 0;
+    return g;
+}
+
+// the grid a kernel works on: one the host made, or the one on the device
+// (read through the constant address space: the kernel before has written it,
+// and scalar loads keep it out of the vector registers)
+__device__ inline Grid grid_of(const GridArg &A) {
+    Grid g = A.val;
+    if (A.dev) {
+        typedef const __attribute__((address_space(4))) uint32_t *Words;
+        const Words w = (Words)(const uint32_t *)&A.dev->g;
+        uint32_t v[sizeof(Grid) / 4];
+        static_assert(sizeof(Grid) % 4 == 0, "the grid is read in words");
+#pragma unroll
+        for (int i = 0; i < (int)(sizeof(Grid) / 4); i++) v[i] = w[i];
+        __builtin_memcpy(&g, v, sizeof(Grid));
+    }
+    return g;
+}
+__device__ inline int64_t cells_of(const GridArg &A, int64_t cells) { return A.dev ? A.dev->cells : cells; }
+
 // ------------------------------------------------------------------ bounds
-// Per-block min/max of each axis and a non-finite flag.
-__global__ void k_bounds(const double *__restrict__ pos, int64_t n, double *__restrict__ part) {
-    __shared__ double smin[3][256], smax[3][256];
-    __shared__ int sbad[256];
-    double mn[3] = {1e308, 1e308, 1e308}, mx[3] = {-1e308, -1e308, -1e308};
-    int bad = 0;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+struct Bounds {
+    double mn[3], mx[3];
+    int bad;  // a coordinate that is not finite
+};
+__device__ inline void bounds_clear(Bounds &b) {
+    for (int d = 0; d < 3; d++) {
+        b.mn[d] = 1e308;
+        b.mx[d] = -1e308;
+    }
+    b.bad = 0;
+}
+__device__ inline void bounds_add(Bounds &b, const double *__restrict__ pos, int64_t i) {
+    for (int d = 0; d < 3; d++) {
+        const double x = pos[3 * i + d];
+        if (!isfinite(x)) b.bad = 1;
+        b.mn[d] = fmin(b.mn[d], x);
+        b.mx[d] = fmax(b.mx[d], x);
+    }
+}
+// over the block (NW waves; ws: LDS); every lane of wave 0 gets the result
+template <int NW>
+__device__ inline void bounds_block(Bounds &b, Bounds *ws) {
+    for (int off = 32; off > 0; off >>= 1) {
         for (int d = 0; d < 3; d++) {
-            double x = pos[3 * i + d];
-            if (!isfinite(x)) bad = 1;
-            mn[d] = fmin(mn[d], x);
-            mx[d] = fmax(mx[d], x);
+            b.mn[d] = fmin(b.mn[d], __shfl_xor(b.mn[d], off));
+            b.mx[d] = fmax(b.mx[d], __shfl_xor(b.mx[d], off));
         }
+        b.bad |= __shfl_xor(b.bad, off);
     }
-    int t = threadIdx.x;
-    for (int d = 0; d < 3; d++) { smin[d][t] = mn[d]; smax[d][t] = mx[d]; }
-    sbad[t] = bad;
+    if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = b;
     __syncthreads();
-    for (int s = blockDim.x / 2; s > 0; s >>= 1) {
-        if (t < s) {
+    if (threadIdx.x < 64) {
+        b = ws[threadIdx.x & (NW - 1)];
+        for (int off = NW / 2; off > 0; off >>= 1) {
             for (int d = 0; d < 3; d++) {
-                smin[d][t] = fmin(smin[d][t], smin[d][t + s]);
-                smax[d][t] = fmax(smax[d][t], smax[d][t + s]);
+                b.mn[d] = fmin(b.mn[d], __shfl_xor(b.mn[d], off));
+                b.mx[d] = fmax(b.mx[d], __shfl_xor(b.mx[d], off));
             }
-            sbad[t] |= sbad[t + s];
+            b.bad |= __shfl_xor(b.bad, off);
         }
-        __syncthreads();
     }
-    if (t == 0) {
+}
+
+// Per-block min/max of each axis and a non-finite flag.
+__global__ void __launch_bounds__(256) k_bounds(const double *__restrict__ pos, int64_t n, double *__restrict__ part) {
+    __shared__ Bounds ws[4];
+    Bounds b;
+    bounds_clear(b);
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        bounds_add(b, pos, i);
+    bounds_block<4>(b, ws);
+    if (threadIdx.x == 0) {
         double *o = part + 7 * blockIdx.x;
-        for (int d = 0; d < 3; d++) { o[d] = smin[d][0]; o[3 + d] = smax[d][0]; }
-        o[6] = (double)sbad[0];
+        for (int d = 0; d < 3; d++) { o[d] = b.mn[d]; o[3 + d] = b.mx[d]; }
+        o[6] = (double)b.bad;
+    }
+}
+
+// the frame's grid from its bounds (one lane); a frame with a coordinate
+// that is not finite gets the flag, and every later kernel leaves it alone
+__device__ inline void grid_finish(GridState *G, const Bounds &b, const double (&box)[3], int64_t n, int kn,
+                                   int32_t *box_fail) {
+    Grid g = make_grid_dev(box, b.mn, b.mx, n, kn);
+    if (b.bad) g.nc[0] = g.nc[1] = g.nc[2] = 1;  // (nothing reads it, but the scan's range comes from it)
+    G->g = g;
+    G->cells = (int64_t)g.nc[0] * g.nc[1] * g.nc[2];
+    int fast = 1;
+    for (int a = 0; a < 3; a++)
+        if (g.periodic[a] && g.nc[a] < 5) fast = 0;
+    G->fast = fast;
+    *box_fail = b.bad ? FRAME_NONFINITE : 0;
+}
+
+// Bounds, cleared cell counters and, by the last block to finish, the frame's
+// own counters (after the cells) and the grid, in one launch: the host need
+// not see the bounds before it launches the rest.  The partial results go
+// through memory (the XCDs' L2s are not coherent) by stores that pass the L2
+// and are waited for; a fence would write back the whole L2 in every block.
+__global__ void __launch_bounds__(256) k_bounds_grid(const double *__restrict__ pos, int64_t n, double bx, double by,
+                                                     double bz, int kn, int32_t *__restrict__ count, int64_t cells,
+                                                     double *part, GridState *G, int32_t *box_fail) {
+    __shared__ Bounds ws[4];
+    __shared__ int last;
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x, first = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    for (int64_t i = first; i < cells; i += stride) count[i] = 0;
+    Bounds b;
+    bounds_clear(b);
+    for (int64_t i = first; i < n; i += stride) bounds_add(b, pos, i);
+    bounds_block<4>(b, ws);
+    if (threadIdx.x == 0) {
+        double *o = part + 7 * blockIdx.x;
+        for (int d = 0; d < 3; d++) {
+            __hip_atomic_store(o + d, b.mn[d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(o + 3 + d, b.mx[d], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __hip_atomic_store(o + 6, (double)b.bad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the partial is in memory before the arrival counts
+        last = __hip_atomic_fetch_add(&G->arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
+    }
+    __syncthreads();
+    if (!last) return;
+    if (threadIdx.x < FRAME_COUNTERS && threadIdx.x != 3) count[cells + threadIdx.x] = 0;  // (3: the flag, below)
+    bounds_clear(b);
+    for (int k = threadIdx.x; k < (int)gridDim.x; k += blockDim.x) {
+        const double *o = part + 7 * k;
+        for (int d = 0; d < 3; d++) {
+            b.mn[d] = fmin(b.mn[d], __hip_atomic_load(o + d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+            b.mx[d] = fmax(b.mx[d], __hip_atomic_load(o + 3 + d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        }
+        b.bad |= __hip_atomic_load(o + 6, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0.0;
+    }
+    bounds_block<4>(b, ws);
+    if (threadIdx.x == 0) {
+        const double box[3] = {bx, by, bz};
+        G->arrived = 0;  // for the next frame
+        grid_finish(G, b, box, n, kn, box_fail);
     }
 }
 
 // ----------------------------------------------------------------- binning
-__global__ void k_bin_count(const double *__restrict__ pos, int64_t n, Grid g, int32_t *__restrict__ cell_of,
-                            int32_t *__restrict__ slot_of, int32_t *__restrict__ count) {
+__global__ void k_bin_count(const double *__restrict__ pos, int64_t n, GridArg A, int32_t *__restrict__ cell_of,
+                            int32_t *__restrict__ slot_of, int32_t *__restrict__ count,
+                            const int32_t *__restrict__ box_fail) {
     int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= n) return;
+    if (i >= n || *box_fail) return;
+    const Grid g = grid_of(A);
     int cx = cell_coord(pos[3 * i + 0], g, 0);
     int cy = cell_coord(pos[3 * i + 1], g, 1);
     int cz = cell_coord(pos[3 * i + 2], g, 2);
@@ -149,9 +312,11 @@ __device__ inline int32_t block_excl_scan(int32_t v, int32_t &total, int32_t *ws
 
 // item totals: 16-byte reads interleaved across the block, so they
 // coalesce (count is 256-byte aligned and items are multiples of 4 cells)
-__global__ void __launch_bounds__(SCAN_THREADS) k_scan_totals(const int32_t *__restrict__ count, int64_t cells,
+__global__ void __launch_bounds__(SCAN_THREADS) k_scan_totals(const int32_t *__restrict__ count, int64_t cells, GridArg A,
                                                                int32_t *__restrict__ bsum) {
     __shared__ int32_t ws[SCAN_THREADS / 64];
+    cells = cells_of(A, cells);
+    if ((int64_t)blockIdx.x * SERVE_SCAN_CELLS > cells) return;
     const int64_t b = (int64_t)blockIdx.x * SERVE_SCAN_CELLS + 4 * (int64_t)threadIdx.x;
     int32_t s = 0;
 #pragma unroll
@@ -185,11 +350,26 @@ __global__ void __launch_bounds__(1024) k_scan_top(int32_t *__restrict__ bsum, i
     }
 }
 
-// each item's cells: a run of SCAN_PER consecutive cells per thread
+// Each item's cells: a run of SCAN_PER consecutive cells per thread.  Top:
+// bsum holds the items' exclusive prefix (k_scan_top); otherwise the block
+// adds up the totals of the items before its own, which for the item counts
+// this is used for costs less than the launch.
+template <bool Top>
 __global__ void __launch_bounds__(SCAN_THREADS) k_scan_cells(const int32_t *__restrict__ count, int64_t cells,
-                                                              const int32_t *__restrict__ bsum,
+                                                              GridArg A, const int32_t *__restrict__ bsum,
                                                               int32_t *__restrict__ start) {
     __shared__ int32_t ws[SCAN_THREADS / 64];
+    cells = cells_of(A, cells);
+    if ((int64_t)blockIdx.x * SERVE_SCAN_CELLS > cells) return;
+    int32_t before = 0;
+    if (Top) {
+        before = bsum[blockIdx.x];
+    } else {
+        int32_t v = 0;
+        for (int k = threadIdx.x; k < (int)blockIdx.x; k += SCAN_THREADS) v += bsum[k];
+        (void)block_excl_scan<SCAN_THREADS>(v, before, ws);
+        __syncthreads();  // ws is used again below
+    }
     const int64_t b = (int64_t)blockIdx.x * SERVE_SCAN_CELLS + (int64_t)threadIdx.x * SCAN_PER;
     int32_t v[SCAN_PER], s = 0;
     if (b + SCAN_PER <= cells) {  // whole run in range: 16-byte reads (b is a multiple of 8)
@@ -209,7 +389,7 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan_cells(const int32_t *__re
 #pragma unroll
     for (int k = 0; k < SCAN_PER; k++) s += v[k];
     int32_t total;
-    int32_t run = bsum[blockIdx.x] + block_excl_scan<SCAN_THREADS>(s, total, ws);
+    int32_t run = before + block_excl_scan<SCAN_THREADS>(s, total, ws);
     int32_t o[SCAN_PER];
 #pragma unroll
     for (int k = 0; k < SCAN_PER; k++) {
@@ -234,11 +414,13 @@ __device__ inline int32_t fixed_coord(double x, const Grid &g, int d) {
     return (int32_t)(uint32_t)fmin(fmax(wrapped(x, g, d) * g.fix[d], 0.0), 4294967295.0);
 }
 
-__global__ void k_bin_scatter(const double *__restrict__ pos, int64_t n, Grid g, const int32_t *__restrict__ cell_of,
-                              const int32_t *__restrict__ slot_of, const int32_t *__restrict__ start,
-                              double *__restrict__ spos, int4 *__restrict__ sfix, int32_t *__restrict__ sid) {
+__global__ void k_bin_scatter(const double *__restrict__ pos, int64_t n, GridArg A,
+                              const int32_t *__restrict__ cell_of, const int32_t *__restrict__ slot_of,
+                              const int32_t *__restrict__ start, double *__restrict__ spos, int4 *__restrict__ sfix,
+                              int32_t *__restrict__ sid, const int32_t *__restrict__ box_fail) {
     int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= n) return;
+    if (i >= n || *box_fail) return;
+    const Grid g = grid_of(A);
     int64_t p = (int64_t)start[cell_of[i]] + slot_of[i];
     const double x = pos[3 * i + 0], y = pos[3 * i + 1], z = pos[3 * i + 2];
     spos[3 * (int64_t)p] = x;
@@ -246,6 +428,85 @@ __global__ void k_bin_scatter(const double *__restrict__ pos, int64_t n, Grid g,
     spos[3 * (int64_t)p + 2] = z;
     sfix[p] = make_int4(fixed_coord(x, g, 0), fixed_coord(y, g, 1), fixed_coord(z, g, 2), (int32_t)i);
     sid[p] = (int32_t)i;
+}
+
+// Bounds, grid and binning of a small frame in one launch of one block: the
+// eight launches they take otherwise cost the host 4 to 8 us each, more than
+// their work (500 atoms: 85 us from the first to the last, with the copy of
+// the bounds to the host between them; this kernel 11 us).  One block's
+// passes over the atoms grow with them: at 8,000 atoms the launches of
+// k_bounds_grid and the rest are 15 us faster.
+constexpr int SETUP_THREADS = 1024;
+constexpr int SETUP_CELLS = 16384;  // counters in LDS up to this many cells
+__global__ void __launch_bounds__(SETUP_THREADS) k_setup_small(const double *__restrict__ pos, int64_t n, double bx,
+                                                               double by, double bz, int kn, GridState *G,
+                                                               int32_t *__restrict__ count, int64_t cells_max,
+                                                               int32_t *__restrict__ cell_of,
+                                                               int32_t *__restrict__ slot_of,
+                                                               int32_t *__restrict__ start, double *__restrict__ spos,
+                                                               int4 *__restrict__ sfix, int32_t *__restrict__ sid,
+                                                               int32_t *box_fail) {
+    constexpr int NW = SETUP_THREADS / 64;
+    __shared__ Bounds wb[NW];
+    __shared__ int32_t ws[NW];
+    __shared__ Grid sg;
+    __shared__ int s_bad;
+    __shared__ int32_t lds_count[SETUP_CELLS];
+    const int t = threadIdx.x;
+    // the frame's counters (after the cells, where the other path has them)
+    if (t < FRAME_COUNTERS && t != 3) count[cells_max + t] = 0;  // (3: the flag, by grid_finish)
+    Bounds b;
+    bounds_clear(b);
+    for (int64_t i = t; i < n; i += SETUP_THREADS) bounds_add(b, pos, i);
+    bounds_block<NW>(b, wb);
+    if (t == 0) {
+        const double box[3] = {bx, by, bz};
+        grid_finish(G, b, box, n, kn, box_fail);
+        sg = G->g;
+        s_bad = b.bad;
+    }
+    __syncthreads();
+    if (s_bad) return;
+    const Grid g = sg;
+    const int cells = g.nc[0] * g.nc[1] * g.nc[2];
+    const bool in_lds = cells <= SETUP_CELLS;
+    if (in_lds)
+        for (int c = t; c < cells; c += SETUP_THREADS) lds_count[c] = 0;
+    else
+        for (int c = t; c < cells; c += SETUP_THREADS) count[c] = 0;
+    __syncthreads();
+    for (int64_t i = t; i < n; i += SETUP_THREADS) {
+        const int cx = cell_coord(pos[3 * i + 0], g, 0), cy = cell_coord(pos[3 * i + 1], g, 1),
+                  cz = cell_coord(pos[3 * i + 2], g, 2);
+        const int c = cell_row(g, cy, cz) * g.nc[0] + cx;
+        cell_of[i] = c;
+        slot_of[i] = in_lds ? atomicAdd(&lds_count[c], 1) : atomicAdd(&count[c], 1);
+    }
+    __syncthreads();
+    // exclusive scan, a run of cells per thread
+    const int per = (cells + SETUP_THREADS - 1) / SETUP_THREADS;
+    const int c0 = min(t * per, cells), c1 = min(c0 + per, cells);
+    int32_t sum = 0, total;
+    for (int c = c0; c < c1; c++) sum += in_lds ? lds_count[c] : count[c];
+    int32_t run = block_excl_scan<SETUP_THREADS>(sum, total, ws);
+    for (int c = c0; c < c1; c++) {
+        start[c] = run;
+        const int32_t k = in_lds ? lds_count[c] : count[c];
+        if (in_lds) lds_count[c] = run;
+        run += k;
+    }
+    if (t == 0) start[cells] = total;
+    __syncthreads();
+    for (int64_t i = t; i < n; i += SETUP_THREADS) {
+        const int c = cell_of[i];
+        const int64_t p = (int64_t)(in_lds ? lds_count[c] : start[c]) + slot_of[i];
+        const double x = pos[3 * i + 0], y = pos[3 * i + 1], z = pos[3 * i + 2];
+        spos[3 * p] = x;
+        spos[3 * p + 1] = y;
+        spos[3 * p + 2] = z;
+        sfix[p] = make_int4(fixed_coord(x, g, 0), fixed_coord(y, g, 1), fixed_coord(z, g, 2), (int32_t)i);
+        sid[p] = (int32_t)i;
+    }
 }
 
 // ---------------------------------------------------------------- k-NN
@@ -655,14 +916,15 @@ __device__ inline bool knn_fast_atom(KnnRanges<W> &S, int t, int64_t p, int64_t 
 }
 
 template <int NK>
-__global__ void __launch_bounds__(256, 4) k_knn_fast(int64_t n, Grid g, const double *__restrict__ spos,
+__global__ void __launch_bounds__(256, 4) k_knn_fast(int64_t n, GridArg A, const double *__restrict__ spos,
                                                   const int4 *__restrict__ sfix, const int32_t *__restrict__ start,
                                                   int32_t *__restrict__ nbr_id, double *__restrict__ nbr_rel,
                                                   int32_t *__restrict__ todo, int32_t *__restrict__ todo_count,
                                                   int32_t *__restrict__ box_fail) {
     __shared__ KnnRanges<256> S;
     int64_t p = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
-    if (p >= n) return;
+    if (p >= n || *box_fail == FRAME_NONFINITE || (A.dev && !A.dev->fast)) return;
+    const Grid g = grid_of(A);
     if (!knn_fast_atom<NK, 256>(S, (int)threadIdx.x, p, n, g, spos, sfix, start, nbr_id, nbr_rel, box_fail))
         todo[atomicAdd(todo_count, 1)] = (int32_t)p;
 }
@@ -680,6 +942,7 @@ __global__ void __launch_bounds__(256, 4) k_knn_fast(int64_t n, Grid g, const do
 // wave-wide minima took 207 us where this takes 86 on the 0.92 M-atom
 // polycrystal.)
 constexpr int KNN_CAND = 256;  // list entries
+constexpr int64_t KNN_WAVE_ATOMS = 16384;  // frames up to this take the wave-per-atom search alone
 struct KnnWave {
     double d2[KNN_CAND];
     int32_t id[KNN_CAND], q[KNN_CAND];
@@ -843,13 +1106,16 @@ __device__ void knn_exact_atom(KnnWave &S, int64_t p, int64_t n, const Grid &g, 
 }
 
 template <int NK>
-__global__ void __launch_bounds__(256) k_knn_exact(int64_t n, Grid g, const double *__restrict__ spos,
+__global__ void __launch_bounds__(256) k_knn_exact(int64_t n, GridArg A, const double *__restrict__ spos,
                                                    const int32_t *__restrict__ sid, const int32_t *__restrict__ start,
                                                    int32_t *__restrict__ nbr_id, double *__restrict__ nbr_rel,
                                                    const int32_t *__restrict__ todo,
                                                    const int32_t *__restrict__ todo_count,
                                                    int32_t *__restrict__ box_fail) {
     __shared__ KnnWave S[4];
+    if (*box_fail == FRAME_NONFINITE) return;
+    if (A.dev && !A.dev->fast) todo = nullptr;  // the fast search left every atom
+    const Grid g = grid_of(A);
     const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x >> 6);
     const int64_t cnt_todo = todo ? (int64_t)*todo_count : n;
     for (int64_t w = blockIdx.x * (int64_t)(blockDim.x >> 6) + (threadIdx.x >> 6); w < cnt_todo; w += nwaves)
@@ -2403,6 +2669,7 @@ constexpr uint32_t ALL_TEMPLATES = (1u << NT) - 1;
 // by a block of NW waves: templates in M, the LDS copies Tl / Ol of the
 // table view and outputs (for the full rule), working LDS Wk.  force_full:
 // every atom with a candidate takes the full rule (a test of that path).
+// apw: atoms of each wave (the first lanes; NW * apw atoms from first).
 // full_count counts the atoms the full rule decides, job_count the
 // superposed candidates.
 template <typename RT, int NW>
@@ -2413,12 +2680,12 @@ __device__ void match_block(const MatchShared &M, const TablesView &Tl, const Ma
                             const int32_t *__restrict__ code, const uint64_t *__restrict__ ords, uint32_t mask,
                             double cutoff, int force_full, const MatchOut &O, int32_t *__restrict__ full_count,
                             unsigned long long *__restrict__ job_count, const int32_t *__restrict__ knn_src,
-                            int32_t *__restrict__ knn_out) {
+                            int32_t *__restrict__ knn_out, int apw) {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     MatchWaveLds<RT> &W = Wk.w[wv];
-    const int64_t wbase = first + (int64_t)wv * 64;
+    const int64_t wbase = first + (int64_t)wv * apw;
     const int64_t p = wbase + lane;
-    const bool live = p < n;
+    const bool live = lane < apw && p < n;
 
     // A. lane = atom
     int cnt[NGRP] = {0, 0, 0};
@@ -2599,16 +2866,19 @@ __global__ void __launch_bounds__(MB, sizeof(RT) == 4 ? 4 : 3) k_match(int64_t n
                                                 int32_t *__restrict__ full_count,
                                                 unsigned long long *__restrict__ job_count,
                                                 const int32_t *__restrict__ knn_src, int32_t *__restrict__ knn_out,
-                                                const int32_t *__restrict__ box_fail) {
+                                                const int32_t *__restrict__ box_fail, int apw, int32_t *host_flag) {
     __shared__ MatchLds<RT, MB / 64> L;
+    if (host_flag && blockIdx.x == 0 && threadIdx.x == 0)
+        __hip_atomic_store(host_flag, *box_fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     if (*box_fail) return;  // uniform over the grid
     if (threadIdx.x == 0) {
         L.T = T;
         L.O = O;
     }
     load_templates(L.M, T);
-    match_block<RT, MB / 64>(L.M, L.T, L.O, L.work, (int64_t)blockIdx.x * MB, n, nbr_rel, nbr_id, sid, species, T,
-                             code, ords, mask, cutoff, force_full, O, full_count, job_count, knn_src, knn_out);
+    match_block<RT, MB / 64>(L.M, L.T, L.O, L.work, (int64_t)blockIdx.x * (MB / 64) * apw, n, nbr_rel, nbr_id, sid, species, T,
+                             code, ords, mask, cutoff, force_full, O, full_count, job_count, knn_src, knn_out,
+                             apw);
 }
 
 // ------------------------------------------------- post-hoc cut-off (Sec. 5.1)
@@ -2867,22 +3137,50 @@ void launch_zero(int32_t *p, int64_t n, hipStream_t st) {
 void launch_bounds(const double *pos, int64_t n, double *part, int nblocks, hipStream_t st) {
     hipLaunchKernelGGL(k_bounds, dim3(nblocks), dim3(256), 0, st, pos, n, part);
 }
-void launch_bin_count(const double *pos, int64_t n, const Grid &g, int32_t *cell_of, int32_t *slot_of,
-                      int32_t *count, hipStream_t st) {
-    hipLaunchKernelGGL(k_bin_count, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, pos, n, g, cell_of, slot_of,
-                       count);
+void launch_bounds_grid(const double *pos, int64_t n, const double *box, int kn, int32_t *count, int64_t cells,
+                        double *part, int nblocks, GridState *G, int32_t *box_fail, hipStream_t st) {
+    hipLaunchKernelGGL(k_bounds_grid, dim3(nblocks), dim3(256), 0, st, pos, n, box[0], box[1], box[2], kn, count,
+                       cells, part, G, box_fail);
 }
-void launch_cell_starts(const int32_t *count, int64_t cells, int32_t *bsum, int32_t *start, hipStream_t st) {
+void launch_setup_small(const double *pos, int64_t n, const double *box, int kn, GridState *G, int32_t *count,
+                        int64_t cells_max, int32_t *cell_of, int32_t *slot_of, int32_t *start, double *spos,
+                        int4 *sfix, int32_t *sid, int32_t *box_fail, hipStream_t st) {
+    hipLaunchKernelGGL(k_setup_small, dim3(1), dim3(SETUP_THREADS), 0, st, pos, n, box[0], box[1], box[2], kn, G,
+                       count, cells_max, cell_of, slot_of, start, spos, sfix, sid, box_fail);
+}
+void launch_bin_count(const double *pos, int64_t n, const GridArg &A, int32_t *cell_of, int32_t *slot_of,
+                      int32_t *count, const int32_t *box_fail, hipStream_t st) {
+    hipLaunchKernelGGL(k_bin_count, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, pos, n, A, cell_of, slot_of,
+                       count, box_fail);
+}
+void launch_cell_starts(const int32_t *count, int64_t cells, const GridArg &A, int32_t *bsum, int32_t *start,
+                        hipStream_t st) {
     const int64_t items = scan_items(cells);
-    hipLaunchKernelGGL(k_scan_totals, dim3((unsigned)items), dim3(SCAN_THREADS), 0, st, count, cells, bsum);
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, st, bsum, items);
-    hipLaunchKernelGGL(k_scan_cells, dim3((unsigned)items), dim3(SCAN_THREADS), 0, st, count, cells,
-                       (const int32_t *)bsum, start);
+    hipLaunchKernelGGL(k_scan_totals, dim3((unsigned)items), dim3(SCAN_THREADS), 0, st, count, cells, A, bsum);
+    // up to 4096 items (8 M cells) a block adds up at most 16 totals per
+    // thread itself: less than a launch
+    if (items > 4096) {
+        hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, st, bsum, items);
+        hipLaunchKernelGGL(k_scan_cells<true>, dim3((unsigned)items), dim3(SCAN_THREADS), 0, st, count, cells, A,
+                           (const int32_t *)bsum, start);
+    } else {
+        hipLaunchKernelGGL(k_scan_cells<false>, dim3((unsigned)items), dim3(SCAN_THREADS), 0, st, count, cells, A,
+                           (const int32_t *)bsum, start);
+    }
 }
-void launch_bin_scatter(const double *pos, int64_t n, const Grid &g, const int32_t *cell_of, const int32_t *slot_of,
-                        const int32_t *start, double *spos, int4 *sfix, int32_t *sid, hipStream_t st) {
-    hipLaunchKernelGGL(k_bin_scatter, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, pos, n, g, cell_of,
-                       slot_of, start, spos, sfix, sid);
+void launch_bin_scatter(const double *pos, int64_t n, const GridArg &A, const int32_t *cell_of, const int32_t *slot_of,
+                        const int32_t *start, double *spos, int4 *sfix, int32_t *sid, const int32_t *box_fail,
+                        hipStream_t st) {
+    hipLaunchKernelGGL(k_bin_scatter, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, pos, n, A, cell_of,
+                       slot_of, start, spos, sfix, sid, box_fail);
+}
+// Atoms per wave of the match kernel.  A wave pays for the longest of its
+// lanes in every loop, so while the chip has SIMDs without a wave the atoms
+// are spread over more of them.
+static int match_atoms_per_wave(int64_t n) {
+    int apw = 1;
+    while (apw < 64 && n > (int64_t)apw * 1024) apw *= 2;
+    return apw;
 }
 bool knn_fast_applies(const Grid &g) {
     for (int a = 0; a < 3; a++)
@@ -2890,30 +3188,32 @@ bool knn_fast_applies(const Grid &g) {
     return true;
 }
 template <int NK>
-static void launch_knn_nk(int64_t n, const Grid &g, const double *spos, const int4 *sfix,
+static void launch_knn_nk(int64_t n, const GridArg &A, const double *spos, const int4 *sfix,
                           const int32_t *sid, const int32_t *start, int32_t *nbr_id, double *nbr_rel,
                           int32_t *todo, int32_t *todo_count, int32_t *box_fail, hipStream_t st) {
     int64_t blocks = (n + 255) / 256;
-    if (knn_fast_applies(g)) {
-        hipLaunchKernelGGL(k_knn_fast<NK>, dim3((unsigned)xcd_pad(blocks)), dim3(256), 0, st, n, g, spos, sfix,
+    // up to KNN_WAVE_ATOMS atoms, a wave each: the chip holds 4096 such waves,
+    // and one takes a fraction of the time of a lane's walk through its block
+    if (n > KNN_WAVE_ATOMS && (A.dev || knn_fast_applies(A.val))) {
+        hipLaunchKernelGGL(k_knn_fast<NK>, dim3((unsigned)xcd_pad(blocks)), dim3(256), 0, st, n, A, spos, sfix,
                            start, nbr_id, nbr_rel, todo, todo_count, box_fail);
         // the atoms left over are few; at most 1024 blocks of four waves stride over them
-        hipLaunchKernelGGL(k_knn_exact<NK>, dim3((unsigned)std::min<int64_t>((n + 15) / 16, 1024)), dim3(256), 0, st, n, g,
+        hipLaunchKernelGGL(k_knn_exact<NK>, dim3((unsigned)std::min<int64_t>((n + 15) / 16, 1024)), dim3(256), 0, st, n, A,
                            spos, sid, start, nbr_id, nbr_rel, (const int32_t *)todo,
                            (const int32_t *)todo_count, box_fail);
     } else {
         hipLaunchKernelGGL(k_knn_exact<NK>, dim3((unsigned)std::min<int64_t>((n + 3) / 4, 16384)), dim3(256), 0, st, n,
-                           g, spos, sid, start, nbr_id, nbr_rel, (const int32_t *)nullptr,
+                           A, spos, sid, start, nbr_id, nbr_rel, (const int32_t *)nullptr,
                            (const int32_t *)nullptr, box_fail);
     }
 }
-void launch_knn(int64_t n, const Grid &g, int nk, const double *spos, const int4 *sfix,
+void launch_knn(int64_t n, const GridArg &A, int nk, const double *spos, const int4 *sfix,
                 const int32_t *sid, const int32_t *start, int32_t *nbr_id, double *nbr_rel, int32_t *todo,
                 int32_t *todo_count, int32_t *box_fail, hipStream_t st) {
     if (nk == VK)
-        launch_knn_nk<VK>(n, g, spos, sfix, sid, start, nbr_id, nbr_rel, todo, todo_count, box_fail, st);
+        launch_knn_nk<VK>(n, A, spos, sfix, sid, start, nbr_id, nbr_rel, todo, todo_count, box_fail, st);
     else
-        launch_knn_nk<KMAX>(n, g, spos, sfix, sid, start, nbr_id, nbr_rel, todo, todo_count, box_fail, st);
+        launch_knn_nk<KMAX>(n, A, spos, sfix, sid, start, nbr_id, nbr_rel, todo, todo_count, box_fail, st);
 }
 void launch_voronoi(int64_t n, const double *rel18, const int32_t *id18, uint32_t *vf, uint32_t *vlive,
                     double *nbr_rel, int32_t *nbr_id, const int32_t *box_fail, hipStream_t st) {
@@ -2952,65 +3252,6 @@ enum {
     PH_KNN = 7,      // neighbours (fast search, exact search for what it leaves)
     PH_MATCH = 8     // hulls and codes, then the match stage, 64 atoms at a time
 };
-
-__device__ inline Grid make_grid_dev(const double (&box)[3], const double (&mn)[3], const double (&mx)[3], int64_t n,
-                                     int kn) {
-    // the host's make_grid (ptm_api.hip), same arithmetic
-    Grid g;
-    double ext[3], vol = 1.0;
-    int flat = 0;
-    for (int a = 0; a < 3; a++) {
-        g.periodic[a] = box[a] > 0;
-        ext[a] = g.periodic[a] ? box[a] : fmax(mx[a] - mn[a], 0.0);
-        if (ext[a] > 0) vol *= ext[a];
-        else flat++;
-    }
-    double h;
-    if (flat == 0 && vol > 0) {
-        const double rho = (double)n / vol;
-        h = 0.6 * cbrt((double)kn / (4.1887902047863905 * rho));
-    } else {
-        h = 1.0;
-        for (int a = 0; a < 3; a++) h = fmax(h, ext[a] / 16.0);
-    }
-    for (int iter = 0; iter < 200; iter++) {
-        double cells = 1;
-        for (int a = 0; a < 3; a++) {
-            int nc;
-            if (g.periodic[a]) nc = (int)fmin(floor(ext[a] / h), (double)(1 << 20));
-            else nc = ext[a] > 0 ? (int)fmin(floor(ext[a] / h), (double)(1 << 20)) : 1;
-            if (g.periodic[a] && nc < 3) nc = 3;
-            if (nc < 1) nc = 1;
-            g.nc[a] = nc;
-            cells *= nc;
-        }
-        if (cells <= (double)(1 << 30) && cells <= 4.0 * (double)n + 4096.0) break;
-        h *= 1.25;
-    }
-    double hmax = 0;
-    for (int a = 0; a < 3; a++) {
-        if (g.periodic[a]) {
-            g.L[a] = box[a];
-            g.invL[a] = 1.0 / box[a];
-            g.lo[a] = 0.0;
-            g.h[a] = box[a] / g.nc[a];
-            g.inv_h[a] = g.nc[a] / box[a];
-        } else {
-            g.L[a] = 0.0;
-            g.invL[a] = 0.0;
-            g.lo[a] = mn[a];
-            g.h[a] = ext[a] > 0 ? ext[a] / g.nc[a] : 1.0;
-            g.inv_h[a] = ext[a] > 0 ? g.nc[a] / ext[a] : 1.0;
-        }
-        hmax = fmax(hmax, g.h[a]);
-    }
-    g.margin = 1e-9 * hmax;
-    set_fixed_scale(g, ext, mn, mx);
-    g.canonical = 1;
-    for (int a = 0; a < 3; a++)
-        if (g.periodic[a] && !(mn[a] >= 0.0 && mx[a] < box[a])) g.canonical = 0;
-    return g;
-}
 
 __device__ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
@@ -3143,7 +3384,7 @@ __device__ __noinline__ void serve_match(__attribute__((address_space(3))) Match
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
         __syncthreads();
         match_block<RT, 1>(M, T, Ol, U.mw, sub, n, nbr_rel, nbr_id, sid, species, T, code, ord, mask, cutoff, 0,
-                           Ol, full_count, job_count, nbr_id, knn_out);
+                           Ol, full_count, job_count, nbr_id, knn_out, 64);
     }
 }
 
@@ -3482,15 +3723,17 @@ void launch_match(int64_t n, const double *nbr_rel, const int32_t *nbr_id, const
                   const int8_t *species, const TablesView &T, const int32_t *code, const uint64_t *ord,
                   uint32_t mask, double cutoff, bool force_full, const MatchOut &O, int32_t *full_count,
                   unsigned long long *job_count, const int32_t *knn_src, int32_t *knn_out, const int32_t *box_fail,
-                  bool f32, hipStream_t st) {
+                  int32_t *host_flag, bool f32, hipStream_t st) {
     if (n <= 0) return;
-    dim3 grid((unsigned)((n + MB - 1) / MB)), block(MB);
+    const int apw = match_atoms_per_wave(n), per = MB / 64 * apw;
+    dim3 grid((unsigned)((n + per - 1) / per)), block(MB);
     if (f32)
         hipLaunchKernelGGL(k_match<float>, grid, block, 0, st, n, nbr_rel, nbr_id, sid, species, T, code, ord, mask,
-                           cutoff, (int)force_full, O, full_count, job_count, knn_src, knn_out, box_fail);
+                           cutoff, (int)force_full, O, full_count, job_count, knn_src, knn_out, box_fail, apw, host_flag);
     else
         hipLaunchKernelGGL(k_match<double>, grid, block, 0, st, n, nbr_rel, nbr_id, sid, species, T, code, ord,
-                           mask, cutoff, (int)force_full, O, full_count, job_count, knn_src, knn_out, box_fail);
+                           mask, cutoff, (int)force_full, O, full_count, job_count, knn_src, knn_out, box_fail, apw,
+                           host_flag);
 }
 
 template <typename RT>

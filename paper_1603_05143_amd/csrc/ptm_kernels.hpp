@@ -39,6 +39,21 @@ __host__ __device__ inline void set_fixed_scale(Grid &g, const double (&ext)[3],
     g.fix_err = sqrt(e2);
 }
 
+// The grid of a frame whose bounds stay on the device.
+struct GridState {
+    Grid g;
+    int64_t cells;
+    int32_t fast;     // the fast k-NN search applies (knn_fast_applies)
+    int32_t arrived;  // blocks of k_bounds_grid that are done (0 between frames)
+};
+// What the kernels take: the grid by value, or (dev not null) on the device.
+struct GridArg {
+    const GridState *dev;
+    Grid val;
+};
+// values of a frame's box flag: every stage after the one that sets it does nothing
+enum { FRAME_BOX = 1, FRAME_NONFINITE = 2 };
+
 struct MatchOut {
     int8_t *type;
     int8_t *alloy;
@@ -56,14 +71,27 @@ struct MatchOut {
 
 void launch_zero(int32_t *p, int64_t n, hipStream_t st);
 void launch_bounds(const double *pos, int64_t n, double *part, int nblocks, hipStream_t st);
-void launch_bin_count(const double *pos, int64_t n, const Grid &g, int32_t *cell_of, int32_t *slot_of,
-                      int32_t *count, hipStream_t st);
+// bounds, cleared counters (cells of them, then the frame's) and grid in one
+// launch (G->arrived must be 0; box_fail = count + cells + 3)
+void launch_bounds_grid(const double *pos, int64_t n, const double *box, int kn, int32_t *count, int64_t cells,
+                        double *part, int nblocks, GridState *G, int32_t *box_fail, hipStream_t st);
+// bounds, grid and binning of a small frame in one launch of one block
+// (clears the frame's counters, which follow cells_max cell counters)
+constexpr int64_t SETUP_SMALL_ATOMS = 4096;
+void launch_setup_small(const double *pos, int64_t n, const double *box, int kn, GridState *G, int32_t *count,
+                        int64_t cells_max, int32_t *cell_of, int32_t *slot_of, int32_t *start, double *spos,
+                        int4 *sfix, int32_t *sid, int32_t *box_fail, hipStream_t st);
+void launch_bin_count(const double *pos, int64_t n, const GridArg &A, int32_t *cell_of, int32_t *slot_of,
+                      int32_t *count, const int32_t *box_fail, hipStream_t st);
 // start[0 .. cells] = exclusive scan of count[0 .. cells - 1] (start[cells]
 // = the total); bsum: scan_items(cells) words of scratch
-void launch_cell_starts(const int32_t *count, int64_t cells, int32_t *bsum, int32_t *start, hipStream_t st);
+// (cells: at least as many as a grid on the device has)
+void launch_cell_starts(const int32_t *count, int64_t cells, const GridArg &A, int32_t *bsum, int32_t *start,
+                        hipStream_t st);
 // (sfix: per sorted atom its fixed-point coordinates and its id)
-void launch_bin_scatter(const double *pos, int64_t n, const Grid &g, const int32_t *cell_of, const int32_t *slot_of,
-                        const int32_t *start, double *spos, int4 *sfix, int32_t *sid, hipStream_t st);
+void launch_bin_scatter(const double *pos, int64_t n, const GridArg &A, const int32_t *cell_of,
+                        const int32_t *slot_of, const int32_t *start, double *spos, int4 *sfix, int32_t *sid,
+                        const int32_t *box_fail, hipStream_t st);
 // k-NN: fast block search, then the exact shell search for the atoms it
 // leaves in todo (n entries) / *todo_count (zeroed by the caller).
 bool knn_fast_applies(const Grid &g);
@@ -72,7 +100,7 @@ bool knn_fast_applies(const Grid &g);
 // (zeroed by the caller) is set when the frame has a periodic axis and some
 // atom's nk-th neighbour is not strictly closer than half a periodic length
 // (or it has fewer than nk neighbours); every later stage then does nothing.
-void launch_knn(int64_t n, const Grid &g, int nk, const double *spos, const int4 *sfix,
+void launch_knn(int64_t n, const GridArg &A, int nk, const double *spos, const int4 *sfix,
                 const int32_t *sid, const int32_t *start, int32_t *nbr_id, double *nbr_rel, int32_t *todo,
                 int32_t *todo_count, int32_t *box_fail, hipStream_t st);
 // topological order (Sec. 3) of the 18 neighbours in rel18 / id18: the first
@@ -89,12 +117,13 @@ void launch_topo(int64_t n, const double *nbr_rel, const int32_t *nbr_id, const 
 // force_full), outputs in input order.  *full_count (int32) and *job_count
 // (zeroed by the caller) count the atoms the full rule decided and the
 // candidates superposed; knn_out (nullable, [n][14] in input order) receives
-// the first 14 rows of knn_src (the Euclidean ids, rank-major).
+// the first 14 rows of knn_src (the Euclidean ids, rank-major).  host_flag
+// (nullable, pinned host memory) receives the box flag.
 void launch_match(int64_t n, const double *nbr_rel, const int32_t *nbr_id, const int32_t *sid,
                   const int8_t *species, const TablesView &T, const int32_t *code, const uint64_t *ord,
                   uint32_t mask, double cutoff, bool force_full, const MatchOut &O, int32_t *full_count,
                   unsigned long long *job_count, const int32_t *knn_src, int32_t *knn_out, const int32_t *box_fail,
-                  bool f32, hipStream_t st);
+                  int32_t *host_flag, bool f32, hipStream_t st);
 
 // int32 entries after the cell counts of a frame's count array: the scan's
 // end, the k-NN leftover counter, the full-rule counter, the box flag, then
