@@ -24,8 +24,8 @@ int ptm_selftest_det3(const double *p9);
 
 /* Key set of a triangulated sphere with k <= 14 vertices given as ntri
  * outward counter-clockwise triangles (int32 [ntri][3]): the start-edge
- * codes (k words each) of its start edges from vertices of minimum
- * degree, u ascending, then counter-clockwise around u from its
+ * codes (k words each, of which the first three are used) of its start
+ * edges from vertices of minimum degree, u ascending, then counter-clockwise around u from its
  * lowest-numbered neighbour (the first is the one the topology kernel looks
  * up).  Writes up to max_codes codes to codes[max_codes][k] and their
  * number to *n_codes.  Isomorphic graphs have equal key sets and the first

@@ -823,12 +823,16 @@ int ptm_selftest_codes(int k, const int32_t *tris, int ntri, uint64_t *codes, in
             nxt[a] |= (uint64_t)c << (4 * b);
             deg[a]++;
         }
+    for (int a = 0; a < k; a++)  // a closed surface: every edge runs both ways
+        for (int b = 0; b < k; b++)
+            if ((((nxt[a] >> (4 * b)) & 0xF) == 0xF) != (((nxt[b] >> (4 * a)) & 0xF) == 0xF)) return -1;
     auto darts = min_degree_darts(k, nxt, deg);
     int m = 0;
     for (auto &d : darts) {
         if (m >= max_codes) break;
-        uint64_t ord;
-        dart_code(k, nxt, deg, d.first, d.second, codes + (size_t)m * k, &ord);
+        uint64_t ord, rows[CODE_WORDS];
+        dart_code(k, nxt, d.first, d.second, rows, &ord);
+        for (int i = 0; i < k; i++) codes[(size_t)m * k + i] = i < CODE_WORDS ? rows[i] : 0;
         m++;
     }
     *n_codes = (int32_t)darts.size();

@@ -1604,64 +1604,22 @@ __global__ void __launch_bounds__(VB) k_voronoi_order(int64_t n, const double *_
 // and neighbour links.  The hull of the first k points is a state of that
 // same construction, so the 6-, 12- and 14-point hulls are read off it
 // after inserting points 5, 11 and 13: for each, the centre must lie
-// strictly inside, then the rotation system and the canonical start-edge
-// code are built and looked up.  Per-lane state lives in LDS, lane-minor,
-// so dynamic indices never conflict across lanes.
+// strictly inside, then the canonical start-edge code is built and looked
+// up.  Per-lane state lives in LDS, lane-minor, so dynamic indices never
+// conflict across lanes.
 constexpr int TB = 64;  // threads per block of the topology kernel
 
 // LDS of one block.  P: the neighbour vectors rounded to FP32 (the input of
 // the predicate filters; every predicate is decided exactly, so both
-// precision forms use this kernel); F: facets; H: the horizon of the
-// current insertion.  The rotation system of the 12-point hull, built
-// between insertions, packs into H and the four facet slots that hull
-// leaves free (F[20..23], which H follows in memory); the 14-point hull is
-// the last, and its rotation system takes the space of P, which is no
-// longer read.  20,480 bytes: eight blocks per CU.
+// precision forms use this kernel); F: facets; H: the horizon of the current
+// insertion, and between insertions the queue of the facet walk.  20,480
+// bytes: eight blocks per CU.
 struct TopoShared {
     float P[3][KMAX][TB];
     uint32_t F[2 * KMAX - 4][TB];
     uint32_t H[KMAX][TB];
 };
-static_assert(sizeof(float) * 3 * KMAX >= sizeof(uint64_t) * KMAX, "a 14-row rotation system fits in P");
-static_assert(offsetof(TopoShared, H) == offsetof(TopoShared, F) + sizeof(uint32_t) * (2 * KMAX - 4) * TB,
-              "H follows F");
 static_assert(sizeof(TopoShared) == 20480, "eight blocks of the topology kernel per CU");
-
-// A lane's rotation system: row x maps each neighbour y (nibble y) to the
-// vertex after y counter-clockwise around x (0xF: not a neighbour).  Rows
-// are kept complemented (0 = no neighbour), so they are built by atomic ORs
-// that need no read-modify-write round trips.
-// Rows of 16 nibbles, one 64-bit word each (the 14-point hull, in P):
-struct RotSys {
-    uint64_t (*w)[TB];
-    int t;
-    __device__ void clear(int k) const {
-        for (int x = 0; x < k; x++) w[x][t] = 0;
-    }
-    __device__ void set_next(int x, int y, int z) const {
-        atomicOr((unsigned long long *)&w[x][t], (unsigned long long)(z ^ 0xF) << (4 * y));
-    }
-    __device__ uint64_t get(int x) const { return ~w[x][t]; }
-};
-// Rows of 12 nibbles packed into 18 consecutive 32-bit words (the 12-point
-// hull: row x starts at bit 48 x, so it spans two words and starts at bit
-// 0 or 16 of the first):
-struct RotSys12 {
-    uint32_t (*w)[TB];
-    int t;
-    __device__ void clear(int) const {
-        for (int i = 0; i < 18; i++) w[i][t] = 0;
-    }
-    __device__ void set_next(int x, int y, int z) const {
-        const int bit = 48 * x + 4 * y;
-        atomicOr(&w[bit >> 5][t], (uint32_t)(z ^ 0xF) << (bit & 31));
-    }
-    __device__ uint64_t get(int x) const {
-        const int i = (48 * x) >> 5, sh = (48 * x) & 31;
-        const uint64_t two = ((uint64_t)w[i + 1][t] << 32) | w[i][t];
-        return ~((two >> sh) & 0xFFFFFFFFFFFFull);  // nibbles 12..15 read as no neighbour
-    }
-};
 
 // facet word: v0 | v1<<4 | v2<<8 | nb0<<12 | nb1<<17 | nb2<<22
 __device__ inline uint32_t fpack(int a, int b, int c, int n0, int n1, int n2) {
@@ -1872,84 +1830,123 @@ __device__ inline int lane_centre_inside(const Lane &L, int K, uint32_t &cv) {
     return 1;
 }
 
-// Start-edge code (definition in ptm_tables.cpp) of the start edge u -> v
-// with u the lowest-numbered vertex of minimum degree and v its
-// lowest-numbered neighbour.  code[] receives the K words; the return value
-// is the labelling (nibble l = vertex of label l).  One code per hull: the
-// tables hold the codes of every start edge from a vertex of minimum degree
-// of every template triangulation, so the choice among them needs no
-// search.
-template <int K, typename RS>
-__device__ uint64_t lane_start_edge_code(const RS &NT, uint64_t degs, uint64_t (&code)[K]) {
-    int mindeg = 15;
-#pragma unroll
-    for (int x = 0; x < K; x++) mindeg = min(mindeg, (int)nib(degs, x));
-    uint32_t mdmask = 0;
-#pragma unroll
-    for (int x = 0; x < K; x++) mdmask |= (uint32_t)(nib(degs, x) == (uint32_t)mindeg) << x;
-    const int bu = __builtin_ctz(mdmask);
-    const uint64_t ntu = NT.get(bu);
-    // lowest-numbered neighbour: first nibble of ntu that is not 0xF
-    uint64_t z = ~ntu;
-    z = (z | (z >> 1) | (z >> 2) | (z >> 3)) & 0x1111111111111111ull;
-    const int bv = __builtin_ctzll(z) >> 2;
-    // every nibble below is written once, from 0xF (lab) or 0 (ord, par, the
-    // signature), so a single XOR or OR sets it
-    uint64_t lab = ~0ull ^ (0xFull << (4 * bu)), ord = (uint64_t)bu, par = 0;
-    uint64_t sig = (uint64_t)mindeg << 60;
-    int y = bv;
-    for (int j = 0; j < mindeg; j++) {
-        lab ^= (uint64_t)(0xF ^ (j + 1)) << (4 * y);
-        ord |= (uint64_t)y << (4 * (j + 1));
-        par |= (uint64_t)bu << (4 * y);
-        sig |= (uint64_t)nib(degs, y) << (56 - 4 * j);
-        y = (int)nib(ntu, y);
-    }
-    code[0] = sig;
-    uint32_t nl = mindeg + 1;
-#pragma unroll
-    for (int i = 1; i < K; i++) {
-        int x = min((int)nib(ord, i), K - 1);
-        int yy = (int)nib(par, x);
-        uint64_t ntx = NT.get(x);
-        int dx = (int)nib(degs, x);
-        uint64_t row = (uint64_t)dx << 60;
-        for (int j = 0; j < dx; j++) {
-            uint32_t ly = nib(lab, yy);
-            if (ly == 0xF) {
-                ly = nl;
-                lab ^= (uint64_t)(0xF ^ nl) << (4 * yy);
-                ord |= (uint64_t)yy << (4 * nl);
-                par |= (uint64_t)x << (4 * yy);
-                nl++;
-            }
-            row |= (uint64_t)ly << (56 - 4 * j);
-            yy = min((int)nib(ntx, yy), K - 1);
-        }
-        code[i] = row;
-    }
-    return ord;
+// full adder on bit slices: a becomes the sum, the carry is returned
+__device__ inline uint32_t add_slices(uint32_t &a, uint32_t b, uint32_t c) {
+    const uint32_t carry = (a & b) | (c & (a | b));
+    a ^= b ^ c;
+    return carry;
+}
+// position of vertex x in facet w (w holds x)
+__device__ inline int fpos(uint32_t w, uint32_t x) { return (w & 0xF) == x ? 0 : (((w >> 4) & 0xF) == x ? 1 : 2); }
+// vertex i + j and link i + j (positions mod 3, i 0..2, j 0..2) of facet w
+__device__ inline int fvr(uint32_t w, int i, int j) {
+    const uint32_t v = w & 0xFFF;
+    return (int)(((v | v << 12) >> (4 * (i + j))) & 0xF);
+}
+__device__ inline int fnr(uint32_t w, int i, int j) {
+    const uint32_t l = w >> 12;
+    return (int)(((l | l << 15) >> (5 * (i + j))) & 0x1F);
 }
 
-// Rotation system and canonical code of the K-point hull now held in F: the
-// K code words into best, the labelling into ordw; returns the code's hash
-// (the table probe comes after the last insertion).
-template <int K, typename RS>
-__device__ uint64_t lane_code(const uint32_t (*F)[TB], const RS &NT, uint64_t (&best)[K], uint64_t &ordw) {
-    const int t = NT.t;
-    // every (x, y) nibble is written once
-    uint64_t degs = 0;
-    NT.clear(K);
-    for (int f = 0; f < 2 * K - 4; f++) {
-        uint32_t w = F[f][t];
-        int a = fv(w, 0), b = fv(w, 1), c = fv(w, 2);
-        NT.set_next(a, b, c);
-        NT.set_next(b, c, a);
-        NT.set_next(c, a, b);
-        degs += (1ull << (4 * a)) + (1ull << (4 * b)) + (1ull << (4 * c));
+// Start-edge code (definition in ptm_tables.cpp: a breadth-first walk over
+// the facets) of the K-point hull in F, from the start edge u -> v with u the
+// lowest-numbered vertex of minimum degree and v its lowest-numbered
+// neighbour.  code receives its words; the return value is the labelling
+// (nibble l = vertex of label l).  One code per hull: the tables hold the
+// codes of every start edge from a vertex of minimum degree of every template
+// triangulation, so the choice among them needs no search.
+//
+// The walk takes one step per facet (19 and 23, of about 45 instructions,
+// without a branch) and needs only the facets and their links.  Walking
+// around every vertex instead takes a step per directed edge (60 and 72, of
+// about 40) and a rotation system, built with as many LDS atomics.  Issue
+// bound as the rest of the kernel; measured on the whole kernel, 17.8 ->
+// 15.4 ms at 31.7 M atoms, 607 -> 520 us at 919,162, 66 -> 57 us at 256.
+template <int K>
+__device__ uint64_t lane_facet_code(TopoShared &S, int t, uint64_t (&code)[CODE_WORDS]) {
+    constexpr int NF = 2 * K - 4;
+    // vertex sets of the facets, and the degrees bit-sliced (w1, w2, w4: bits
+    // of the degree of vertex x in bit x; w8: 8 or more)
+    uint32_t m[NF], c2[NF / 2], c4[NF / 4], w1 = 0, w2 = 0, w4 = 0, w8 = 0;
+#pragma unroll
+    for (int f = 0; f < NF; f++) {
+        const uint32_t w = S.F[f][t];
+        m[f] = 1u << fv(w, 0) | 1u << fv(w, 1) | 1u << fv(w, 2);
     }
-    ordw = lane_start_edge_code<K>(NT, degs, best);
-    return code_hash(best, K);
+#pragma unroll
+    for (int f = 0; f < NF / 2; f++) c2[f] = add_slices(w1, m[2 * f], m[2 * f + 1]);
+#pragma unroll
+    for (int f = 0; f < NF / 4; f++) c4[f] = add_slices(w2, c2[2 * f], c2[2 * f + 1]);
+#pragma unroll
+    for (int f = 0; f < NF / 4; f += 2) w8 |= add_slices(w4, c4[f], f + 1 < NF / 4 ? c4[f + 1] : 0u);
+    // a triangulated sphere has a vertex of degree 3, 4 or 5
+    const uint32_t z3 = w1 & w2 & ~(w4 | w8), z4 = w4 & ~(w1 | w2 | w8), z5 = w1 & w4 & ~(w2 | w8);
+    const uint32_t z = z3 ? z3 : (z4 ? z4 : z5);
+    const uint32_t u = z ? (uint32_t)__builtin_ctz(z) : 0u;
+    // facets at u and the lowest-numbered neighbour
+    uint32_t at_u = 0, nb = 0;
+#pragma unroll
+    for (int f = 0; f < NF; f++) {
+        const uint32_t in = (m[f] >> u) & 1;
+        at_u |= in << f;
+        nb |= m[f] & (0u - in);
+    }
+    nb &= ~(1u << u);
+    const uint32_t v = nb ? (uint32_t)__builtin_ctz(nb) : 0u;
+    // of the two facets with both, the one in which v follows u
+    uint32_t at_v = 0;
+#pragma unroll
+    for (int f = 0; f < NF; f++) at_v |= ((m[f] >> v) & 1) << f;
+    const uint32_t both = at_u & at_v;
+    const int fa = both ? __builtin_ctz(both) : 0, fb = both ? 31 - __builtin_clz(both) : 0;
+    const uint32_t wa = S.F[fa][t], wb = S.F[fb][t];
+    const bool first = fvr(wa, fpos(wa, u), 1) == (int)v;
+    const int f0 = first ? fa : fb;
+    const uint32_t w0 = first ? wa : wb;
+    const int i0 = fpos(w0, u);
+    const int x2 = fvr(w0, i0, 2);
+    uint64_t lab = ~0ull ^ 0xFull << (4 * u) ^ 0xEull << (4 * v) ^ 0xDull << (4 * x2);
+    uint64_t ord = (uint64_t)u | (uint64_t)v << 4 | (uint64_t)x2 << 8;
+    uint32_t nl = 3, seen = 1u << f0;
+    // queue of facets to visit, a 16-bit entry and a row of TB each: facet |
+    // start of the entry edge in it << 5
+    typedef uint16_t __attribute__((may_alias)) entry_t;
+    entry_t *queue = reinterpret_cast<entry_t *>(&S.H[0][0]) + t;
+    uint32_t tail = (uint32_t)t * 2;  // byte offset
+    auto push = [&](uint32_t g, uint32_t start) {
+        const uint32_t fresh = (~seen >> g) & 1;
+        // (the next entry overwrites it if it does not count)
+        *reinterpret_cast<entry_t *>(reinterpret_cast<char *>(&S.H[0][0]) + tail) = (entry_t)(g | start << 5);
+        seen |= 1u << g;
+        tail = (fresh << 7) + tail;
+        return fresh;
+    };
+    push(fnr(w0, i0, 1), x2);
+    push(fnr(w0, i0, 2), u);
+    push(fnr(w0, i0, 0), v);
+    uint64_t c0 = 0, c1 = 0, bits = 0;
+#pragma unroll
+    for (int k = 0; k < NF - 1; k++) {
+        const uint32_t e = queue[k * TB];
+        const uint32_t start = e >> 5;
+        const uint32_t gw = S.F[e & 0x1F][t];  // (rows from 24 lie in H: in range for any entry)
+        const int i = fpos(gw, start), c = fvr(gw, i, 2);
+        // the facet's third vertex, labelled if it is new
+        const uint32_t lc = nib(lab, c);
+        const bool fresh = lc == 0xF;
+        const uint32_t l = fresh ? nl : lc;
+        lab ^= (uint64_t)(lc ^ l) << (4 * c);
+        ord |= (uint64_t)(fresh ? (uint32_t)c : 0u) << (4 * l);
+        nl += fresh;
+        if (k < 16) c0 |= (uint64_t)l << (4 * (k & 15));
+        else c1 |= (uint64_t)l << (4 * (k & 15));
+        const uint32_t p1 = push(fnr(gw, i, 1), c), p2 = push(fnr(gw, i, 2), start);
+        bits |= (uint64_t)(p1 | p2 << 1) << (2 * k);
+    }
+    code[0] = c0;
+    code[1] = c1;
+    code[2] = bits;
+    return ord;
 }
 
 // The 6-point hull: the only template triangulation of six points is the
@@ -1958,9 +1955,10 @@ __device__ uint64_t lane_code(const uint32_t (*F)[TB], const RS &NT, uint64_t (&
 // start-edge code (code 0 of the group; they refuse to build otherwise).  So
 // the hull either is the octahedron -- code 0, with the labelling of the
 // start edge from vertex 0 to its lowest-numbered neighbour read off the
-// rotation around vertex 0: that neighbour, the next three counter-clockwise,
-// then the one vertex not adjacent to 0 -- or has no candidate.  Only vertex
-// 0's row of the rotation system is needed, built in a register.
+// rotation around vertex 0 -- or has no candidate.  With the neighbours
+// counter-clockwise y1..y4 from that one, the facet walk from (0, y1, y2)
+// meets the one vertex not adjacent to 0 across y1->y2, then y3 and y4.  Only
+// the rotation around vertex 0 is needed, built in a register.
 __device__ inline bool lane_octahedron(const uint32_t (*F)[TB], int t, uint64_t &ordw) {
     uint64_t degs = 0, row = 0;  // row 0, complemented (0 = no neighbour)
 #pragma unroll
@@ -1981,35 +1979,34 @@ __device__ inline bool lane_octahedron(const uint32_t (*F)[TB], int t, uint64_t 
     int sum = 0;
 #pragma unroll
     for (int j = 1; j <= 4; j++) {
-        ord |= (uint64_t)y << (4 * j);
+        ord |= (uint64_t)y << (4 * (j < 3 ? j : j + 1));
         sum += y;
         y = (int)nib(nt0, y);
     }
-    ordw = ord | ((uint64_t)(15 - sum) << 20);  // the vertices 0..5 sum to 15
+    ordw = ord | ((uint64_t)(15 - sum) << 12);  // the vertices 0..5 sum to 15
     return true;
 }
 
-// code row c of group grp equals best (all K words compared)
-template <int K>
-__device__ inline bool row_equal(const TablesView &T, int grp, int32_t c, const uint64_t (&best)[K]) {
-    const uint64_t *cw = T.codes[grp] + (int64_t)c * K;
+// code row c of group grp equals best (all words compared)
+__device__ inline bool row_equal(const TablesView &T, int grp, int32_t c, const uint64_t (&best)[CODE_WORDS]) {
+    const uint64_t *cw = T.codes[grp] + (int64_t)c * CODE_WORDS;
     uint64_t diff = 0;
 #pragma unroll
-    for (int i = 0; i < K; i++) diff |= cw[i] ^ best[i];
+    for (int i = 0; i < CODE_WORDS; i++) diff |= cw[i] ^ best[i];
     return diff == 0;
 }
 
 // Table probe of a code of group grp whose first slot s held c: the code id
 // (full-code verification), or -1 when no template triangulation has it.
-template <int K>
-__device__ int32_t probe_rest(const TablesView &T, int grp, const uint64_t (&best)[K], int s, int32_t c, bool hit) {
+__device__ int32_t probe_rest(const TablesView &T, int grp, const uint64_t (&best)[CODE_WORDS], int s, int32_t c,
+                              bool hit) {
     const int mask = T.hmask[grp];
     for (int probe = 0; probe <= mask; probe++) {
         if (c < 0) return -1;
         if (hit) return c;
         s = (s + 1) & mask;
         c = T.slots[grp][s];
-        hit = c >= 0 && row_equal<K>(T, grp, c, best);
+        hit = c >= 0 && row_equal(T, grp, c, best);
     }
     return -1;
 }
@@ -2054,10 +2051,8 @@ __device__ __attribute__((always_inline)) inline void topo_atom(TopoShared &S, i
         Lane L{S, t, nbr_rel, n, p, f32_orient_bound(m32), f32_det3_bound(m32), f64_orient_bound(m64),
                f64_det3_bound(m64)};
         lane_hull_start(L);
-        const RotSys12 nt{&S.F[2 * 12 - 4], t};
-        const RotSys nt14{reinterpret_cast<uint64_t (*)[TB]>(&S.P[0][0][0]), t};
         // codes of the valid hulls, probed together after the last insertion
-        uint64_t c12[12] = {}, c14[14] = {}, h[NGRP] = {0, 0, 0};
+        uint64_t c12[CODE_WORDS] = {}, c14[CODE_WORDS] = {}, h[NGRP] = {0, 0, 0};
         bool pend[NGRP] = {false, false, false};
         uint32_t cv = 0;  // facet slots whose centre test passed
         bool ok = lane_insert(L, 4, cv) && lane_insert(L, 5, cv);
@@ -2081,9 +2076,15 @@ __device__ __attribute__((always_inline)) inline void topo_atom(TopoShared &S, i
             if (!lane_insert(L, q, cv)) break;
             const int K = q + 1;
             if (K == 12 && (want & 2)) {
-                if ((pend[1] = lane_centre_inside(L, 12, cv))) h[1] = lane_code<12>(S.F, nt, c12, ordw[1]);
+                if ((pend[1] = lane_centre_inside(L, 12, cv))) {
+                    ordw[1] = lane_facet_code<12>(S, t, c12);
+                    h[1] = code_hash(c12, CODE_WORDS);
+                }
             } else if (K == 14) {
-                if ((pend[2] = lane_centre_inside(L, 14, cv))) h[2] = lane_code<14>(S.F, nt14, c14, ordw[2]);
+                if ((pend[2] = lane_centre_inside(L, 14, cv))) {
+                    ordw[2] = lane_facet_code<14>(S, t, c14);
+                    h[2] = code_hash(c14, CODE_WORDS);
+                }
             }
         }
         cid[0] = pend[0] ? 0 : -1;  // the octahedron's code
@@ -2097,10 +2098,10 @@ __device__ __attribute__((always_inline)) inline void topo_atom(TopoShared &S, i
         // every group has a code row 0 (the tables refuse to build
         // otherwise): it stands in for a missing hit, so the rows load
         // unconditionally, before any comparison waits
-        const bool hit1 = row_equal<12>(T, 1, max(c[1], 0), c12) & (c[1] >= 0);
-        const bool hit2 = row_equal<14>(T, 2, max(c[2], 0), c14) & (c[2] >= 0);
-        cid[1] = probe_rest<12>(T, 1, c12, sl[1], c[1], hit1);
-        cid[2] = probe_rest<14>(T, 2, c14, sl[2], c[2], hit2);
+        const bool hit1 = row_equal(T, 1, max(c[1], 0), c12) & (c[1] >= 0);
+        const bool hit2 = row_equal(T, 2, max(c[2], 0), c14) & (c[2] >= 0);
+        cid[1] = probe_rest(T, 1, c12, sl[1], c[1], hit1);
+        cid[2] = probe_rest(T, 2, c14, sl[2], c[2], hit2);
     }
     for (int g = 0; g < NGRP; g++) {
         code_out[(int64_t)g * n + p] = cid[g];

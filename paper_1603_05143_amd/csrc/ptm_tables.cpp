@@ -197,34 +197,73 @@ std::vector<std::vector<int>> shell_faces(const std::vector<V3> &w) {
 
 }  // namespace
 
-// Start-edge code of a triangulated sphere, from a directed edge u->v.
-//   word 0 (signature): deg(u) in the top nibble, then deg(v), then the
-//     degrees of u's other neighbours in counter-clockwise order after v;
-//   words 1..k-1 (BFS rows): u gets label 0 and its neighbours labels
-//     1..deg(u) counter-clockwise from v; vertices are then processed in
-//     label order and vertex x (label i >= 1) emits one row: deg(x) in the
-//     top nibble, then the labels of its neighbours counter-clockwise from
-//     the vertex that labelled x, new vertices being labelled in that order.
-// The words determine the labelled rotation system.  A graph's key set is
-// the set of codes of its start edges from vertices of minimum degree;
-// isomorphisms preserve degrees and so map such start edges onto each
-// other, so the code of any one of them is found in the key set of every
-// graph it is isomorphic to (and in no other), and pairing the labellings
-// of the two start edges gives the isomorphism.  The tables hold the key
-// sets of all template triangulations; a hull needs the code of a single
-// start edge, which the kernel takes without a search.
-uint64_t dart_signature(int k, const uint64_t *nxt, const int *deg, int u, int v) {
-    (void)k;
-    uint64_t sig = ((uint64_t)deg[u] << 60) | ((uint64_t)deg[v] << 56);
-    int w = v;
-    for (int j = 1; j < deg[u]; j++) {
-        w = (int)((nxt[u] >> (4 * w)) & 0xF);
-        sig |= (uint64_t)deg[w] << (56 - 4 * j);
+// Start-edge code of a triangulated sphere, from a directed edge u->v: a
+// breadth-first walk over the facets.  The facet left of u->v has vertices u,
+// v, w, which get labels 0, 1, 2, and puts the facets across v->w, w->u and
+// u->v into the queue.  A facet taken from the queue was entered across an
+// edge a->b of its own (the reverse of its parent's edge); its third vertex c
+// gets the next label if it has none, and the facets across b->c and c->a join
+// the queue unless they were in it before.
+//   words 0, 1: the labels of c, 16 facets a word, in queue order;
+//   word 2:     two bits per facet, whether each of the two facets joined.
+// The words determine every facet's labels, hence the labelled
+// triangulation.  A graph's key set is the set of codes of its start edges
+// from vertices of minimum degree; isomorphisms preserve degrees and so map
+// such start edges onto each other, so the code of any one of them is found
+// in the key set of every graph it is isomorphic to (and in no other), and
+// pairing the labellings of the two start edges gives the isomorphism.  The
+// tables hold the key sets of all template triangulations; a hull needs the
+// code of a single start edge, which the kernel takes without a search.
+void dart_code(int k, const uint64_t *nxt, int u, int v, uint64_t *rows, uint64_t *ordp) {
+    int lab[KMAX], nl = 3;
+    for (int i = 0; i < k; i++) lab[i] = -1;
+    auto third = [&](int a, int b) { return (int)((nxt[a] >> (4 * b)) & 0xF); };
+    const int w = third(u, v);
+    lab[u] = 0;
+    lab[v] = 1;
+    lab[w] = 2;
+    uint64_t ord = (uint64_t)u | (uint64_t)v << 4 | (uint64_t)w << 8;
+    uint16_t seen[KMAX] = {};  // bit b of entry a: the facet left of a->b joined the queue
+    std::pair<int, int> queue[2 * KMAX];  // entry edges
+    int tail = 0;
+    auto mark = [&](int a, int b) {
+        const int c = third(a, b);
+        seen[a] |= (uint16_t)(1 << b);
+        seen[b] |= (uint16_t)(1 << c);
+        seen[c] |= (uint16_t)(1 << a);
+    };
+    auto push = [&](int a, int b) -> uint64_t {
+        if ((seen[a] >> b) & 1) return 0;
+        mark(a, b);
+        queue[tail++] = {a, b};
+        return 1;
+    };
+    mark(u, v);
+    push(w, v);
+    push(u, w);
+    push(v, u);
+    for (int i = 0; i < CODE_WORDS; i++) rows[i] = 0;
+    for (int f = 0; f < tail; f++) {
+        const int a = queue[f].first, b = queue[f].second, c = third(a, b);
+        if (lab[c] < 0) {
+            lab[c] = nl;
+            ord |= (uint64_t)c << (4 * nl);
+            nl++;
+        }
+        rows[f / 16] |= (uint64_t)lab[c] << (4 * (f % 16));
+        const uint64_t p1 = push(c, b), p2 = push(a, c);
+        rows[2] |= (p1 | p2 << 1) << (2 * f);
     }
-    return sig;
+    *ordp = ord;
 }
 
-void dart_code(int k, const uint64_t *nxt, const int *deg, int u, int v, uint64_t *rows, uint64_t *ordp) {
+// The vertex walk's labelling from u->v: u gets label 0 and its neighbours
+// labels 1..deg(u) counter-clockwise from v; vertices are then taken in
+// label order and label their unlabelled neighbours counter-clockwise from
+// the vertex that labelled them.  It picks the correspondence that stands for
+// its orbit under the template's rotations (build_tables): any of the orbit
+// would do, but this one fixes the rounding of the FP32 superposition.
+static uint64_t vertex_walk(int k, const uint64_t *nxt, const int *deg, int u, int v) {
     int lab[KMAX], ord[KMAX], par[KMAX];
     for (int i = 0; i < k; i++) lab[i] = -1;
     lab[u] = 0;
@@ -237,11 +276,9 @@ void dart_code(int k, const uint64_t *nxt, const int *deg, int u, int v, uint64_
         nl++;
         y = (int)((nxt[u] >> (4 * y)) & 0xF);
     }
-    rows[0] = dart_signature(k, nxt, deg, u, v);
     for (int i = 1; i < k; i++) {
         int x = ord[i];
         y = par[x];
-        uint64_t row = (uint64_t)deg[x] << 60;
         for (int j = 0; j < deg[x]; j++) {
             if (lab[y] < 0) {
                 lab[y] = nl;
@@ -249,14 +286,12 @@ void dart_code(int k, const uint64_t *nxt, const int *deg, int u, int v, uint64_
                 par[y] = x;
                 nl++;
             }
-            row |= (uint64_t)lab[y] << (56 - 4 * j);
             y = (int)((nxt[x] >> (4 * y)) & 0xF);
         }
-        rows[i] = row;
     }
     uint64_t o = 0;
     for (int i = 0; i < k; i++) o |= (uint64_t)ord[i] << (4 * i);
-    *ordp = o;
+    return o;
 }
 
 // Start edges from the vertices of minimum degree: u ascending, then v
@@ -278,8 +313,10 @@ std::vector<std::pair<int, int>> min_degree_darts(int k, const uint64_t *nxt, co
 }
 
 bool build_tables(HostTables &T, std::string &err) {
-    // per hull group: code (as vector) -> list of (template, perm)
-    std::map<std::vector<uint64_t>, std::vector<std::pair<int, uint64_t>>> bucket[NGRP];
+    // per hull group: code -> list of (template, the orbit's
+    // smallest image of the vertex walk, the same correspondence from the
+    // code's labels)
+    std::map<std::array<uint64_t, CODE_WORDS>, std::vector<std::array<uint64_t, 3>>> bucket[NGRP];
     for (int t = 0; t < NT; t++) {
         std::vector<V3> w = template_points(t);
         int k = (int)w.size();
@@ -346,7 +383,7 @@ bool build_tables(HostTables &T, std::string &err) {
         }
         int nq = (int)quads.size();
         T.ntri[t] = 1ll << nq;
-        std::set<std::vector<uint64_t>> codes_t;
+        std::set<std::array<uint64_t, CODE_WORDS>> codes_t;
         int64_t full = 0;
         for (int64_t s = 0; s < (1ll << nq); s++) {
             std::vector<std::array<int, 3>> tris = fixed;
@@ -371,19 +408,29 @@ bool build_tables(HostTables &T, std::string &err) {
                     deg[a]++;
                 }
             for (auto &d : min_degree_darts(k, nxt, deg)) {
-                uint64_t rows[KMAX], perm;
-                dart_code(k, nxt, deg, d.first, d.second, rows, &perm);
-                std::vector<uint64_t> key(rows, rows + k);
+                std::array<uint64_t, CODE_WORDS> key;
+                uint64_t perm;
+                dart_code(k, nxt, d.first, d.second, key.data(), &perm);
+                const uint64_t walk = vertex_walk(k, nxt, deg, d.first, d.second);
                 codes_t.insert(key);
                 full++;
-                // canonical orbit representative: smallest g o perm
-                uint64_t best = ~0ull;
-                for (auto &pm : gperm) {
+                // orbit representative: the rotation g with the smallest g o walk
+                auto image = [&](const std::vector<int> &pm, uint64_t labels) {
                     uint64_t img = 0;
-                    for (int lb = 0; lb < k; lb++) img |= (uint64_t)pm[(perm >> (4 * lb)) & 0xF] << (4 * lb);
-                    best = std::min(best, img);
+                    for (int lb = 0; lb < k; lb++) img |= (uint64_t)pm[(labels >> (4 * lb)) & 0xF] << (4 * lb);
+                    return img;
+                };
+                uint64_t best = ~0ull;
+                const std::vector<int> *g = nullptr;
+                for (auto &pm : gperm) {
+                    if ((uint64_t)pm[(walk >> (4 * k - 4)) & 0xF] > best >> (4 * k - 4)) continue;
+                    const uint64_t img = image(pm, walk);
+                    if (img < best) {
+                        best = img;
+                        g = &pm;
+                    }
                 }
-                bucket[group_of_template(t)][key].push_back({t, best});
+                bucket[group_of_template(t)][key].push_back({(uint64_t)t, best, image(*g, perm)});
             }
         }
         T.ncand_full[t] = full;
@@ -397,12 +444,12 @@ bool build_tables(HostTables &T, std::string &err) {
         T.cstart[g].assign(1, 0);
         T.max_cand_per_code[g] = 0;
         for (auto &kv : bucket[g]) {
-            std::vector<std::pair<int, uint64_t>> v = kv.second;
+            std::vector<std::array<uint64_t, 3>> v = kv.second;
             std::sort(v.begin(), v.end());
             v.erase(std::unique(v.begin(), v.end()), v.end());
             for (auto &pr : v) {
-                T.cand[g].push_back({pr.second, pr.first, 0});
-                T.ncand_kept[pr.first]++;
+                T.cand[g].push_back({pr[2], (int32_t)pr[0], 0});
+                T.ncand_kept[pr[0]]++;
             }
             T.max_cand_per_code[g] = std::max(T.max_cand_per_code[g], (int)v.size());
             T.cstart[g].push_back((int32_t)T.cand[g].size());
@@ -423,7 +470,7 @@ bool build_tables(HostTables &T, std::string &err) {
         T.hmask[g] = size - 1;
         T.slots[g].assign(size, -1);
         for (int c = 0; c < nc; c++) {
-            uint64_t h = code_hash(&T.codes[g][(size_t)c * k], k);
+            uint64_t h = code_hash(&T.codes[g][(size_t)c * CODE_WORDS], CODE_WORDS);
             int s = (int)(h & (uint64_t)(size - 1));
             while (T.slots[g][s] >= 0) s = (s + 1) & (size - 1);
             T.slots[g][s] = c;

@@ -18,6 +18,7 @@ constexpr int KMAX = 14; // largest neighbour shell (BCC, Table 1)
 constexpr int NMAX = KMAX + 1;
 constexpr int NGRP = 3;  // hull sizes k = 6, 12, 14
 constexpr int GMAX = 60; // largest rotation group (ICO)
+constexpr int CODE_WORDS = 3; // words of a start-edge code
 
 __host__ __device__ constexpr int template_k(int t) { return t == 0 ? 6 : (t == 4 ? 14 : 12); }
 __host__ __device__ constexpr int group_k(int g) { return g == 0 ? 6 : (g == 1 ? 12 : 14); }
@@ -43,7 +44,7 @@ struct Candidate {
 // Device view of the tables: plain pointers, passed to kernels by value.
 struct TablesView {
     const TemplateDev *tpl;               // [NT]
-    const uint64_t *codes[NGRP];          // [ncodes][k] canonical code rows
+    const uint64_t *codes[NGRP];          // [ncodes][CODE_WORDS] code rows
     const int32_t *slots[NGRP];           // [hmask+1] code id or -1
     const int32_t *cstart[NGRP];          // [ncodes+1] candidate ranges
     const Candidate *cand[NGRP];          // candidates
@@ -67,10 +68,10 @@ struct HostTables {
     int max_cand_per_code[NGRP];
 };
 
-// Hash of a code (k row words); used identically by host and device.
-__host__ __device__ inline uint64_t code_hash(const uint64_t *rows, int k) {
+// Hash of a code; used identically by host and device.
+__host__ __device__ inline uint64_t code_hash(const uint64_t *rows, int words) {
     uint64_t h = 0x243F6A8885A308D3ull;
-    for (int i = 0; i < k; i++) {
+    for (int i = 0; i < words; i++) {
         h ^= rows[i];
         h *= 0x9E3779B97F4A7C15ull;
         h ^= h >> 29;
@@ -85,8 +86,8 @@ bool build_tables(HostTables &T, std::string &err);
 // given by nxt[x] (nibble y = vertex after y counter-clockwise around x,
 // 0xF = none) and deg.  Host versions used by the generator and by the
 // self-check entry points.
-uint64_t dart_signature(int k, const uint64_t *nxt, const int *deg, int u, int v);
-void dart_code(int k, const uint64_t *nxt, const int *deg, int u, int v, uint64_t *rows, uint64_t *ordp);
+// rows: CODE_WORDS words; ordp: nibble l = vertex of label l
+void dart_code(int k, const uint64_t *nxt, int u, int v, uint64_t *rows, uint64_t *ordp);
 std::vector<std::pair<int, int>> min_degree_darts(int k, const uint64_t *nxt, const int *deg);
 
 } // namespace ptm
