@@ -548,11 +548,18 @@ __host__ __device__ inline T qcp_solve(const T S[3][3], T Ga, T Gb, T q[4], T *c
         T n2 = v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3];
         if (n2 > best) {
             best = n2;
-            T inv = n2 > T(0) ? T(1) / sqrt(n2) : T(0);
+            // (FP64: the column kept is normalised below, not each)
+            const T inv = sizeof(T) == 8 ? T(1) : (n2 > T(0) ? T(1) / sqrt(n2) : T(0));
             for (int i = 0; i < 4; i++) q[i] = v[i] * inv;
         }
     }
-    if (!(best > T(0))) { q[0] = 1; q[1] = q[2] = q[3] = 0; }
+    if (!(best > T(0))) {
+        q[0] = 1;
+        q[1] = q[2] = q[3] = 0;
+    } else if (sizeof(T) == 8) {
+        const T inv = T(1) / sqrt(best);
+        for (int i = 0; i < 4; i++) q[i] *= inv;
+    }
     if (cond) {
         T c = (lam > T(0) && best > T(0)) ? sqrt(best) / (lam * lam * lam) : T(0);
         T rho = 0;

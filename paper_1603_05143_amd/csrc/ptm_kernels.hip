@@ -1852,7 +1852,7 @@ __device__ inline int fnr(uint32_t w, int i, int j) {
 // the facets) of the K-point hull in F, from the start edge u -> v with u the
 // lowest-numbered vertex of minimum degree and v its lowest-numbered
 // neighbour.  code receives its words; the return value is the labelling
-// (nibble l = vertex of label l).  One code per hull: the tables hold the
+// (nibble x = label of vertex x).  One code per hull: the tables hold the
 // codes of every start edge from a vertex of minimum degree of every template
 // triangulation, so the choice among them needs no search.
 //
@@ -1906,7 +1906,6 @@ __device__ uint64_t lane_facet_code(TopoShared &S, int t, uint64_t (&code)[CODE_
     const int i0 = fpos(w0, u);
     const int x2 = fvr(w0, i0, 2);
     uint64_t lab = ~0ull ^ 0xFull << (4 * u) ^ 0xEull << (4 * v) ^ 0xDull << (4 * x2);
-    uint64_t ord = (uint64_t)u | (uint64_t)v << 4 | (uint64_t)x2 << 8;
     uint32_t nl = 3, seen = 1u << f0;
     // queue of facets to visit, a 16-bit entry and a row of TB each: facet |
     // start of the entry edge in it << 5
@@ -1936,7 +1935,6 @@ __device__ uint64_t lane_facet_code(TopoShared &S, int t, uint64_t (&code)[CODE_
         const bool fresh = lc == 0xF;
         const uint32_t l = fresh ? nl : lc;
         lab ^= (uint64_t)(lc ^ l) << (4 * c);
-        ord |= (uint64_t)(fresh ? (uint32_t)c : 0u) << (4 * l);
         nl += fresh;
         if (k < 16) c0 |= (uint64_t)l << (4 * (k & 15));
         else c1 |= (uint64_t)l << (4 * (k & 15));
@@ -1946,7 +1944,7 @@ __device__ uint64_t lane_facet_code(TopoShared &S, int t, uint64_t (&code)[CODE_
     code[0] = c0;
     code[1] = c1;
     code[2] = bits;
-    return ord;
+    return lab;
 }
 
 // The 6-point hull: the only template triangulation of six points is the
@@ -1959,7 +1957,7 @@ __device__ uint64_t lane_facet_code(TopoShared &S, int t, uint64_t (&code)[CODE_
 // counter-clockwise y1..y4 from that one, the facet walk from (0, y1, y2)
 // meets the one vertex not adjacent to 0 across y1->y2, then y3 and y4.  Only
 // the rotation around vertex 0 is needed, built in a register.
-__device__ inline bool lane_octahedron(const uint32_t (*F)[TB], int t, uint64_t &ordw) {
+__device__ inline bool lane_octahedron(const uint32_t (*F)[TB], int t, uint64_t &labels) {
     uint64_t degs = 0, row = 0;  // row 0, complemented (0 = no neighbour)
 #pragma unroll
     for (int f = 0; f < 8; f++) {
@@ -1975,15 +1973,15 @@ __device__ inline bool lane_octahedron(const uint32_t (*F)[TB], int t, uint64_t 
     uint64_t z = row;
     z = (z | (z >> 1) | (z >> 2) | (z >> 3)) & 0x1111111111111111ull;
     int y = __builtin_ctzll(z) >> 2;  // lowest-numbered neighbour of 0
-    uint64_t ord = 0;
+    uint32_t lab = 0;
     int sum = 0;
 #pragma unroll
     for (int j = 1; j <= 4; j++) {
-        ord |= (uint64_t)y << (4 * (j < 3 ? j : j + 1));
+        lab |= (uint32_t)(j < 3 ? j : j + 1) << (4 * y);
         sum += y;
         y = (int)nib(nt0, y);
     }
-    ordw = ord | ((uint64_t)(15 - sum) << 12);  // the vertices 0..5 sum to 15
+    labels = lab | 3u << (4 * (15 - sum));  // the vertices 0..5 sum to 15
     return true;
 }
 
@@ -2012,14 +2010,14 @@ __device__ int32_t probe_rest(const TablesView &T, int grp, const uint64_t (&bes
 }
 
 // One lane per atom: the hulls of the first 6, 12 and 14 neighbours (those
-// enabled by need: bit g for hull group g), code ids and labellings into
-// code_out / ord_out [group][n] (-1 / 0 for a group without a valid hull or
-// not needed).
+// enabled by need: bit g for hull group g), the candidates of their codes
+// (pack_range) and labellings (nibble r = label of rank r) into code_out /
+// lab_out [group][n] (-1 / 0 for a group without a candidate or not needed).
 // One atom p per lane t of a 64-lane wave, with the wave's LDS S (always
 // inlined: the LDS accesses must stay LDS instructions).
 __device__ __attribute__((always_inline)) inline void topo_atom(TopoShared &S, int t, int64_t p, int64_t n, const double *__restrict__ nbr_rel,
                           const int32_t *__restrict__ nbr_id, const TablesView &T, uint32_t need,
-                          int32_t *__restrict__ code_out, uint64_t *__restrict__ ord_out) {
+                          int32_t *__restrict__ code_out, uint64_t *__restrict__ lab_out) {
     // the neighbour ids that say which hulls are possible (the K-th neighbour
     // exists) and all KMAX relative vectors are loaded in one round trip;
     // rows past the last wanted one are stored but never read
@@ -2032,7 +2030,7 @@ __device__ __attribute__((always_inline)) inline void topo_atom(TopoShared &S, i
     for (int g = 0; g < NGRP; g++)
         if (((need >> g) & 1) && kid[g] >= 0) want |= 1u << g;
     int32_t cid[NGRP] = {-1, -1, -1};
-    uint64_t ordw[NGRP] = {0, 0, 0};
+    uint64_t labw[NGRP] = {0, 0, 0};
     if (want) {
         const int kl = (want & 4) ? 14 : ((want & 2) ? 12 : 6);  // last point to insert
         // The first six points go to LDS first: their loads were issued
@@ -2057,7 +2055,7 @@ __device__ __attribute__((always_inline)) inline void topo_atom(TopoShared &S, i
         uint32_t cv = 0;  // facet slots whose centre test passed
         bool ok = lane_insert(L, 4, cv) && lane_insert(L, 5, cv);
         if (ok && (want & 1))
-            pend[0] = lane_centre_inside(L, 6, cv) && lane_octahedron(S.F, t, ordw[0]);
+            pend[0] = lane_centre_inside(L, 6, cv) && lane_octahedron(S.F, t, labw[0]);
         // the other points (rows past the last wanted one are stored but
         // never read)
         for (int r = 6; r < KMAX; r++)
@@ -2077,12 +2075,12 @@ __device__ __attribute__((always_inline)) inline void topo_atom(TopoShared &S, i
             const int K = q + 1;
             if (K == 12 && (want & 2)) {
                 if ((pend[1] = lane_centre_inside(L, 12, cv))) {
-                    ordw[1] = lane_facet_code<12>(S, t, c12);
+                    labw[1] = lane_facet_code<12>(S, t, c12);
                     h[1] = code_hash(c12, CODE_WORDS);
                 }
             } else if (K == 14) {
                 if ((pend[2] = lane_centre_inside(L, 14, cv))) {
-                    ordw[2] = lane_facet_code<14>(S, t, c14);
+                    labw[2] = lane_facet_code<14>(S, t, c14);
                     h[2] = code_hash(c14, CODE_WORDS);
                 }
             }
@@ -2103,21 +2101,26 @@ __device__ __attribute__((always_inline)) inline void topo_atom(TopoShared &S, i
         cid[1] = probe_rest(T, 1, c12, sl[1], c[1], hit1);
         cid[2] = probe_rest(T, 2, c14, sl[2], c[2], hit2);
     }
+    int32_t range[NGRP];
     for (int g = 0; g < NGRP; g++) {
-        code_out[(int64_t)g * n + p] = cid[g];
-        ord_out[(int64_t)g * n + p] = cid[g] >= 0 ? ordw[g] : 0;
+        const int32_t *cs = T.cstart[g] + max(cid[g], 0);
+        range[g] = cid[g] >= 0 ? pack_range(cs[0], cs[1] - cs[0]) : -1;
+    }
+    for (int g = 0; g < NGRP; g++) {
+        code_out[(int64_t)g * n + p] = range[g];
+        lab_out[(int64_t)g * n + p] = cid[g] >= 0 ? labw[g] : 0;
     }
 }
 
 __global__ void __launch_bounds__(TB) k_topo(int64_t n, const double *__restrict__ nbr_rel,
                                               const int32_t *__restrict__ nbr_id, TablesView T, uint32_t need,
-                                              int32_t *__restrict__ code_out, uint64_t *__restrict__ ord_out,
+                                              int32_t *__restrict__ code_out, uint64_t *__restrict__ lab_out,
                                               const int32_t *__restrict__ box_fail) {
     __shared__ TopoShared S;
     const int t = threadIdx.x;
     const int64_t p = blockIdx.x * (int64_t)TB + t;
     if (p >= n || *box_fail) return;
-    topo_atom(S, t, p, n, nbr_rel, nbr_id, T, need, code_out, ord_out);
+    topo_atom(S, t, p, n, nbr_rel, nbr_id, T, need, code_out, lab_out);
 }
 
 // ------------------------------------------------------------------ match
@@ -2125,46 +2128,65 @@ constexpr int MB = 256;  // threads per block of the match kernels
 
 // What the match kernel keeps of each template in LDS: the normalised
 // points b (eq. 4), the pseudoinverse V+ (eq. 6), the inverses of the
-// rotation group's elements as vertex maps, k and the group order.  The
-// group's quaternions are read from the device tables.
+// rotation group's elements as vertex maps, for each vertex the elements
+// whose inverse takes vertex 0 there, G_b = sum |b|^2, k and the group
+// order.  The group's quaternions are read from the device tables.
 struct TemplateGeom {
     double b[NMAX][3];
     double vpinv[3][NMAX];
     uint64_t ginv[GMAX];
+    uint64_t gfirst[KMAX];
+    double gb;
     int32_t k, ngroup;
 };
 struct MatchShared {
     TemplateGeom geo[NT];
 };
 
-// rank vector of the representative: min over g of (c(g^-1(m)))_m, packed
-// with m = 0 in the most significant nibble.  Only the group elements whose
-// first entry is minimal can win, so the full vectors are built for those
-// alone (a vertex lies in the image of g^-1(0) for |G| / orbit elements).
-__device__ inline uint64_t rep_vector(const TemplateGeom &D, uint64_t cmap, int &gbest) {
-    uint32_t first = 16;
-    uint64_t cand = 0;  // bit g: g attains the minimal first entry
-    for (int g = 0; g < D.ngroup; g++) {
-        uint32_t f = nib(cmap, (int)nib(D.ginv[g], 0));
-        if (f < first) {
-            first = f;
-            cand = 0;
-        }
-        if (f == first) cand |= 1ull << g;
-    }
-    uint64_t best = ~0ull;
-    gbest = 0;
-    for (; cand; cand &= cand - 1) {
-        int g = __builtin_ctzll(cand);
-        uint64_t gi = D.ginv[g];
-        uint64_t v = 0;
-        for (int m = 0; m < D.k; m++) v |= (uint64_t)nib(cmap, (int)nib(gi, m)) << (4 * (15 - m));
-        if (v < best) {
-            best = v;
-            gbest = g;
+// f(r) for the ranks r < K of a hull group (6, 12 or 14), unrolled: arrays
+// indexed by r stay in registers, and lanes of different K run one code path
+template <typename F>
+__device__ inline void each_rank(int K, F f) {
+#pragma unroll
+    for (int r = 0; r < 6; r++) f(r);
+    if (K > 6) {
+#pragma unroll
+        for (int r = 6; r < 12; r++) f(r);
+        if (K > 12) {
+#pragma unroll
+            for (int r = 12; r < KMAX; r++) f(r);
         }
     }
-    return best;
+}
+
+// rank vector of the representative: min over g of (c(g^-1(m)))_m, c(v) the
+// rank at template vertex v (tv its inverse), packed with m = 0 in the most
+// significant nibble.  The first entry is the lowest rank of the orbit of
+// vertex 0, attained by the elements that gfirst names; further entries are
+// compared only until one element is left (two or three as a rule: an
+// element is fixed by the images of few vertices), and one vector is built.
+__device__ inline uint64_t rep_vector(const TemplateGeom &D, uint64_t tv, uint64_t c, int &gbest) {
+    uint64_t cand = 0;  // bit g: g attains the minimal entries so far
+    for (int r = 0; !cand && r < D.k; r++) cand = D.gfirst[nib(tv, r)];
+    for (int m = 1; (cand & (cand - 1)) && m < D.k; m++) {
+        uint32_t least = 16;
+        uint64_t keep = 0;
+        for (uint64_t rest = cand; rest; rest &= rest - 1) {
+            const int g = __builtin_ctzll(rest);
+            const uint32_t f = nib(c, (int)nib(D.ginv[g], m));
+            if (f < least) {
+                least = f;
+                keep = 0;
+            }
+            if (f == least) keep |= 1ull << g;
+        }
+        cand = keep;
+    }
+    gbest = cand ? __builtin_ctzll(cand) : 0;
+    const uint64_t gi = D.ginv[gbest];
+    uint64_t v = 0;
+    each_rank(D.k, [&](int m) { v |= (uint64_t)nib(c, (int)nib(gi, m)) << (4 * (15 - m)); });
+    return v;
 }
 
 template <typename T>
@@ -2173,23 +2195,37 @@ struct CandEval {
     T c;  // FP32 form: bound on the eigen-solve's excess of RMSD^2 (f32_excess_bound)
 };
 
+// template vertex of rank r for candidate perm (label -> vertex) and
+// labelling lab (rank -> label)
+__device__ inline int vertex_of_rank(uint64_t perm, uint64_t lab, int r) { return (int)nib(perm, (int)nib(lab, r)); }
+
+// template vertex of each observed rank
+__device__ inline uint64_t tv_of_rank(uint64_t perm, uint64_t lab, int k) {
+    uint64_t tv = 0;
+    each_rank(k, [&](int r) { tv |= (uint64_t)vertex_of_rank(perm, lab, r) << (4 * r); });
+    return tv;
+}
+
+// observed rank at each template vertex
+__device__ inline uint64_t rank_of_tv(uint64_t tv, int k) {
+    uint64_t c = 0;
+    each_rank(k, [&](int r) { c |= (uint64_t)r << (4 * nib(tv, r)); });
+    return c;
+}
+
 // eq.(3) for one candidate of K = 6, 12 or 14 neighbours (observed rank r
-// <-> template vertex tv(r); the template from the FP64 table) with the
-// observed points streamed from the (cached) neighbour vectors instead of
-// held in registers: covariance and G_a / G_b in one pass, the residual in
-// a second, each recomputing the centred points from the barycentre cb
-// (FP64, eq. 2).  K is a run-time value, so lanes of different hull sizes
-// run one code path.  Moments (FP64 only): the residual at (s, q) is also
-// G_b + s (s G_a - 2 rho), rho = sum_i a_i . R b_i = tr(R S^T); it is
-// stationary in q and s at the optimum, and its rounding error, a few ulps
-// of G_b ~ N, is at most 2e-13 in the RMSD once RMSD >= 0.01 (the
-// difference cancels below that, where the explicit second pass runs).
-template <typename T, bool Moments = false>
-__device__ inline void eval_streamed(int K, const double *__restrict__ nbr_rel, int64_t n, int64_t p,
-                                     const double (&cb)[3], const TemplateGeom &D, uint64_t tv, CandEval<T> &out) {
+// <-> template vertex tv(r); the template from the FP64 table), FP32 form,
+// with the observed points streamed from the (cached) neighbour vectors
+// instead of held in registers: covariance and G_a / G_b in one pass, the
+// residual in a second, each recomputing the centred points from the
+// barycentre cb (FP64, eq. 2).  K is a run-time value, so lanes of different
+// hull sizes run one code path.
+__device__ inline void eval_f32(int K, const double *__restrict__ nbr_rel, int64_t n, int64_t p,
+                                const double (&cb)[3], const TemplateGeom &D, uint64_t tv, CandEval<float> &out) {
     // products and sums may fuse into FMAs here (one rounding instead of two; no
     // result depends on a particular rounding)
 #pragma clang fp contract(fast)
+    typedef float T;
     T S[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
     T Gb = 0;
     double g = 0;
@@ -2217,22 +2253,11 @@ __device__ inline void eval_streamed(int K, const double *__restrict__ nbr_rel, 
     }
     const T Ga = (T)g;
     T cond = 0;
-    T lam = qcp_solve<T>(S, Ga, Gb, out.q, sizeof(T) == 4 ? &cond : nullptr);
-    if constexpr (sizeof(T) == 4) out.c = f32_excess_bound(lam, cond, Ga);
+    T lam = qcp_solve<T>(S, Ga, Gb, out.q, &cond);
+    out.c = f32_excess_bound(lam, cond, Ga);
     T s = Ga > T(0) ? lam / Ga : T(0);
     T R[3][3];
     quat_rot<T>(out.q, R);
-    if constexpr (Moments && sizeof(T) == 8) {
-        T rho = 0;
-        for (int x = 0; x < 3; x++)
-            for (int y = 0; y < 3; y++) rho += R[x][y] * S[y][x];
-        const T rm = Gb + s * (s * Ga - T(2) * rho);
-        if (rm >= T(1e-4) * T(K + 1)) {
-            out.r = sqrt(rm / T(K + 1));
-            out.s = s;
-            return;
-        }
-    }
     T res = 0;
     {
         const T bb[3] = {(T)D.b[0][0], (T)D.b[0][1], (T)D.b[0][2]};
@@ -2256,40 +2281,153 @@ __device__ inline void eval_streamed(int K, const double *__restrict__ nbr_rel, 
     out.s = s;
 }
 
-// template vertex of each observed rank for candidate perm (label -> vertex)
-// and labelling ord (label -> rank)
-__device__ inline uint64_t tv_of_rank(uint64_t perm, uint64_t ord, int k) {
-    uint64_t tv = 0;
-    for (int l = 0; l < k; l++) tv |= (uint64_t)nib(perm, l) << (4 * nib(ord, l));
-    return tv;
+// x, the same in every lane of the wave, in scalar registers
+__device__ inline int64_t uniform(int64_t x) {
+    return (int64_t)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)x) |
+                     (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(x >> 32)) << 32);
 }
 
-// observed rank at each template vertex
-__device__ inline uint64_t rank_of_tv(uint64_t perm, uint64_t ord, int k) {
-    uint64_t c = 0;
-    for (int l = 0; l < k; l++) c |= (uint64_t)nib(ord, l) << (4 * nib(perm, l));
-    return c;
+// The neighbour vectors of the wave's atoms: component d of rank r of atom a
+// (0..63) at rel[(3 r + d) n + a], rel and n in scalar registers, so the
+// loads take their addresses from a scalar base and one 32-bit offset.
+struct WavePoints {
+    const double *__restrict__ rel;
+    int64_t n;
+    __device__ inline double at(int r, int d, uint32_t a) const { return rel[(int64_t)(3 * r + d) * n + a]; }
+};
+
+// The K neighbour vectors of atom a, all in flight together.  The address of
+// a row is one scalar addition past the last row's; the empty asm keeps the
+// compiler from computing the 42 of them beforehand, where they would not fit
+// the scalar registers.
+__device__ inline void load_points(int K, const WavePoints &W, uint32_t a, double (&v)[KMAX][3]) {
+    typedef const double __attribute__((address_space(1))) *Row;
+    uint64_t row = (uint64_t)W.rel;
+    each_rank(K, [&](int r) {
+        for (int d = 0; d < 3; d++) {
+            asm volatile("" : "+s"(row));
+            v[r][d] = ((Row)row)[a];
+            row += (uint64_t)W.n * 8;
+        }
+    });
+}
+
+// x of lane src / 4 (every lane of the wave must be active)
+__device__ inline double from_lane(int src, double x) {
+    const uint64_t u = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)(uint32_t)u);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)(uint32_t)(u >> 32));
+    return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
+// x or 0, for a mask of all or no bits (also where x is not finite)
+__device__ inline double masked(double x, uint32_t mask) {
+    const uint64_t u = (uint64_t)__double_as_longlong(x);
+    return __longlong_as_double((long long)((uint64_t)((uint32_t)(u >> 32) & mask) << 32 | ((uint32_t)u & mask)));
+}
+
+// eq.(3) in FP64 for one candidate per lane, of K = 6, 12 or 14 neighbours
+// (observed rank r <-> template vertex perm(lab(r))), by the whole wave: on
+// marks the lanes that have one.  pt(r, d) is component d of rank r of the
+// lane's atom, called by every lane; sum and Ga are the sum of the atom's
+// first K points and G_a.  The template's points sum to zero (eq. 4), so the
+// covariance needs no barycentre.
+// Moments: the residual at (s, q) is also
+// G_b + s (s G_a - 2 rho), rho = sum_i a_i . R b_i = tr(R S^T); it is
+// stationary in q and s at the optimum, and its rounding error, a few ulps
+// of G_b ~ N, is at most 2e-13 in the RMSD once RMSD >= 0.01 (the
+// difference cancels below that, where the explicit sum runs).
+template <bool Moments, typename Point>
+__device__ inline void eval_f64(bool on, int K, Point pt, const double (&sum)[3], double Ga, const TemplateGeom &D,
+                                uint64_t perm, uint64_t lab, CandEval<double> &out) {
+    // products and sums may fuse into FMAs here (one rounding instead of two; no
+    // result depends on a particular rounding)
+#pragma clang fp contract(fast)
+    double S[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
+    const bool any12 = __ballot(on && K > 6) != 0, any14 = __ballot(on && K > 12) != 0;
+    const uint32_t m12 = K > 6 ? ~0u : 0u, m14 = K > 12 ? ~0u : 0u;
+    auto add_rank = [&](int r, uint32_t mask) {
+        const double *b = D.b[vertex_of_rank(perm, lab, r) + 1];
+        for (int y = 0; y < 3; y++) {
+            const double c = masked(pt(r, y), mask);
+            for (int x = 0; x < 3; x++) S[x][y] += b[x] * c;
+        }
+    };
+#pragma unroll
+    for (int r = 0; r < 6; r++) add_rank(r, ~0u);
+    if (any12) {
+#pragma unroll
+        for (int r = 6; r < 12; r++) add_rank(r, m12);
+        if (any14) {
+#pragma unroll
+            for (int r = 12; r < KMAX; r++) add_rank(r, m14);
+        }
+    }
+    double R[3][3], s = 0, a0[3], res = 0;
+    bool explicit_sum = on;
+    if (on) {
+        const double Gb = D.gb, lam = qcp_solve<double>(S, Ga, Gb, out.q);
+        s = Ga > 0 ? lam / Ga : 0;
+        quat_rot<double>(out.q, R);
+        out.s = s;
+        if (Moments) {
+            double rho = 0;
+            for (int x = 0; x < 3; x++)
+                for (int y = 0; y < 3; y++) rho += R[x][y] * S[y][x];
+            const double rm = Gb + s * (s * Ga - 2 * rho);
+            explicit_sum = !(rm >= 1e-4 * (K + 1));
+            out.r = sqrt(rm / (K + 1));
+        }
+    }
+    if (!__ballot(explicit_sum)) return;
+    auto add_point = [&](const double (&p)[3], const double *b) {
+        for (int x = 0; x < 3; x++) {
+            const double d = s * p[x] - (R[x][0] * b[0] + R[x][1] * b[1] + R[x][2] * b[2]);
+            res += d * d;
+        }
+    };
+    for (int d = 0; d < 3; d++) a0[d] = -sum[d] / (K + 1);
+    add_point(a0, D.b[0]);
+    auto resid_rank = [&](int r) {
+        double p[3];
+        for (int d = 0; d < 3; d++) p[d] = pt(r, d) + a0[d];
+        if (r < K) add_point(p, D.b[vertex_of_rank(perm, lab, r) + 1]);
+    };
+#pragma unroll
+    for (int r = 0; r < 6; r++) resid_rank(r);
+    if (any12) {
+#pragma unroll
+        for (int r = 6; r < KMAX; r++) resid_rank(r);
+    }
+    if (explicit_sum) out.r = sqrt(res / (K + 1));
+}
+
+// 16-byte stores to records of 8-byte alignment: a store of scattered records
+// costs a cycle per record and instruction, whatever its width
+typedef double double2u __attribute__((ext_vector_type(2), aligned(8)));
+typedef int32_t int4u __attribute__((ext_vector_type(4), aligned(8)));
+
+// group g's candidates (the pointers selected in registers)
+__device__ inline const Candidate *group_candidates(const TablesView &T, int g) {
+    return g == 0 ? T.cand[0] : (g == 1 ? T.cand[1] : T.cand[2]);
 }
 
 // Outputs of the winning candidate from its superposition ev and the
 // strain inputs A^T (sum over points of V+ columns times centred points, in
 // template order) and l (mean point norm).
 template <typename RT>
-__device__ inline void finish_outputs(int K, const MatchShared &M, const TablesView &T, int grp, int c, uint64_t ord,
+__device__ inline void finish_outputs(int K, const MatchShared &M, const Candidate &cd, const TablesView &T, uint64_t tv,
                                       const CandEval<RT> &ev, RT l, const RT (&At)[3][3], RT resid, double cutoff,
                                       int64_t p, int64_t n, int32_t i, const int32_t *__restrict__ nbr_id,
                                       const int8_t *__restrict__ species, const MatchOut &O) {
     // products and sums may fuse into FMAs here (one rounding instead of two; no
     // result depends on a particular rounding)
 #pragma clang fp contract(fast)
-    Candidate cd = T.cand[grp][c];
     const TemplateGeom &G = M.geo[cd.tmpl];
     const TemplateDev &D = T.tpl[cd.tmpl];  // the group's quaternions
-    const uint64_t tv = tv_of_rank(cd.perm, ord, K);
     const int type = ((double)ev.r <= cutoff) ? cd.tmpl + 1 : 0;
     if (O.best_type) O.best_type[i] = (int8_t)(cd.tmpl + 1);
     int g;
-    const uint64_t rep = rep_vector(G, rank_of_tv(cd.perm, ord, K), g);
+    const uint64_t rep = rep_vector(G, tv, rank_of_tv(tv, K), g);
     {
         // q' = q * conj(q_g), sign fixed so that the first non-zero component is positive
         const double *qg = D.gq[g];
@@ -2360,10 +2498,11 @@ __device__ inline void finish_outputs(int K, const MatchShared &M, const TablesV
             }
             ids[m] = id;
         }
-        // as 8-byte pairs (the array is 8-byte aligned)
-        int2 *no = reinterpret_cast<int2 *>(O.neighbours + (int64_t)i * KMAX);
+        // 16 bytes a store (the array is 8-byte aligned)
+        int32_t *no = O.neighbours + (int64_t)i * KMAX;
 #pragma unroll
-        for (int m = 0; m < KMAX / 2; m++) no[m] = make_int2(ids[2 * m], ids[2 * m + 1]);
+        for (int m = 0; m < 12; m += 4) *(int4u *)(no + m) = int4u{ids[m], ids[m + 1], ids[m + 2], ids[m + 3]};
+        *(int2 *)(no + 12) = make_int2(ids[12], ids[13]);
     }
     if (O.strain || O.vm_strain) {
         // Sec. 8: P of A = P U with U right-handed
@@ -2373,10 +2512,16 @@ __device__ inline void finish_outputs(int K, const MatchShared &M, const TablesV
         for (int x = 0; x < 3; x++)
             for (int y = 0; y < 3; y++) {
                 const RT s = P[x][y];
-                if (O.strain) O.strain[9 * (int64_t)i + 3 * x + y] = (double)s;
                 sq += s * s;
                 if (x == y) tr += s;
             }
+        if (O.strain) {
+            const RT *e = &P[0][0];
+            double *so = O.strain + 9 * (int64_t)i;
+#pragma unroll
+            for (int k = 0; k < 8; k += 2) *(double2u *)(so + k) = double2u{(double)e[k], (double)e[k + 1]};
+            so[8] = (double)e[8];
+        }
         // Sec. 8: von Mises shear strain of P
         if (O.vm_strain) O.vm_strain[i] = (double)sqrt(fmax(RT(1.5) * sq - RT(0.5) * tr * tr, RT(0)));
     }
@@ -2415,20 +2560,19 @@ __device__ inline void finish_outputs(int K, const MatchShared &M, const TablesV
 }
 
 
-// Outputs of the winning candidate from its superposition ev (r, q, s):
-// the strain inputs are gathered from the points in one pass (the
-// barycentre cb is known); the optional eq.(6) residual takes a second.
-template <typename RT>
-__device__ inline void finish(int K, const MatchShared &M, const TablesView &T, int grp, int c, uint64_t ord,
-                              const CandEval<RT> &ev, const double (&cb)[3], const double *__restrict__ nbr_rel,
+// Outputs of the winning candidate from its superposition ev (r, q, s), FP32
+// form: the points streamed from the (cached) neighbour vectors, about the
+// barycentre cb
+__device__ inline void finish_f32(int K, const MatchShared &M, const TablesView &T, const Candidate &cd, uint64_t lab,
+                              const CandEval<float> &ev, const double (&cb)[3], const double *__restrict__ nbr_rel,
                               double cutoff, int64_t p, int64_t n, int32_t i, const int32_t *__restrict__ nbr_id,
                               const int8_t *__restrict__ species, const MatchOut &O) {
     // products and sums may fuse into FMAs here (one rounding instead of two; no
     // result depends on a particular rounding)
 #pragma clang fp contract(fast)
-    Candidate cd = T.cand[grp][c];
+    typedef float RT;
     const TemplateGeom &D = M.geo[cd.tmpl];
-    const uint64_t tv = tv_of_rank(cd.perm, ord, K);
+    const uint64_t tv = tv_of_rank(cd.perm, lab, K);
     RT a0[3], At[3][3], l;
     strain_begin<RT>(D, cb, a0, At, l);
 #pragma unroll
@@ -2457,7 +2601,46 @@ __device__ inline void finish(int K, const MatchShared &M, const TablesView &T, 
         }
         resid /= l * l;
     }
-    finish_outputs<RT>(K, M, T, grp, c, ord, ev, l, At, resid, cutoff, p, n, i, nbr_id, species, O);
+    finish_outputs<RT>(K, M, cd, T, tv, ev, l, At, resid, cutoff, p, n, i, nbr_id, species, O);
+}
+
+// The same in FP64, from the atom's neighbour vectors v and their sum
+__device__ inline void finish_f64(int K, const MatchShared &M, const TablesView &T, const Candidate &cd, uint64_t lab,
+                              const CandEval<double> &ev, const double (&v)[KMAX][3], const double (&sum)[3],
+                              double cutoff, int64_t p, int64_t n, int32_t i, const int32_t *__restrict__ nbr_id,
+                              const int8_t *__restrict__ species, const MatchOut &O) {
+    // products and sums may fuse into FMAs here (one rounding instead of two; no
+    // result depends on a particular rounding)
+#pragma clang fp contract(fast)
+    const TemplateGeom &D = M.geo[cd.tmpl];
+    const uint64_t tv = tv_of_rank(cd.perm, lab, K);
+    const double cb[3] = {sum[0] / (K + 1), sum[1] / (K + 1), sum[2] / (K + 1)};
+    double a0[3], At[3][3], l;
+    strain_begin<double>(D, cb, a0, At, l);
+    each_rank(K, [&](int r) {
+        double ar[3];
+        for (int d = 0; d < 3; d++) ar[d] = (v[r][d] - cb[d]);
+        strain_add<double>(D, (int)nib(tv, r) + 1, ar, At, l);
+    });
+    l /= (K + 1);
+    double resid = 0;
+    if (O.strain_residual) {
+        // eq.(6) residual: sum over points of |V_i A^T - a_i|^2 / l^2
+        auto add = [&](const double *b, const double (&ay)[3]) {
+            for (int y = 0; y < 3; y++) {
+                double d = b[0] * At[0][y] + b[1] * At[1][y] + b[2] * At[2][y] - ay[y];
+                resid += d * d;
+            }
+        };
+        add(D.b[0], a0);
+        each_rank(K, [&](int r) {
+            double ar[3];
+            for (int d = 0; d < 3; d++) ar[d] = (v[r][d] - cb[d]);
+            add(D.b[(int)nib(tv, r) + 1], ar);
+        });
+        resid /= l * l;
+    }
+    finish_outputs<double>(K, M, cd, T, tv, ev, l, At, resid, cutoff, p, n, i, nbr_id, species, O);
 }
 
 __device__ inline void write_none(const MatchOut &O, int32_t i) {
@@ -2491,7 +2674,10 @@ __device__ inline void load_templates(MatchShared &M, const TablesView &T) {
         else (&M.geo[t].vpinv[0][0])[e - NB] = (&T.tpl[t].vpinv[0][0])[e - NB];
     }
     for (int w = threadIdx.x; w < NT * GMAX; w += blockDim.x) M.geo[w / GMAX].ginv[w % GMAX] = T.tpl[w / GMAX].ginv[w % GMAX];
+    for (int w = threadIdx.x; w < NT * KMAX; w += blockDim.x)
+        M.geo[w / KMAX].gfirst[w % KMAX] = T.tpl[w / KMAX].gfirst[w % KMAX];
     if ((int)threadIdx.x < NT) {
+        M.geo[threadIdx.x].gb = T.tpl[threadIdx.x].gb;
         M.geo[threadIdx.x].k = T.tpl[threadIdx.x].k;
         M.geo[threadIdx.x].ngroup = T.tpl[threadIdx.x].ngroup;
     }
@@ -2502,37 +2688,57 @@ __device__ inline void load_templates(MatchShared &M, const TablesView &T) {
 // One kernel superposes every candidate correspondence of the atoms' hull
 // codes (eq. 3), takes the decision of Alg. 1 and writes the outputs of the
 // winner.  A wave owns 64 consecutive atoms (cell order):
-//  A. lane = atom: the Euclidean neighbour list is copied out, the
-//     barycentres of the 6-, 12- and 14-neighbour groups (eq. 2, FP64) and
-//     the first candidate of each code go to LDS, the enabled candidates
-//     are counted;
+//  A. lane = atom: the Euclidean neighbour list is copied out, the candidate
+//     ranges of the codes go to LDS with the enabled candidates counted, and
+//     the points are read once, all 42 components in flight together: FP64
+//     keeps them in registers up to the finish, with the sums of the first
+//     6, 12 and 14 of them (and G_a) in LDS;
 //  B. the wave's candidates form one job list, atom after atom and within
 //     an atom in (group, candidate) order, superposed 64 at a time with
 //     lane = job (the superposition takes the hull size as a run-time
-//     value, so a chunk mixing sizes runs one code path); after each chunk
-//     every atom lane folds its jobs of the chunk, in order, into its
-//     running minimum and marks itself as the owner of its jobs in the
-//     next chunk;
+//     value, so a chunk mixing sizes runs one code path); a bit set of the
+//     atoms' first jobs tells each lane its atom.  In FP64 a job takes its
+//     atom's points from that atom's lane (ds_bpermute), and the next
+//     chunk's candidates are read during this one; after each chunk every
+//     atom lane folds its jobs of the chunk, in order, into its running
+//     minimum;
 //  C. an atom whose decision the common rule cannot take (a near tie, an
 //     FP32 margin that the error bounds do not clear) is decided by the
 //     full rule in FP64 by the whole wave; every other lane finishes its
 //     own winner (the hull size is a run-time value there too, so a wave
 //     mixing sizes runs one code path).
-// Nothing per candidate leaves the chip: the neighbour vectors are read
-// once per atom in A and again from the caches by the jobs and the finish.
+// Nothing per candidate leaves the chip.
+//
+// What bounds it (FP64, 31.7 M atoms, three candidates an atom): of some
+// 95,000 cycles of a wave, 31,000 go to the superpositions and 20,000 to the
+// finish, both near the issue rate of two waves per SIMD, 13,000 to the fold,
+// 12,000 to the first read of the points.  When every job and the finish read
+// the points for themselves, rank after rank, a wave waited for each: lanes
+// that share an atom hit on each other's outstanding misses, and the waves of
+// a CU hold more points than its caches, so 47 GB were fetched for 10.7 GB of
+// points.  Measured: 14.9 -> 11.5 ms (17 GB); 486 -> 389 us at 918,996 atoms.
+// All 42 components of a job read by the job itself: 14.0 ms; held at three
+// waves per SIMD (168 registers) they spill, each spill a wait: 15.8 ms.
+// FP32 keeps the points of a job in the caches (a job is shorter, four waves
+// per SIMD hide more, and its 128 registers would not hold them).
 
 // LDS of one wave
 template <typename RT>
 struct MatchWaveLds {
-    double cb[NGRP][3][64];  // barycentre of each hull group of the wave's atoms
-    int32_t k0[NGRP][64];    // first candidate of each atom's code in the group's list
-    int32_t cnt[64];         // enabled candidates of each atom per group, 8 bits each
-    int32_t off[64];         // each atom's first job
-    int32_t owner[64];       // the atom of each job of the current chunk
-    double r[64];            // the current chunk's results: RMSD,
-    RT qs[5][64];            // quaternion and scale,
-    float d2[64];            // FP32 form: excess bound (f32_excess_bound),
-    int32_t cand[64];        // candidate index in the group's list
+    // sum of the first 6, 12 and 14 points of the wave's atoms (FP32 form:
+    // their barycentre), and G_a (FP64 form)
+    double sum[NGRP][3][64];
+    double ga[NGRP][sizeof(RT) == 8 ? 64 : 1];
+    uint64_t lab[NGRP][sizeof(RT) == 8 ? 64 : 1];  // labellings (FP32 form: read per job)
+    int32_t range[NGRP][64];  // candidates of each atom's code (see pack_range), the enabled ones counted
+    uint64_t starts[64];      // bit t of word c: an atom's first job is job 64 c + t
+    uint16_t off[64];         // each atom's first job
+    uint8_t act[64];          // the atoms with jobs, in order
+    double r[64];             // the current chunk's results: RMSD,
+    RT qs[5][64];             // quaternion and scale,
+    float d2[64];             // FP32 form: excess bound (f32_excess_bound),
+    // template << 56 | permutation (FP32 form: candidate index in the group's list)
+    typename std::conditional<sizeof(RT) == 8, uint64_t, int32_t>::type cand[64];
 };
 // working LDS of a block of NW waves
 template <typename RT, int NW>
@@ -2550,35 +2756,28 @@ struct MatchLds {
     MatchWork<RT, NW> work;
 };
 
-// one job: the candidate with tv of the atom at p, K neighbours, barycentre cb
-template <typename RT>
-__device__ inline void eval_job(int K, const double *__restrict__ nbr_rel, int64_t n, int64_t p,
-                                const double (&cb)[3], const TemplateGeom &D, uint64_t tv, CandEval<RT> &ev) {
-    // (FP64: the residual from the moments where that is exact enough)
-    eval_streamed<RT, true>(K, nbr_rel, n, p, cb, D, tv, ev);
-}
-
-// The full rule of Alg. 1 for the wave's atom a (at p), in FP64, by the
+// The full rule of Alg. 1 for the atom at p, in FP64, by the
 // whole wave: lane j superposes the atom's j-th candidate (the codes of one
 // atom hold at most 64 together, checked when the tables are built), the
 // minimum r* is reduced over the wave, every enabled candidate within the
 // tie tolerance of r* computes its representative vector, the (template,
 // representative) minimum is reduced, and lane 0 finishes the winner.
-// Wave-uniform arguments; cbw: the barycentres of the wave's atoms.
-__device__ __noinline__ void full_rule(const MatchShared &M, const TablesView &T, int64_t n, int64_t p, int a,
-                          const double (&cbw)[NGRP][3][64], const double *__restrict__ nbr_rel,
+// Wave-uniform arguments.
+__device__ __noinline__ void full_rule(const MatchShared &M, const TablesView &T, int64_t n, int64_t p,
+                          const double *__restrict__ nbr_rel,
                           const int32_t *__restrict__ nbr_id, const int32_t *__restrict__ sid,
                           const int8_t *__restrict__ species, const int32_t *__restrict__ code,
-                          const uint64_t *__restrict__ ords, uint32_t mask, double cutoff, const MatchOut &O) {
+                          const uint64_t *__restrict__ labs, uint32_t mask, double cutoff, const MatchOut &O) {
     const int lane = threadIdx.x & 63;
     const int32_t i = sid[p];
+    const WavePoints W = {(const double *)uniform((int64_t)(nbr_rel + p)), uniform(n)};
     int32_t c0[NGRP], nc[NGRP];
-    uint64_t ord[NGRP];
+    uint64_t lab[NGRP];
     for (int g = 0; g < NGRP; g++) {
         const int32_t cid = code[(int64_t)g * n + p];
-        ord[g] = ords[(int64_t)g * n + p];
-        c0[g] = cid >= 0 ? T.cstart[g][cid] : 0;
-        nc[g] = cid >= 0 ? T.cstart[g][cid + 1] - c0[g] : 0;
+        lab[g] = labs[(int64_t)g * n + p];
+        c0[g] = range_first(cid);
+        nc[g] = range_count(cid);
     }
     // this lane's candidate
     int g = -1, c = -1, tmpl = 99;
@@ -2598,13 +2797,22 @@ __device__ __noinline__ void full_rule(const MatchShared &M, const TablesView &T
     CandEval<double> ev = {0, 0, {0, 0, 0, 0}};
     if (g >= 0) {
         cd = T.cand[g][c];
-        if ((mask >> cd.tmpl) & 1) {
-            tmpl = cd.tmpl;
-            const double cb[3] = {cbw[g][0][a], cbw[g][1][a], cbw[g][2][a]};
-            const int K = group_k(g);
-            eval_streamed<double>(K, nbr_rel, n, p, cb, M.geo[cd.tmpl], tv_of_rank(cd.perm, ord[g], K), ev);
-            r = ev.r;
-        }
+        if ((mask >> cd.tmpl) & 1) tmpl = cd.tmpl;
+    }
+    {
+        const bool on = tmpl < 99;
+        const int K = on ? group_k(g) : 6;
+        double sum[3] = {0, 0, 0}, gs = 0;
+        for (int q = 0; q < K; q++)
+            for (int d = 0; d < 3; d++) {
+                const double x = W.at(q, d, 0);
+                sum[d] += x;
+                gs += x * x;
+            }
+        const double ga = gs - (sum[0] * sum[0] + sum[1] * sum[1] + sum[2] * sum[2]) / (K + 1);
+        eval_f64<false>(on, K, [&](int q, int d) { return W.at(q, d, 0); }, sum, ga, M.geo[on ? tmpl : 0], cd.perm,
+                        on ? (g == 0 ? lab[0] : (g == 1 ? lab[1] : lab[2])) : 0, ev);
+        if (on) r = ev.r;
     }
     double m1 = r;
     for (int off = 32; off > 0; off >>= 1) m1 = fmin(m1, __shfl_xor(m1, off));
@@ -2618,7 +2826,8 @@ __device__ __noinline__ void full_rule(const MatchShared &M, const TablesView &T
     if (r <= m1 + 1e-12) {
         int gsel;
         kt = tmpl;
-        krep = rep_vector(M.geo[tmpl], rank_of_tv(cd.perm, ord[g], group_k(g)), gsel);
+        const uint64_t tv = tv_of_rank(cd.perm, lab[g], group_k(g));
+        krep = rep_vector(M.geo[tmpl], tv, rank_of_tv(tv, group_k(g)), gsel);
     }
     int bt = kt, bl = lane;
     uint64_t brep = krep;
@@ -2639,11 +2848,14 @@ __device__ __noinline__ void full_rule(const MatchShared &M, const TablesView &T
     we.s = __shfl(ev.s, bl);
     for (int k = 0; k < 4; k++) we.q[k] = __shfl(ev.q[k], bl);
     if (lane == 0) {
-        const double cb[3] = {cbw[wg][0][a], cbw[wg][1][a], cbw[wg][2][a]};
-        if (wg == 0) finish<double>(6, M, T, 0, wc, ord[0], we, cb, nbr_rel, cutoff, p, n, i, nbr_id, species, O);
-        else if (wg == 1)
-            finish<double>(12, M, T, 1, wc, ord[1], we, cb, nbr_rel, cutoff, p, n, i, nbr_id, species, O);
-        else finish<double>(14, M, T, 2, wc, ord[2], we, cb, nbr_rel, cutoff, p, n, i, nbr_id, species, O);
+        const int K = group_k(wg);
+        double v[KMAX][3], sum[3] = {0, 0, 0};
+        load_points(K, W, 0, v);
+        each_rank(K, [&](int q) {
+            for (int d = 0; d < 3; d++) sum[d] += v[q][d];
+        });
+        finish_f64(K, M, T, T.cand[wg][wc], wg == 0 ? lab[0] : (wg == 1 ? lab[1] : lab[2]), we, v, sum, cutoff, p, n,
+                   i, nbr_id, species, O);
     }
 }
 
@@ -2678,7 +2890,7 @@ __device__ void match_block(const MatchShared &M, const TablesView &Tl, const Ma
                             int64_t first, int64_t n, const double *__restrict__ nbr_rel,
                             const int32_t *__restrict__ nbr_id, const int32_t *__restrict__ sid,
                             const int8_t *__restrict__ species, const TablesView &T,
-                            const int32_t *__restrict__ code, const uint64_t *__restrict__ ords, uint32_t mask,
+                            const int32_t *__restrict__ code, const uint64_t *__restrict__ labs, uint32_t mask,
                             double cutoff, int force_full, const MatchOut &O, int32_t *__restrict__ full_count,
                             unsigned long long *__restrict__ job_count, const int32_t *__restrict__ knn_src,
                             int32_t *__restrict__ knn_out, int apw) {
@@ -2687,9 +2899,20 @@ __device__ void match_block(const MatchShared &M, const TablesView &Tl, const Ma
     const int64_t wbase = first + (int64_t)wv * apw;
     const int64_t p = wbase + lane;
     const bool live = lane < apw && p < n;
+    // (a wave past the last atom reads that one's)
+    const WavePoints WP = {(const double *)uniform((int64_t)(nbr_rel + min(wbase, n - 1))), uniform(n)};
 
     // A. lane = atom
     int cnt[NGRP] = {0, 0, 0};
+    double v[KMAX][3];  // FP64 form: the atom's points, from here to the finish
+    int32_t rg[NGRP] = {-1, -1, -1};
+    if (live)
+        for (int g = 0; g < NGRP; g++) {
+            rg[g] = code[(int64_t)g * n + p];
+            if constexpr (sizeof(RT) == 8) W.lab[g][lane] = labs[(int64_t)g * n + p];
+        }
+    if constexpr (sizeof(RT) == 8) load_points(KMAX, WP, live ? (uint32_t)lane : 0u, v);
+    W.starts[lane] = 0;
     if (live) {
         if (knn_out) {
             // the Euclidean order (Sec. 3) whatever the ordering of the hulls
@@ -2697,29 +2920,16 @@ __device__ void match_block(const MatchShared &M, const TablesView &Tl, const Ma
 #pragma unroll
             for (int m = 0; m < KMAX; m++) knn_out[(int64_t)i * KMAX + m] = knn_src[(int64_t)m * n + p];
         }
-        // barycentres of the centre and the first 6, 12 and 14 neighbours
-        double s[3] = {0, 0, 0};
-#pragma unroll
-        for (int r = 0; r < KMAX; r++) {
-            for (int d = 0; d < 3; d++) s[d] += nbr_rel[((int64_t)r * 3 + d) * n + p];
-#pragma unroll
-            for (int g = 0; g < NGRP; g++)
-                if (r + 1 == group_k(g))
-                    for (int d = 0; d < 3; d++) W.cb[g][d][lane] = s[d] / (group_k(g) + 1);
-        }
         for (int g = 0; g < NGRP; g++) {
-            const int32_t cid = code[(int64_t)g * n + p];
-            int k0 = 0;
-            if (cid >= 0) {
-                k0 = T.cstart[g][cid];
-                const int k1 = T.cstart[g][cid + 1];
-                if ((mask & ALL_TEMPLATES) == ALL_TEMPLATES) cnt[g] = k1 - k0;
-                else
-                    for (int k = k0; k < k1; k++) cnt[g] += (mask >> T.cand[g][k].tmpl) & 1;
+            const int k0 = range_first(rg[g]);
+            cnt[g] = range_count(rg[g]);
+            if ((mask & ALL_TEMPLATES) != ALL_TEMPLATES) {
+                const int k1 = k0 + cnt[g];
+                cnt[g] = 0;
+                for (int k = k0; k < k1; k++) cnt[g] += (mask >> T.cand[g][k].tmpl) & 1;
             }
-            W.k0[g][lane] = k0;
+            W.range[g][lane] = pack_range(k0, cnt[g]);
         }
-        W.cnt[lane] = cnt[0] | (cnt[1] << 8) | (cnt[2] << 16);
     }
     // job offsets: exclusive scan over the wave
     const int mine = cnt[0] + cnt[1] + cnt[2];
@@ -2728,83 +2938,162 @@ __device__ void match_block(const MatchShared &M, const TablesView &Tl, const Ma
         const int y = __shfl_up(my_off, d);
         if (lane >= d) my_off += y;
     }
-    const int jobs = __shfl(my_off, 63);
+    const int jobs = __builtin_amdgcn_readlane(my_off, 63);
     my_off -= mine;
-    W.off[lane] = my_off;
+    W.off[lane] = (uint16_t)my_off;
+    const uint64_t active = __ballot(mine > 0);
+    wave_lds_sync();
+    if (mine > 0) {
+        W.act[__popcll(active & ((1ull << lane) - 1))] = (uint8_t)lane;
+        atomicOr((unsigned long long *)&W.starts[my_off >> 6], 1ull << (my_off & 63));
+    }
     if (lane == 0 && jobs > 0) atomicAdd(job_count, (unsigned long long)jobs);
-    for (int t = my_off; t < min(my_off + mine, 64); t++) W.owner[t] = lane;  // owners of the first chunk
+    if (live) {
+        // barycentres of the centre and the first 6, 12 and 14 neighbours
+        double s[3] = {0, 0, 0}, gs = 0;
+#pragma unroll
+        for (int r = 0; r < KMAX; r++) {
+            for (int d = 0; d < 3; d++) {
+                if constexpr (sizeof(RT) == 4) {
+                    s[d] += WP.at(r, d, (uint32_t)lane);
+                } else {
+                    s[d] += v[r][d];
+                    gs = __builtin_fma(v[r][d], v[r][d], gs);
+                }
+            }
+#pragma unroll
+            for (int g = 0; g < NGRP; g++)
+                if (r + 1 == group_k(g)) {
+                    for (int d = 0; d < 3; d++) W.sum[g][d][lane] = sizeof(RT) == 4 ? s[d] / (group_k(g) + 1) : s[d];
+                    // (the centre is the origin, the barycentre far shorter
+                    // than the points: nothing cancels)
+                    if constexpr (sizeof(RT) == 8)
+                        W.ga[g][lane] = gs - (s[0] * s[0] + s[1] * s[1] + s[2] * s[2]) * (1.0 / (group_k(g) + 1));
+                }
+        }
+    }
     wave_lds_sync();
 
     // B. jobs, 64 at a time
-    double m1 = INFINITY, m2 = INFINITY, b1 = 0.0, lo2 = INFINITY;
-    int arg_g = -1, arg_c = -1;
-    RT wq[4] = {1, 0, 0, 0}, ws = 0;
-    for (int c0 = 0; c0 < jobs; c0 += 64) {
+    struct Job {
+        int a, g, k;   // atom, group, candidate index
+        uint64_t cand;  // template << 56 | permutation
+    };
+    int begun = 0;  // atoms whose first job lies in an earlier chunk
+    auto job = [&](int c0) {
+        Job J = {lane, 0, 0, 0};
+        if (c0 >= jobs) return J;
+        const uint64_t starts = (uint64_t)uniform((int64_t)W.starts[c0 >> 6]);
         if (c0 + lane < jobs) {
-            const int a = W.owner[lane];
-            int j = c0 + lane - W.off[a];
-            const int32_t cn = W.cnt[a];
-            int g = 0;
-            if (j >= (cn & 0xFF)) {
-                j -= cn & 0xFF;
-                g = 1;
-                if (j >= ((cn >> 8) & 0xFF)) {
-                    j -= (cn >> 8) & 0xFF;
-                    g = 2;
+            J.a = W.act[begun + __popcll(starts & ((2ull << lane) - 1)) - 1];
+            int j = c0 + lane - W.off[J.a];
+            const int32_t r0 = W.range[0][J.a], r1 = W.range[1][J.a], r2 = W.range[2][J.a];
+            int32_t rj = r0;
+            if (j >= range_count(r0)) {
+                j -= range_count(r0);
+                J.g = 1;
+                rj = r1;
+                if (j >= range_count(r1)) {
+                    j -= range_count(r1);
+                    J.g = 2;
+                    rj = r2;
                 }
             }
-            const int64_t pa = wbase + a;
-            int k = W.k0[g][a];
+            const Candidate *list = group_candidates(T, J.g);
+            J.k = range_first(rj);
             if ((mask & ALL_TEMPLATES) == ALL_TEMPLATES) {
-                k += j;
+                J.k += j;
             } else {
                 // the j-th enabled candidate of the code
-                for (;; k++)
-                    if ((mask >> T.cand[g][k].tmpl) & 1) {
+                for (;; J.k++)
+                    if ((mask >> list[J.k].tmpl) & 1) {
                         if (j == 0) break;
                         j--;
                     }
             }
-            const Candidate cd = T.cand[g][k];
-            const uint64_t ord = ords[(int64_t)g * n + pa];
-            const double cb[3] = {W.cb[g][0][a], W.cb[g][1][a], W.cb[g][2][a]};
-            const int K = group_k(g);
-            CandEval<RT> ev;
-            eval_job<RT>(K, nbr_rel, n, pa, cb, M.geo[cd.tmpl], tv_of_rank(cd.perm, ord, K), ev);
+            J.cand = list[J.k].perm | (uint64_t)list[J.k].tmpl << 56;
+        }
+        begun += __popcll(starts);
+        return J;
+    };
+    double m1 = INFINITY, m2 = INFINITY, b1 = 0.0, lo2 = INFINITY;
+    int arg_g = -1;
+    decltype(W.cand[0] + 0) arg_c = 0;
+    RT wq[5] = {1, 0, 0, 0, 0};  // quaternion and scale of the best job
+    Job J = job(0);
+    for (int c0 = 0; c0 < jobs; c0 += 64) {
+        // (the next chunk's candidates are on the way during this one)
+        const Job next = job(c0 + 64);
+        const bool on = c0 + lane < jobs;
+        const int K = group_k(J.g);
+        const uint64_t perm = J.cand & ((1ull << 56) - 1);
+        const TemplateGeom &D = M.geo[J.cand >> 56];
+        CandEval<RT> ev;
+        const double sum[3] = {W.sum[J.g][0][J.a], W.sum[J.g][1][J.a], W.sum[J.g][2][J.a]};
+        if constexpr (sizeof(RT) == 4) {
+            if (on) {
+                const uint64_t lab = labs[(int64_t)J.g * n + wbase + J.a];
+                eval_f32(K, nbr_rel, n, wbase + J.a, sum, D, tv_of_rank(perm, lab, K), ev);
+            }
+        } else {
+            const int src = 4 * J.a;
+            eval_f64<true>(on, K, [&](int r, int d) { return from_lane(src, v[r][d]); }, sum, W.ga[J.g][J.a], D, perm,
+                           W.lab[J.g][J.a], ev);
+        }
+        if (on) {
             W.r[lane] = (double)ev.r;
             for (int e = 0; e < 4; e++) W.qs[e][lane] = ev.q[e];
             W.qs[4][lane] = ev.s;
-            if constexpr (sizeof(RT) == 4) W.d2[lane] = ev.c;
-            W.cand[lane] = k;
+            if constexpr (sizeof(RT) == 4) {
+                W.d2[lane] = ev.c;
+                W.cand[lane] = J.k;
+            } else {
+                W.cand[lane] = J.cand;
+            }
         }
+        J = next;
         wave_lds_sync();
         if (mine > 0) {
             // this atom's jobs of the chunk, in order (group, then
             // candidate); strict comparisons: ties go to the earlier job
             const int lo = max(my_off, c0), hi = min(my_off + mine, c0 + 64);
-            for (int t = lo; t < hi; t++) {
-                const int jj = t - my_off;
-                const int g = jj < cnt[0] ? 0 : (jj < cnt[0] + cnt[1] ? 1 : 2);
-                const int u = t - c0;
-                const double r = W.r[u];
-                double b = 0.0;
-                if constexpr (sizeof(RT) == 4) b = rmsd_f32_bound(r, (double)W.d2[u]);
-                if (r < m1) {
-                    if constexpr (sizeof(RT) == 4) lo2 = fmin(lo2, m1 - b1);  // the previous winner joins the others
-                    b1 = b;
-                    m2 = m1;
-                    m1 = r;
-                    arg_g = g;
-                    arg_c = W.cand[u];
-                    for (int e = 0; e < 4; e++) wq[e] = W.qs[e][u];
-                    ws = W.qs[4][u];
-                } else {
-                    if (r < m2) m2 = r;
-                    if constexpr (sizeof(RT) == 4) lo2 = fmin(lo2, r - b);
+            int bt = -1;
+            if constexpr (sizeof(RT) == 4) {
+                for (int t = lo; t < hi; t++) {
+                    const double r = W.r[t - c0], b = rmsd_f32_bound(r, (double)W.d2[t - c0]);
+                    if (r < m1) {
+                        lo2 = fmin(lo2, m1 - b1);  // the previous winner joins the others
+                        b1 = b;
+                        m2 = m1;
+                        m1 = r;
+                        bt = t;
+                    } else {
+                        if (r < m2) m2 = r;
+                        lo2 = fmin(lo2, r - b);
+                    }
+                }
+            } else {
+                for (int t = lo; t < hi; t += 4) {  // four on the way at a time
+                    double r[4];
+                    for (int e = 0; e < 4; e++) r[e] = W.r[(t + e) & 63];
+                    for (int e = 0; e < 4; e++) {
+                        const double x = t + e < hi ? r[e] : INFINITY;
+                        if (x < m1) {
+                            m2 = m1;
+                            m1 = x;
+                            bt = t + e;
+                        } else if (x < m2) {
+                            m2 = x;
+                        }
+                    }
                 }
             }
-            // owners of the next chunk (its jobs have read this one's)
-            for (int t = max(my_off, c0 + 64); t < min(my_off + mine, c0 + 128); t++) W.owner[t - c0 - 64] = lane;
+            if (bt >= 0) {  // the best job so far is one of this chunk's
+                const int jj = bt - my_off, u = bt - c0;
+                arg_g = jj < cnt[0] ? 0 : (jj < cnt[0] + cnt[1] ? 1 : 2);
+                arg_c = W.cand[u];
+                for (int e = 0; e < 5; e++) wq[e] = W.qs[e][u];
+            }
         }
         wave_lds_sync();
     }
@@ -2815,23 +3104,21 @@ __device__ void match_block(const MatchShared &M, const TablesView &Tl, const Ma
     // working precision; the others take the full rule.
     bool full = false;
     int cls = -1;  // hull group of the winner to finish below, -1 for none
-    double cbw[3] = {0, 0, 0};
     if (live) {
-        full = arg_c >= 0 && (force_full || !(m2 > m1 + 1e-12));
+        full = arg_g >= 0 && (force_full || !(m2 > m1 + 1e-12));
         if constexpr (sizeof(RT) == 4) {
-            if (arg_c >= 0) full = full || !(lo2 - (m1 + b1) > 1e-12) || fabs(m1 - cutoff) <= b1;
+            if (arg_g >= 0) full = full || !(lo2 - (m1 + b1) > 1e-12) || fabs(m1 - cutoff) <= b1;
         } else {
             // RMSDs from the moments carry up to 2e-13 each: near ties and
             // the cut-off get that much room (the full rule uses explicit
             // residuals)
-            if (arg_c >= 0) full = full || !(m2 > m1 + 2e-12) || fabs(m1 - cutoff) <= 1e-12;
+            if (arg_g >= 0) full = full || !(m2 > m1 + 2e-12) || fabs(m1 - cutoff) <= 1e-12;
         }
         if (!full) {
-            if (arg_c < 0) {
+            if (arg_g < 0) {
                 write_none(O, sid[p]);
             } else {
                 cls = arg_g;
-                for (int d = 0; d < 3; d++) cbw[d] = W.cb[arg_g][d][lane];
             }
         }
     }
@@ -2840,29 +3127,43 @@ __device__ void match_block(const MatchShared &M, const TablesView &Tl, const Ma
     while (fb) {
         const int a = __builtin_ctzll(fb);
         fb &= fb - 1;
-        full_rule(M, Tl, n, wbase + a, a, W.cb, nbr_rel, nbr_id, sid, species, code, ords, mask, cutoff, Ol);
+        full_rule(M, Tl, n, wbase + a, nbr_rel, nbr_id, sid, species, code, labs, mask, cutoff, Ol);
     }
 
     // every lane finishes its own winner, whatever its hull size
     if (cls >= 0) {
         const int32_t iw = sid[p];
-        const uint64_t ord = ords[(int64_t)cls * n + p];
+        uint64_t lab;
+        Candidate cd;
+        if constexpr (sizeof(RT) == 4) {
+            lab = labs[(int64_t)cls * n + p];
+            cd = group_candidates(T, cls)[arg_c];
+        } else {
+            lab = W.lab[cls][lane];
+            cd.perm = arg_c & ((1ull << 56) - 1);
+            cd.tmpl = (int32_t)(arg_c >> 56);
+        }
         CandEval<RT> ev;
         ev.r = (RT)m1;
         for (int e = 0; e < 4; e++) ev.q[e] = wq[e];
-        ev.s = ws;
-        finish<RT>(group_k(cls), M, T, cls, arg_c, ord, ev, cbw, nbr_rel, cutoff, p, n, iw, nbr_id, species, O);
+        ev.s = wq[4];
+        const int K = group_k(cls);
+        const double sum[3] = {W.sum[cls][0][lane], W.sum[cls][1][lane], W.sum[cls][2][lane]};
+        if constexpr (sizeof(RT) == 4)
+            finish_f32(K, M, T, cd, lab, ev, sum, nbr_rel, cutoff, p, n, iw, nbr_id, species, O);
+        else
+            finish_f64(K, M, T, cd, lab, ev, v, sum, cutoff, p, n, iw, nbr_id, species, O);
     }
 }
 
-// The match kernel: blocks of four waves, 256 atoms each.  FP64: three
-// blocks per CU (168 VGPRs at most) with the LDS of three; FP32: four (128
-// VGPRs at most, the spills only around the rare full-rule call).
+// The match kernel: blocks of four waves, 256 atoms each.  FP64: two blocks
+// per CU (256 VGPRs, 84 of them an atom's points); FP32: four (128 VGPRs at
+// most, the spills only around the rare full-rule call).
 template <typename RT>
-__global__ void __launch_bounds__(MB, sizeof(RT) == 4 ? 4 : 3) k_match(int64_t n, const double *__restrict__ nbr_rel,
+__global__ void __launch_bounds__(MB, sizeof(RT) == 4 ? 4 : 2) k_match(int64_t n, const double *__restrict__ nbr_rel,
                                                 const int32_t *__restrict__ nbr_id, const int32_t *__restrict__ sid,
                                                 const int8_t *__restrict__ species, TablesView T,
-                                                const int32_t *__restrict__ code, const uint64_t *__restrict__ ords,
+                                                const int32_t *__restrict__ code, const uint64_t *__restrict__ labs,
                                                 uint32_t mask, double cutoff, int force_full, MatchOut O,
                                                 int32_t *__restrict__ full_count,
                                                 unsigned long long *__restrict__ job_count,
@@ -2878,7 +3179,7 @@ __global__ void __launch_bounds__(MB, sizeof(RT) == 4 ? 4 : 3) k_match(int64_t n
     }
     load_templates(L.M, T);
     match_block<RT, MB / 64>(L.M, L.T, L.O, L.work, (int64_t)blockIdx.x * (MB / 64) * apw, n, nbr_rel, nbr_id, sid, species, T,
-                             code, ords, mask, cutoff, force_full, O, full_count, job_count, knn_src, knn_out,
+                             code, labs, mask, cutoff, force_full, O, full_count, job_count, knn_src, knn_out,
                              apw);
 }
 

@@ -109,7 +109,7 @@ void launch_knn(int64_t n, const GridArg &A, int nk, const double *spos, const i
 void launch_voronoi(int64_t n, const double *rel18, const int32_t *id18, uint32_t *vf, uint32_t *vlive,
                     double *nbr_rel, int32_t *nbr_id, const int32_t *box_fail, hipStream_t st);
 // hulls of the first 6 / 12 / 14 neighbours (need: bit g for group g);
-// code ids and labellings into code / ord [group][n]
+// candidate ranges of the codes and labellings into code / ord [group][n]
 void launch_topo(int64_t n, const double *nbr_rel, const int32_t *nbr_id, const TablesView &T, uint32_t need,
                  int32_t *code, uint64_t *ord, const int32_t *box_fail, hipStream_t st);
 // match stage: superposition of every candidate of the codes, decision

@@ -336,6 +336,7 @@ bool build_tables(HostTables &T, std::string &err) {
             V3 bj = (1.0 / l) * (w[j] - c);
             D.b[j + 1][0] = bj.x; D.b[j + 1][1] = bj.y; D.b[j + 1][2] = bj.z;
         }
+        for (int j = 0; j <= k; j++) D.gb += D.b[j][0] * D.b[j][0] + D.b[j][1] * D.b[j][1] + D.b[j][2] * D.b[j][2];
         // pseudoinverse (B^T B)^-1 B^T
         double g[3][3] = {{0}};
         for (int i = 0; i <= k; i++)
@@ -368,6 +369,7 @@ bool build_tables(HostTables &T, std::string &err) {
                 inv |= (uint64_t)j << (4 * pm[j]);
             }
             D.ginv[gi2] = inv;
+            D.gfirst[inv & 0xF] |= 1ull << gi2;
             mat_to_quat(G[gi2], D.gq[gi2]);
             gperm.push_back(pm);
         }
@@ -462,6 +464,11 @@ bool build_tables(HostTables &T, std::string &err) {
         }
         if (g == 0 && nc != 1) {  // the hull kernel takes the octahedron's code as code 0
             err = "template tables: more than one code for six points";
+            return false;
+        }
+        // candidate ranges travel packed (pack_range)
+        if (T.cand[g].size() >= ((size_t)1 << RANGE_BITS) || T.max_cand_per_code[g] >= 1 << (31 - RANGE_BITS)) {
+            err = "template tables: too many candidates for hull size " + std::to_string(k);
             return false;
         }
         T.ncodes[g] = nc;

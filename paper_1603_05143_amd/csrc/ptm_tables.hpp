@@ -32,6 +32,8 @@ struct TemplateDev {
     double b[NMAX][3];      // eq.(4)-normalised points, row 0 = centre, row j+1 = vertex j
     double vpinv[3][NMAX];  // Moore-Penrose pseudoinverse of b (3 x N), eq.(6)
     uint64_t ginv[GMAX];    // nibble m = g^-1(m) for every group element g
+    uint64_t gfirst[KMAX];  // bit g: g^-1(0) = this vertex
+    double gb;              // sum of |b|^2
     double gq[GMAX][4];     // unit quaternion (w,x,y,z) of R_g, R_g w_j = w_{g(j)}
 };
 
@@ -67,6 +69,14 @@ struct HostTables {
     int64_t ncodes_t[NT];    // distinct table keys (start-edge codes) per template
     int max_cand_per_code[NGRP];
 };
+
+// The candidates of a code in its group's list, as the hull kernel passes
+// them on: number << 20 | first (the tables are refused when that overflows),
+// or -1 for none.
+constexpr int RANGE_BITS = 20;
+__host__ __device__ inline int32_t pack_range(int32_t first, int32_t count) { return count << RANGE_BITS | first; }
+__host__ __device__ inline int32_t range_first(int32_t r) { return r < 0 ? 0 : r & ((1 << RANGE_BITS) - 1); }
+__host__ __device__ inline int32_t range_count(int32_t r) { return r < 0 ? 0 : r >> RANGE_BITS; }
 
 // Hash of a code; used identically by host and device.
 __host__ __device__ inline uint64_t code_hash(const uint64_t *rows, int words) {
