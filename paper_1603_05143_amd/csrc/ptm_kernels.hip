@@ -3279,45 +3279,57 @@ void launch_rmsd_histogram(int64_t n, const int8_t *best_type, const double *rms
 // Sec. 7: smallest rotation angle of conj(q1) q2 q_h over the template's
 // proper rotations (identity only for type NONE), as 2 atan2(|v|, |w|) of
 // the best product, which stays accurate near zero.  Invalid types give NaN.
+// Blocks stride over the pairs, 256 at a time.  A wave of mixed types would
+// scan the longest list among its lanes, so the pairs of a round are regrouped
+// by type (wave ballots give each its slot): the lanes load their pairs in
+// order and form the products m, which change places through LDS with the
+// angles on the way back, so every access of global memory is in order.
+// Bound by HBM: 16.8 M pairs of 73 bytes take 291 us, 253 at the rate of a
+// large copy; 434 us when whole groups (24 elements, 60 for ICO) were scanned,
+// the pairs loaded in slot order and the tables staged for every 256 pairs.
 template <bool Vec>
 __global__ void __launch_bounds__(256) k_misorientation(int64_t n, TablesView T, const int8_t *__restrict__ type,
                                                         const double *__restrict__ q1, const double *__restrict__ q2,
                                                         double *__restrict__ angle) {
-    // every template's rotation group, staged in LDS: lanes of one type read
-    // the same word (a broadcast)
-    __shared__ double4 G[NT * GMAX];
-    __shared__ int gbase[NT + 1];
-    if (threadIdx.x == 0) {
-        int b = 0;
-        for (int t = 0; t < NT; t++) {
-            gbase[t] = b;
-            b += T.tpl[t].ngroup;
-        }
-        gbase[NT] = b;
-    }
-    __syncthreads();
-    for (int t = 0; t < NT; t++)
-        for (int h = threadIdx.x; h < T.tpl[t].ngroup; h += blockDim.x) {
-            const double *g = T.tpl[t].gq[h];
-            G[gbase[t] + h] = make_double4(g[0], g[1], g[2], g[3]);
-        }
-    __syncthreads();
-    // Waves of mixed types would each scan the largest group among their
-    // lanes (60 for ICO).  The block's pairs are regrouped by type first
-    // (wave ballots give each lane its slot) and every lane takes the pair
-    // in its slot: waves then mostly scan one group, and its LDS words are
-    // broadcasts.  Out-of-range types form a class of their own.
+    // products and sums may fuse into FMAs here (one rounding instead of two; no
+    // result depends on a particular rounding)
+#pragma clang fp contract(fast)
     constexpr int NCLS = NT + 2;  // types 0..NT, then invalid
+    __shared__ double4 G[NT][SCAN_MAX];  // lanes of one type read the same word (a broadcast)
+    __shared__ int rows[NT + 1], any_sign[NT + 1];
     __shared__ int32_t s_cnt[4][NCLS];
-    __shared__ int64_t s_i[256];
-    {
-        const int64_t i0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    __shared__ double s_m[4][256], s_angle[256];
+    __shared__ uint16_t s_who[256];  // thread | class << 8 of the pair in a slot
+    for (int w = threadIdx.x; w < NT * SCAN_MAX; w += blockDim.x) {
+        const double *g = T.tpl[w / SCAN_MAX].scan[w % SCAN_MAX];
+        G[w / SCAN_MAX][w % SCAN_MAX] = make_double4(g[0], g[1], g[2], g[3]);
+    }
+    if (threadIdx.x <= NT) {
+        rows[threadIdx.x] = threadIdx.x ? T.tpl[threadIdx.x - 1].nscan : 0;
+        any_sign[threadIdx.x] = threadIdx.x ? T.tpl[threadIdx.x - 1].all_signs : 0;
+    }
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int64_t rounds = (n + 255) / 256;
+    for (int64_t round = blockIdx.x; round < rounds; round += gridDim.x) {
+        const int64_t i = round * 256 + tid;
         int cls = -1;
-        if (i0 < n) {
-            const int t0 = type[i0];
-            cls = (t0 < 0 || t0 > NT) ? NT + 1 : t0;
+        double m0 = 0, m1 = 0, m2 = 0, m3 = 0;
+        if (i < n) {
+            const int t = type[i];
+            double a0, a1, a2, a3, b0, b1, b2, b3;
+            if (Vec) {  // 16-byte aligned quaternion arrays
+                const double2 *p1 = (const double2 *)(q1 + 4 * i), *p2 = (const double2 *)(q2 + 4 * i);
+                const double2 u0 = p1[0], u1 = p1[1], v0 = p2[0], v1 = p2[1];
+                a0 = u0.x, a1 = -u0.y, a2 = -u1.x, a3 = -u1.y;  // conj(q1)
+                b0 = v0.x, b1 = v0.y, b2 = v1.x, b3 = v1.y;
+            } else {
+                a0 = q1[4 * i], a1 = -q1[4 * i + 1], a2 = -q1[4 * i + 2], a3 = -q1[4 * i + 3];
+                b0 = q2[4 * i], b1 = q2[4 * i + 1], b2 = q2[4 * i + 2], b3 = q2[4 * i + 3];
+            }
+            cls = (t < 0 || t > NT) ? NT + 1 : t;
+            m0 = a0 * b0 - a1 * b1 - a2 * b2 - a3 * b3, m1 = a0 * b1 + a1 * b0 + a2 * b3 - a3 * b2;
+            m2 = a0 * b2 - a1 * b3 + a2 * b0 + a3 * b1, m3 = a0 * b3 + a1 * b2 - a2 * b1 + a3 * b0;
         }
-        const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
         uint64_t bal[NCLS];
 #pragma unroll
         for (int k = 0; k < NCLS; k++) bal[k] = __ballot(cls == k);
@@ -3335,56 +3347,56 @@ __global__ void __launch_bounds__(256) k_misorientation(int64_t n, TablesView T,
             if (k == cls) slot = total + before + __popcll(bal[k] & ((1ull << lane) - 1));
             total += tk;
         }
-        if (cls >= 0) s_i[slot] = i0;
-        __syncthreads();
-        if ((int)threadIdx.x >= total) return;
-    }
-    const int64_t i = s_i[threadIdx.x];
-    const int ty = type[i];
-    double a0, a1, a2, a3, b0, b1, b2, b3;
-    if (Vec) {  // 16-byte aligned quaternion arrays
-        const double2 *p1 = (const double2 *)(q1 + 4 * i), *p2 = (const double2 *)(q2 + 4 * i);
-        const double2 u0 = p1[0], u1 = p1[1], v0 = p2[0], v1 = p2[1];
-        a0 = u0.x, a1 = -u0.y, a2 = -u1.x, a3 = -u1.y;  // conj(q1)
-        b0 = v0.x, b1 = v0.y, b2 = v1.x, b3 = v1.y;
-    } else {
-        a0 = q1[4 * i], a1 = -q1[4 * i + 1], a2 = -q1[4 * i + 2], a3 = -q1[4 * i + 3];
-        b0 = q2[4 * i], b1 = q2[4 * i + 1], b2 = q2[4 * i + 2], b3 = q2[4 * i + 3];
-    }
-    const double m0 = a0 * b0 - a1 * b1 - a2 * b2 - a3 * b3, m1 = a0 * b1 + a1 * b0 + a2 * b3 - a3 * b2;
-    const double m2 = a0 * b2 - a1 * b3 + a2 * b0 + a3 * b1, m3 = a0 * b3 + a1 * b2 - a2 * b1 + a3 * b0;
-    if (ty < 0 || ty > NT) {
-        angle[i] = NAN;
-        return;
-    }
-    // the w of m q_h is a dot product: scan the group for the largest |w|,
-    // then form the vector part of that one product only
-    double bw = fabs(m0);
-    int best = -1;
-    if (ty > 0) {
-        const int h0 = gbase[ty - 1], h1 = gbase[ty];
-        for (int h = h0; h < h1; h++) {
-            const double4 g = G[h];
-            const double c0 = fabs(m0 * g.x - m1 * g.y - m2 * g.z - m3 * g.w);
-            if (c0 > bw) {
-                bw = c0;
-                best = h;
-            }
+        if (cls >= 0) {
+            s_m[0][slot] = m0;
+            s_m[1][slot] = m1;
+            s_m[2][slot] = m2;
+            s_m[3][slot] = m3;
+            s_who[slot] = (uint16_t)(tid | cls << 8);
         }
+        __syncthreads();
+        if (tid < total) {
+            const int who = s_who[tid] & 0xFF, ty = s_who[tid] >> 8;
+            m0 = s_m[0][tid], m1 = s_m[1][tid], m2 = s_m[2][tid], m3 = s_m[3][tid];
+            double a = NAN;
+            if (ty <= NT) {
+                // the w of m q_h is a dot product: scan for the largest |w|,
+                // then form the vector part of that one product only
+                const bool moduli = any_sign[ty];
+                const double x0 = moduli ? fabs(m0) : m0, x1 = moduli ? fabs(m1) : m1;
+                const double x2 = moduli ? fabs(m2) : m2, x3 = moduli ? fabs(m3) : m3;
+                double bw = fabs(m0);
+                int best = -1;
+                for (int h = 0; h < rows[ty]; h++) {
+                    const double4 g = G[ty - 1][h];
+                    const double c0 = fabs(x0 * g.x + x1 * g.y + x2 * g.z + x3 * g.w);
+                    if (c0 > bw) {
+                        bw = c0;
+                        best = h;
+                    }
+                }
+                double c1 = m1, c2 = m2, c3 = m3;
+                if (best >= 0) {
+                    double4 g = G[ty - 1][best];
+                    if (moduli)
+                        g = make_double4(copysign(g.x, m0), copysign(g.y, m1), copysign(g.z, m2), copysign(g.w, m3));
+                    g.y = -g.y, g.z = -g.z, g.w = -g.w;
+                    c1 = m0 * g.y + m1 * g.x + m2 * g.w - m3 * g.z;
+                    c2 = m0 * g.z - m1 * g.w + m2 * g.x + m3 * g.y;
+                    c3 = m0 * g.w + m1 * g.z - m2 * g.y + m3 * g.x;
+                }
+                a = 2.0 * atan2(sqrt(c1 * c1 + c2 * c2 + c3 * c3), bw);
+            }
+            s_angle[who] = a;
+        }
+        __syncthreads();
+        if (i < n) angle[i] = s_angle[tid];
     }
-    double c1 = m1, c2 = m2, c3 = m3;
-    if (best >= 0) {
-        const double4 g = G[best];
-        c1 = m0 * g.y + m1 * g.x + m2 * g.w - m3 * g.z;
-        c2 = m0 * g.z - m1 * g.w + m2 * g.x + m3 * g.y;
-        c3 = m0 * g.w + m1 * g.z - m2 * g.y + m3 * g.x;
-    }
-    angle[i] = 2.0 * atan2(sqrt(c1 * c1 + c2 * c2 + c3 * c3), bw);
 }
 
 void launch_misorientation(int64_t n, const TablesView &T, const int8_t *type, const double *q1, const double *q2,
                            double *angle, hipStream_t st) {
-    const dim3 grid((unsigned)((n + 255) / 256));
+    const dim3 grid(stream_blocks(n));
     if ((uintptr_t)q1 % 16 == 0 && (uintptr_t)q2 % 16 == 0)
         hipLaunchKernelGGL(k_misorientation<true>, grid, dim3(256), 0, st, n, T, type, q1, q2, angle);
     else

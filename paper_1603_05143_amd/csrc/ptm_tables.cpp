@@ -312,6 +312,44 @@ std::vector<std::pair<int, int>> min_degree_darts(int k, const uint64_t *nxt, co
     return out;
 }
 
+// TemplateDev::scan from the group's quaternions
+static bool scan_rows(TemplateDev &D) {
+    std::vector<std::array<double, 4>> rows;
+    std::vector<int> members;
+    for (int g = 0; g < D.ngroup; g++) {
+        std::array<double, 4> a;
+        for (int c = 0; c < 4; c++) a[c] = std::fabs(D.gq[g][c]) < 1e-9 ? 0.0 : std::fabs(D.gq[g][c]);
+        size_t r = 0;
+        for (; r < rows.size(); r++) {
+            double d = 0;
+            for (int c = 0; c < 4; c++) d = std::max(d, std::fabs(rows[r][c] - a[c]));
+            if (d < 1e-9) break;
+        }
+        if (r == rows.size()) {
+            rows.push_back(a);
+            members.push_back(0);
+        }
+        members[r]++;
+    }
+    // the elements are distinct rotations, so a pattern of z non-zero moduli
+    // has every choice of signs when it has 2^(z-1) elements
+    D.all_signs = 1;
+    for (size_t r = 0; r < rows.size(); r++) {
+        int nz = 0;
+        for (double v : rows[r]) nz += v != 0;
+        if (members[r] != 1 << (nz - 1)) D.all_signs = 0;
+    }
+    if (!D.all_signs) {
+        rows.clear();
+        for (int g = 0; g < D.ngroup; g++) rows.push_back({D.gq[g][0], -D.gq[g][1], -D.gq[g][2], -D.gq[g][3]});
+    }
+    D.nscan = (int)rows.size();
+    if (D.nscan > SCAN_MAX) return false;
+    for (int r = 0; r < D.nscan; r++)
+        for (int c = 0; c < 4; c++) D.scan[r][c] = rows[r][c];
+    return true;
+}
+
 bool build_tables(HostTables &T, std::string &err) {
     // per hull group: code -> list of (template, the orbit's
     // smallest image of the vertex walk, the same correspondence from the
@@ -373,6 +411,7 @@ bool build_tables(HostTables &T, std::string &err) {
             mat_to_quat(G[gi2], D.gq[gi2]);
             gperm.push_back(pm);
         }
+        if (!scan_rows(D)) { err = "rotation group too large to scan"; return false; }
 
         // faces and triangulations
         std::vector<std::vector<int>> faces = shell_faces(w);

@@ -19,6 +19,7 @@ constexpr int NMAX = KMAX + 1;
 constexpr int NGRP = 3;  // hull sizes k = 6, 12, 14
 constexpr int GMAX = 60; // largest rotation group (ICO)
 constexpr int CODE_WORDS = 3; // words of a start-edge code
+constexpr int SCAN_MAX = 24;  // rows of TemplateDev::scan
 
 __host__ __device__ constexpr int template_k(int t) { return t == 0 ? 6 : (t == 4 ? 14 : 12); }
 __host__ __device__ constexpr int group_k(int g) { return g == 0 ? 6 : (g == 1 ? 12 : 14); }
@@ -28,12 +29,18 @@ __host__ __device__ constexpr int group_of_template(int t) { return t == 0 ? 0 :
 struct TemplateDev {
     int k;
     int ngroup;
-    int pad0, pad1;
+    int nscan;      // rows of scan
+    int all_signs;  // scan holds moduli, every choice of signs of which is in the group
     double b[NMAX][3];      // eq.(4)-normalised points, row 0 = centre, row j+1 = vertex j
     double vpinv[3][NMAX];  // Moore-Penrose pseudoinverse of b (3 x N), eq.(6)
     uint64_t ginv[GMAX];    // nibble m = g^-1(m) for every group element g
     uint64_t gfirst[KMAX];  // bit g: g^-1(0) = this vertex
     double gb;              // sum of |b|^2
+    // The group for a search of the largest |w| of a product (k_misorientation):
+    // the cubic and icosahedral rotations are, up to a common sign, all choices
+    // of signs of few patterns of moduli (11 and 17), of which the signs that
+    // make every term positive win; otherwise the elements (w, -x, -y, -z).
+    double scan[SCAN_MAX][4];
     double gq[GMAX][4];     // unit quaternion (w,x,y,z) of R_g, R_g w_j = w_{g(j)}
 };
 
