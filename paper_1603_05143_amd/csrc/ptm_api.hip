@@ -35,7 +35,7 @@ size_t frame_bytes(int64_t n, int64_t cells, int nbounds, bool topo) {
     b += align_up(24 * (size_t)n);           // sorted positions
     b += align_up(4 * (size_t)n * KMAX);      // neighbour ids
     b += align_up(8 * (size_t)n * KMAX * 3);  // neighbour vectors
-    b += align_up(4 * (size_t)n * NGRP);      // code ids
+    b += align_up(4 * (size_t)n * NGRP);      // candidate ranges of the codes
     b += align_up(8 * (size_t)n * NGRP);      // labellings
     b += align_up(8 * 7 * (size_t)nbounds);   // bounds partials
     b += align_up(8 * 7 * (size_t)serve_bounds_items(n));  // persistent serving: per-item bounds

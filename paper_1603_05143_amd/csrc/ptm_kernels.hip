@@ -1735,11 +1735,12 @@ __device__ int lane_insert(const Lane &L, int p, uint32_t &cv) {
     if (vis == 0) return 0;  // p inside: never a vertex
     const int nvis = __builtin_popcount(vis);
     // horizon edges (a -> b) of the visible facets f whose neighbour g is
-    // not visible, one per start vertex: H[a] = b | g << 4 | f << 9.  Inner
-    // edges write to row KMAX - 1, which is no start vertex (a < p <=
-    // KMAX - 1), so the loop body has no branch.
+    // not visible, one per start vertex: H[a] = b | g << 4 | f << 9 | s << 14,
+    // s the slot of the new facet (a, b, p): the freed slots, then two new
+    // ones, in the order met.  Inner edges write to row KMAX - 1, which is no
+    // start vertex (a < p <= KMAX - 1), so the loop body has no branch.
     uint32_t hv = 0, he = 0;  // start and end vertices of the horizon
-    uint64_t pred = 0;        // nibble b: a of the horizon edge a -> b
+    uint32_t slots = vis | 3u << nf;
     int nh = 0;
     bool bad = false;
     for (uint32_t vm = vis; vm; vm &= vm - 1) {  // visible facets only
@@ -1751,46 +1752,41 @@ __device__ int lane_insert(const Lane &L, int p, uint32_t &cv) {
             bad |= g >= nf;  // broken link (cannot happen with exact predicates)
             const bool hz = !((vis >> g) & 1);
             const int ha = fv(w, e), hb = fv(w, e == 2 ? 0 : e + 1);
-            S.H[hz ? ha : KMAX - 1][t] = (uint32_t)hb | ((uint32_t)g << 4) | ((uint32_t)f << 9);
+            S.H[hz ? ha : KMAX - 1][t] = (uint32_t)hb | ((uint32_t)g << 4) | ((uint32_t)f << 9) |
+                                         ((uint32_t)__builtin_ctz(slots | 1u << 31) << 14);
             hv |= (uint32_t)hz << ha;
             he |= (uint32_t)hz << hb;
-            pred |= (uint64_t)(hz ? ha : 0) << (4 * hb);
+            slots &= slots - (uint32_t)hz;  // (drops the lowest slot, or nothing)
             nh += hz;
         }
     }
     // a horizon of nvis+2 edges <=> no earlier vertex is swallowed; one
     // edge leaves and one enters every horizon vertex
     if (bad || nh != nvis + 2 || __builtin_popcount(hv) != nh || he != hv) return 0;
-    // slots: freed visible facets first (increasing), then two new ones, in
-    // increasing order of the start vertex; then the new facet (a, b, p)
-    // links to g across a -> b, to the facet of b across b -> p and to the
-    // facet of pred(a) across p -> a, and g's link turns from the visible
-    // facet to the new one (an XOR: every link changes at most once, so no
-    // read-modify-write is needed)
-    uint64_t slo = 0, shi = 0;  // 5-bit slot per start vertex
-    uint32_t freed = vis;
-    int nf_new = nf;
-    for (uint32_t m = hv; m; m &= m - 1) {
-        int sl;
-        if (freed) {
-            sl = __builtin_ctz(freed);
-            freed &= freed - 1;
-        } else {
-            sl = nf_new++;
-        }
-        set5(slo, shi, __builtin_ctz(m), sl);
-    }
-    for (uint32_t m = hv; m; m &= m - 1) {
-        const int a = __builtin_ctz(m);
-        const uint32_t hw = S.H[a][t];
+    // once around the horizon: the new facet (a, b, p) links to g across
+    // a -> b, to the next one across b -> p and to the last one across p -> a
+    // (so each edge is read once, a step ahead, and no table of slots per
+    // vertex is needed), and g's link turns from the visible facet to the new
+    // one (an XOR: every link changes at most once, so no read-modify-write
+    // is needed)
+    int a = __builtin_ctz(hv);
+    uint32_t hw = S.H[a][t];
+    uint32_t last = (hw >> 14) & 0x1F;  // the first edge is taken at the end of the round
+    a = (int)(hw & 0xF);
+    hw = S.H[a][t];
+    for (int k = 0; k < nh; k++) {
         const int b = hw & 0xF, g = (hw >> 4) & 0x1F, f = (hw >> 9) & 0x1F;
-        const int sa = field5(slo, shi, a);
-        S.F[sa][t] = fpack(a, b, p, g, field5(slo, shi, b), field5(slo, shi, (int)nib(pred, a)));
+        const uint32_t sa = (hw >> 14) & 0x1F;
+        const uint32_t next = S.H[b][t];
         // g (not visible, so never a slot taken here) holds the edge b -> a
         // as its edge eg; only its links may have changed
         const uint32_t gw = S.F[g][t];
+        S.F[sa][t] = fpack(a, b, p, g, (int)((next >> 14) & 0x1F), (int)last);
         const int eg = (fv(gw, 0) == b) ? 0 : ((fv(gw, 1) == b) ? 1 : 2);
-        atomicXor(&S.F[g][t], (uint32_t)(f ^ sa) << (12 + 5 * eg));
+        atomicXor(&S.F[g][t], ((uint32_t)f ^ sa) << (12 + 5 * eg));
+        last = sa;
+        a = b;
+        hw = next;
     }
     cv &= ~vis;  // the freed slots hold new facets
     return 1;
