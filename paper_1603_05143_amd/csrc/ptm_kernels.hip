@@ -1763,6 +1763,8 @@ __device__ int lane_insert(const Lane &L, int p, uint32_t &cv) {
     // a horizon of nvis+2 edges <=> no earlier vertex is swallowed; one
     // edge leaves and one enters every horizon vertex
     if (bad || nh != nvis + 2 || __builtin_popcount(hv) != nh || he != hv) return 0;
+    // (with the slots in a table of 5-bit fields per vertex the kernel took
+    // 15.3 ms at 31.7 M atoms, where it takes 13.6)
     // once around the horizon: the new facet (a, b, p) links to g across
     // a -> b, to the next one across b -> p and to the last one across p -> a
     // (so each edge is read once, a step ahead, and no table of slots per
@@ -1857,7 +1859,8 @@ __device__ inline int fnr(uint32_t w, int i, int j) {
 // around every vertex instead takes a step per directed edge (60 and 72, of
 // about 40) and a rotation system, built with as many LDS atomics.  Issue
 // bound as the rest of the kernel; measured on the whole kernel, 17.8 ->
-// 15.4 ms at 31.7 M atoms, 607 -> 520 us at 919,162, 66 -> 57 us at 256.
+// 15.4 ms at 31.7 M atoms, 607 -> 520 us at 918,996, 66 -> 57 us at 256
+// (13.6 ms with the new facets linked around the horizon, lane_insert).
 template <int K>
 __device__ uint64_t lane_facet_code(TopoShared &S, int t, uint64_t (&code)[CODE_WORDS]) {
     constexpr int NF = 2 * K - 4;
@@ -2397,11 +2400,6 @@ __device__ inline void eval_f64(bool on, int K, Point pt, const double (&sum)[3]
     if (explicit_sum) out.r = sqrt(res / (K + 1));
 }
 
-// 16-byte stores to records of 8-byte alignment: a store of scattered records
-// costs a cycle per record and instruction, whatever its width
-typedef double double2u __attribute__((ext_vector_type(2), aligned(8)));
-typedef int32_t int4u __attribute__((ext_vector_type(4), aligned(8)));
-
 // group g's candidates (the pointers selected in registers)
 __device__ inline const Candidate *group_candidates(const TablesView &T, int g) {
     return g == 0 ? T.cand[0] : (g == 1 ? T.cand[1] : T.cand[2]);
@@ -2494,11 +2492,10 @@ __device__ inline void finish_outputs(int K, const MatchShared &M, const Candida
             }
             ids[m] = id;
         }
-        // 16 bytes a store (the array is 8-byte aligned)
-        int32_t *no = O.neighbours + (int64_t)i * KMAX;
+        // as 8-byte pairs (the array is 8-byte aligned)
+        int2 *no = reinterpret_cast<int2 *>(O.neighbours + (int64_t)i * KMAX);
 #pragma unroll
-        for (int m = 0; m < 12; m += 4) *(int4u *)(no + m) = int4u{ids[m], ids[m + 1], ids[m + 2], ids[m + 3]};
-        *(int2 *)(no + 12) = make_int2(ids[12], ids[13]);
+        for (int m = 0; m < KMAX / 2; m++) no[m] = make_int2(ids[2 * m], ids[2 * m + 1]);
     }
     if (O.strain || O.vm_strain) {
         // Sec. 8: P of A = P U with U right-handed
@@ -2512,11 +2509,8 @@ __device__ inline void finish_outputs(int K, const MatchShared &M, const Candida
                 if (x == y) tr += s;
             }
         if (O.strain) {
-            const RT *e = &P[0][0];
             double *so = O.strain + 9 * (int64_t)i;
-#pragma unroll
-            for (int k = 0; k < 8; k += 2) *(double2u *)(so + k) = double2u{(double)e[k], (double)e[k + 1]};
-            so[8] = (double)e[8];
+            for (int k = 0; k < 9; k++) so[k] = (double)P[k / 3][k % 3];
         }
         // Sec. 8: von Mises shear strain of P
         if (O.vm_strain) O.vm_strain[i] = (double)sqrt(fmax(RT(1.5) * sq - RT(0.5) * tr * tr, RT(0)));
