@@ -34,6 +34,12 @@ int ptm_selftest_det3(const double *p9);
  * triangulation. */
 int ptm_selftest_codes(int k, const int32_t *tris, int ntri, uint64_t *codes, int max_codes, int32_t *n_codes);
 
+/* The cell grid that the library (host and device alike) chooses for n atoms
+ * with bounds mn .. mx in a box, kn = 14 or 18 neighbours: out[0..2] = cells
+ * per axis, out[3] = their number.  Returns 1 if the frame's arrays are laid
+ * out for as many, 0 if not: such a frame is refused. */
+int ptm_selftest_grid(const double *box, const double *mn, const double *mx, int64_t n, int kn, int64_t *out);
+
 /* Eq. (3) superposition for a fixed correspondence with the library's QCP
  * solver: obs and tpl are [N][3] (N <= 15, not centred / not normalised).
  * Writes rmsd, scale and the quaternion (w,x,y,z) rotating the template

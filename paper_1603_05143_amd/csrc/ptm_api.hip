@@ -51,8 +51,8 @@ size_t frame_bytes(int64_t n, int64_t cells, int nbounds, bool topo) {
 
 bool FrameScratch::reserve(int64_t n, int64_t cells, bool topo, std::string &err) {
     int nb = bounds_blocks(n);
-    if (scan_items(cells) > serve_scan_items(n)) {  // make_grid keeps cells <= 4n + 4096
-        err = "cell grid larger than the scratch layout allows";
+    if (scan_items(cells) > serve_scan_items(n)) {  // (the extents leave make_grid no grid that fits)
+        err = GRID_MESSAGE;
         return false;
     }
     size_t need = frame_bytes(n, cells, nb, topo);
@@ -106,76 +106,11 @@ void FrameScratch::release() {
     bytes = 0;
 }
 
-// the most cells make_grid chooses for n atoms
-static int64_t max_cells(int64_t n) { return 4 * n + 4096; }
-
 int bounds_blocks(int64_t n) {
     int64_t b = (n + 255) / 256;
     if (b > 1024) b = 1024;
     if (b < 1) b = 1;
     return (int)b;
-}
-
-// Choose the cell grid: cell edge 0.6 x the expected distance of the kn-th
-// neighbour (kn = 14, or 18 for the topological ordering), so that shells
-// 0..2 of cells around an atom (5x5x5 block) usually certify its kn nearest
-// neighbours; at least 3 cells on periodic axes.  The grid affects only
-// speed: the search is certified exact.
-Grid make_grid(const double box[3], const double mn[3], const double mx[3], int64_t n, int kn) {
-    Grid g;
-    double ext[3], vol = 1.0;
-    int flat = 0;
-    for (int a = 0; a < 3; a++) {
-        g.periodic[a] = box[a] > 0;
-        ext[a] = g.periodic[a] ? box[a] : std::fmax(mx[a] - mn[a], 0.0);
-        if (ext[a] > 0) vol *= ext[a];
-        else flat++;
-    }
-    double h;
-    if (flat == 0 && vol > 0) {
-        double rho = (double)n / vol;
-        h = 0.6 * std::cbrt((double)kn / (4.1887902047863905 * rho));
-    } else {
-        h = 1.0;
-        for (int a = 0; a < 3; a++) h = std::fmax(h, ext[a] / 16.0);
-    }
-    for (int iter = 0; iter < 200; iter++) {
-        double cells = 1;
-        for (int a = 0; a < 3; a++) {
-            int nc;
-            if (g.periodic[a]) nc = (int)std::fmin(std::floor(ext[a] / h), 1 << 20);
-            else nc = ext[a] > 0 ? (int)std::fmin(std::floor(ext[a] / h), 1 << 20) : 1;
-            if (g.periodic[a] && nc < 3) nc = 3;
-            if (nc < 1) nc = 1;
-            g.nc[a] = nc;
-            cells *= nc;
-        }
-        if (cells <= (double)(1 << 30) && cells <= 4.0 * (double)n + 4096.0) break;
-        h *= 1.25;
-    }
-    double hmax = 0;
-    for (int a = 0; a < 3; a++) {
-        if (g.periodic[a]) {
-            g.L[a] = box[a];
-            g.invL[a] = 1.0 / box[a];
-            g.lo[a] = 0.0;
-            g.h[a] = box[a] / g.nc[a];
-            g.inv_h[a] = g.nc[a] / box[a];
-        } else {
-            g.L[a] = 0.0;
-            g.invL[a] = 0.0;
-            g.lo[a] = mn[a];
-            g.h[a] = ext[a] > 0 ? ext[a] / g.nc[a] : 1.0;
-            g.inv_h[a] = ext[a] > 0 ? g.nc[a] / ext[a] : 1.0;
-        }
-        hmax = std::fmax(hmax, g.h[a]);
-    }
-    g.margin = 1e-9 * hmax;
-    set_fixed_scale(g, ext, mn, mx);
-    g.canonical = 1;
-    for (int a = 0; a < 3; a++)
-        if (g.periodic[a] && !(mn[a] >= 0.0 && mx[a] < box[a])) g.canonical = 0;
-    return g;
 }
 
 // Enqueue the whole pipeline for one frame: with its grid known (J.grid), or
@@ -192,7 +127,7 @@ ptm_status enqueue_frame(ptm_ctx *ctx, FrameScratch &S, const FrameJob &J, hipSt
     ptm_status ps;
     const Grid &g = J.grid;
     if ((ps = mark(PTM_STAGE_BIN)) != PTM_OK) return ps;
-    const int64_t cells = J.dgrid ? max_cells(n) : (int64_t)g.nc[0] * g.nc[1] * g.nc[2];
+    const int64_t cells = J.dgrid ? max_cells(n) : grid_cells(g);
     // count[cells + 1] and count[cells + 2] count the atoms the fast k-NN
     // search leaves over and those the full rule decides; count[cells + 3]
     // is the box flag (set by the bounds and k-NN kernels, read by every later
@@ -386,15 +321,18 @@ ptm_status classify_frame(ptm_ctx *ctx, FrameScratch &S, bool noalloc, const dou
             ctx->err = "non-finite coordinate";
             return PTM_E_INVALID;
         }
-        if (*ctx->pinned) {
+        if (*ctx->pinned == FRAME_BOX) {
             ctx->err = box_message(J.topo);
             return PTM_E_BOX;
         }
-        if (H.active) {  // (host outputs are copied only now: nothing is written on an error)
-            if ((st = stage_out(ctx, out, n_atoms, J, H, ctx->stream)) != PTM_OK) return st;
-            PTM_HIP(ctx, hipStreamSynchronize(ctx->stream));
+        if (*ctx->pinned == 0) {
+            if (H.active) {  // (host outputs are copied only now: nothing is written on an error)
+                if ((st = stage_out(ctx, out, n_atoms, J, H, ctx->stream)) != PTM_OK) return st;
+                PTM_HIP(ctx, hipStreamSynchronize(ctx->stream));
+            }
+            return PTM_OK;
         }
-        return PTM_OK;
+        J.dgrid = nullptr;  // FRAME_GRID: the frame was left alone; refused (or laid out) by its own grid below
     }
     // bounds first (needs scratch for the partials): reserve with a tiny grid
     if ((st = reserve(1)) != PTM_OK) return st;
@@ -408,7 +346,7 @@ ptm_status classify_frame(ptm_ctx *ctx, FrameScratch &S, bool noalloc, const dou
         return PTM_E_INVALID;
     }
     J.grid = make_grid(box, mn, mx, n_atoms, J.topo ? VK : KMAX);
-    int64_t cells = (int64_t)J.grid.nc[0] * J.grid.nc[1] * J.grid.nc[2];
+    const int64_t cells = grid_cells(J.grid);
     if (ctx->budget && frame_bytes(n_atoms, cells, bounds_blocks(n_atoms), J.topo) > ctx->budget) {
         ctx->err = "frame scratch exceeds the HBM budget";
         return PTM_E_NOMEM;
@@ -795,6 +733,13 @@ ptm_status ptm_rmsd_histogram(ptm_ctx *ctx, const int8_t *best_type, const doubl
 #include "ptm_device.hpp"
 
 extern "C" {
+
+int ptm_selftest_grid(const double *box, const double *mn, const double *mx, int64_t n, int kn, int64_t *out) {
+    const Grid g = make_grid(box, mn, mx, n, kn);
+    for (int a = 0; a < 3; a++) out[a] = g.nc[a];
+    out[3] = grid_cells(g);
+    return out[3] <= max_cells(n);
+}
 
 int ptm_selftest_orient(const double *p, const int32_t *r) {
     if (r[0] == r[1] || r[0] == r[2] || r[0] == r[3] || r[1] == r[2] || r[1] == r[3] || r[2] == r[3]) return 0;

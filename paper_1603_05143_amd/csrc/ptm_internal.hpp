@@ -89,6 +89,7 @@ struct Ticket {
     bool complete = false;
     bool box_fail = false;  // the frame's periodic box was too short (PTM_E_BOX)
     bool nonfinite = false; // (persistent serving) a coordinate was not finite
+    bool grid_fail = false; // (persistent serving) more cells than the scratch is laid out for
     int slot = -1;          // persistent serving: the frame's slot and generation
     uint64_t gen = 0;
 };
@@ -96,15 +97,15 @@ struct Ticket {
 size_t frame_bytes(int64_t n, int64_t cells, int nbounds, bool topo);
 // the box flag of a frame whose kernels have been enqueued (count[cells + 3])
 inline int32_t *box_flag(const FrameScratch &S, const Grid &g) {
-    return S.count + (int64_t)g.nc[0] * g.nc[1] * g.nc[2] + 3;
+    return S.count + grid_cells(g) + 3;
 }
 int bounds_blocks(int64_t n);
-Grid make_grid(const double box[3], const double mn[3], const double mx[3], int64_t n, int kn);
 ptm_status enqueue_frame(struct ::ptm_ctx *ctx, FrameScratch &S, const FrameJob &J, hipStream_t st,
                          bool prof = false, int32_t *host_flag = nullptr);
 ptm_status frame_bounds(struct ::ptm_ctx *ctx, FrameScratch &S, const double *pos, int64_t n, double mn[3],
                         double mx[3], bool &bad, hipStream_t st);
 const char *box_message(bool topo);
+constexpr const char *GRID_MESSAGE = "cell grid larger than the scratch layout allows";
 hipError_t noalloc_scratch_of(int device, void **ptr);
 ptm_status classify_frame(struct ::ptm_ctx *ctx, FrameScratch &S, bool noalloc, const double *positions,
                           const int8_t *species, const double *box, int64_t n_atoms, uint32_t template_mask,

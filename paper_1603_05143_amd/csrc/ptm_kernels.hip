@@ -67,65 +67,6 @@ __device__ inline double wrapped(double x, const Grid &g, int d) {
     return g.periodic[d] ? x - g.L[d] * floor(x * g.invL[d]) : x - g.lo[d];
 }
 
-__device__ inline Grid make_grid_dev(const double (&box)[3], const double (&mn)[3], const double (&mx)[3], int64_t n,
-                                     int kn) {
-    // the host's make_grid (ptm_api.hip), same arithmetic
-    Grid g;
-    double ext[3], vol = 1.0;
-    int flat = 0;
-    for (int a = 0; a < 3; a++) {
-        g.periodic[a] = box[a] > 0;
-        ext[a] = g.periodic[a] ? box[a] : fmax(mx[a] - mn[a], 0.0);
-        if (ext[a] > 0) vol *= ext[a];
-        else flat++;
-    }
-    double h;
-    if (flat == 0 && vol > 0) {
-        const double rho = (double)n / vol;
-        h = 0.6 * cbrt((double)kn / (4.1887902047863905 * rho));
-    } else {
-        h = 1.0;
-        for (int a = 0; a < 3; a++) h = fmax(h, ext[a] / 16.0);
-    }
-    for (int iter = 0; iter < 200; iter++) {
-        double cells = 1;
-        for (int a = 0; a < 3; a++) {
-            int nc;
-            if (g.periodic[a]) nc = (int)fmin(floor(ext[a] / h), (double)(1 << 20));
-            else nc = ext[a] > 0 ? (int)fmin(floor(ext[a] / h), (double)(1 << 20)) : 1;
-            if (g.periodic[a] && nc < 3) nc = 3;
-            if (nc < 1) nc = 1;
-            g.nc[a] = nc;
-            cells *= nc;
-        }
-        if (cells <= (double)(1 << 30) && cells <= 4.0 * (double)n + 4096.0) break;
-        h *= 1.25;
-    }
-    double hmax = 0;
-    for (int a = 0; a < 3; a++) {
-        if (g.periodic[a]) {
-            g.L[a] = box[a];
-            g.invL[a] = 1.0 / box[a];
-            g.lo[a] = 0.0;
-            g.h[a] = box[a] / g.nc[a];
-            g.inv_h[a] = g.nc[a] / box[a];
-        } else {
-            g.L[a] = 0.0;
-            g.invL[a] = 0.0;
-            g.lo[a] = mn[a];
-            g.h[a] = ext[a] > 0 ? ext[a] / g.nc[a] : 1.0;
-            g.inv_h[a] = ext[a] > 0 ? g.nc[a] / ext[a] : 1.0;
-        }
-        hmax = fmax(hmax, g.h[a]);
-    }
-    g.margin = 1e-9 * hmax;
-    set_fixed_scale(g, ext, mn, mx);
-    g.canonical = 1;
-    for (int a = 0; a < 3; a++)
-        if (g.periodic[a] && !(mn[a] >= 0.0 && mx[a] < box[a])) g.canonical = 0;
-    return g;
-}
-
 // the grid a kernel works on: one the host made, or the one on the device
 // (read through the constant address space: the kernel before has written it,
 // and scalar loads keep it out of the vector registers)
@@ -203,19 +144,21 @@ __global__ void __launch_bounds__(256) k_bounds(const double *__restrict__ pos, 
     }
 }
 
-// the frame's grid from its bounds (one lane); a frame with a coordinate
-// that is not finite gets the flag, and every later kernel leaves it alone
+// the frame's grid from its bounds (one lane); a frame with a coordinate that
+// is not finite, or whose grid has more cells than its arrays are laid out
+// for, gets the flag, and every later kernel leaves it alone
 __device__ inline void grid_finish(GridState *G, const Bounds &b, const double (&box)[3], int64_t n, int kn,
                                    int32_t *box_fail) {
-    Grid g = make_grid_dev(box, b.mn, b.mx, n, kn);
-    if (b.bad) g.nc[0] = g.nc[1] = g.nc[2] = 1;  // (nothing reads it, but the scan's range comes from it)
+    Grid g = make_grid(box, b.mn, b.mx, n, kn);
+    const int flag = b.bad ? FRAME_NONFINITE : (grid_cells(g) > max_cells(n) ? FRAME_GRID : 0);
+    if (flag) g.nc[0] = g.nc[1] = g.nc[2] = 1;  // (nothing reads it, but the scan's range comes from it)
     G->g = g;
-    G->cells = (int64_t)g.nc[0] * g.nc[1] * g.nc[2];
+    G->cells = grid_cells(g);
     int fast = 1;
     for (int a = 0; a < 3; a++)
         if (g.periodic[a] && g.nc[a] < 5) fast = 0;
     G->fast = fast;
-    *box_fail = b.bad ? FRAME_NONFINITE : 0;
+    *box_fail = flag;
 }
 
 // Bounds, cleared cell counters and, by the last block to finish, the frame's
@@ -450,7 +393,7 @@ __global__ void __launch_bounds__(SETUP_THREADS) k_setup_small(const double *__r
     __shared__ Bounds wb[NW];
     __shared__ int32_t ws[NW];
     __shared__ Grid sg;
-    __shared__ int s_bad;
+    __shared__ int s_flag;
     __shared__ int32_t lds_count[SETUP_CELLS];
     const int t = threadIdx.x;
     // the frame's counters (after the cells, where the other path has them)
@@ -463,10 +406,10 @@ __global__ void __launch_bounds__(SETUP_THREADS) k_setup_small(const double *__r
         const double box[3] = {bx, by, bz};
         grid_finish(G, b, box, n, kn, box_fail);
         sg = G->g;
-        s_bad = b.bad;
+        s_flag = *box_fail;
     }
     __syncthreads();
-    if (s_bad) return;
+    if (s_flag) return;
     const Grid g = sg;
     const int cells = g.nc[0] * g.nc[1] * g.nc[2];
     const bool in_lds = cells <= SETUP_CELLS;
@@ -923,7 +866,7 @@ __global__ void __launch_bounds__(256, 4) k_knn_fast(int64_t n, GridArg A, const
                                                   int32_t *__restrict__ box_fail) {
     __shared__ KnnRanges<256> S;
     int64_t p = xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
-    if (p >= n || *box_fail == FRAME_NONFINITE || (A.dev && !A.dev->fast)) return;
+    if (p >= n || *box_fail > FRAME_BOX || (A.dev && !A.dev->fast)) return;
     const Grid g = grid_of(A);
     if (!knn_fast_atom<NK, 256>(S, (int)threadIdx.x, p, n, g, spos, sfix, start, nbr_id, nbr_rel, box_fail))
         todo[atomicAdd(todo_count, 1)] = (int32_t)p;
@@ -1113,7 +1056,7 @@ __global__ void __launch_bounds__(256) k_knn_exact(int64_t n, GridArg A, const d
                                                    const int32_t *__restrict__ todo_count,
                                                    int32_t *__restrict__ box_fail) {
     __shared__ KnnWave S[4];
-    if (*box_fail == FRAME_NONFINITE) return;
+    if (*box_fail > FRAME_BOX) return;
     if (A.dev && !A.dev->fast) todo = nullptr;  // the fast search left every atom
     const Grid g = grid_of(A);
     const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x >> 6);
@@ -3547,7 +3490,7 @@ void launch_topo(int64_t n, const double *nbr_rel, const int32_t *nbr_id, const 
 // stop: no wave waits on another, so every wave reaches an exit.
 enum {
     PH_BOUNDS = 0,   // per-item bounds and non-finite flag
-    PH_GRID = 1,     // one item: the grid from the bounds (make_grid on the device)
+    PH_GRID = 1,     // one item: the grid from the bounds
     PH_ZERO = 2,     // cell counters and frame counters to zero
     PH_COUNT = 3,    // cell of every atom, slot in its cell (atomic counts)
     PH_SCAN = 4,     // exclusive scan of the counts within each item, item totals
@@ -3747,13 +3690,14 @@ __device__ void serve_item(const MatchShared &M, const TablesView &Tl, MatchOut 
         }
         if (lane == 0) {
             const double box[3] = {R.box[0], R.box[1], R.box[2]};
-            S.g = make_grid_dev(box, mn, mx, n, KMAX);
-            S.cells = (int64_t)S.g.nc[0] * S.g.nc[1] * S.g.nc[2];
+            S.g = make_grid(box, mn, mx, n, KMAX);
+            S.cells = grid_cells(S.g);
             bool fast = true;
             for (int a = 0; a < 3; a++)
                 if (S.g.periodic[a] && S.g.nc[a] < 5) fast = false;
             S.fast = fast;
-            S.bad = bad;  // non-finite coordinate: the frame stops here
+            // a non-finite coordinate, or more cells than the scratch has: the frame stops here
+            S.bad = bad ? SERVE_NONFINITE : (S.cells > max_cells(n) ? SERVE_GRID : SERVE_OK);
         }
     } else if (ph == PH_ZERO) {
         const int64_t m = S.cells + FRAME_COUNTERS;
@@ -3844,7 +3788,7 @@ __device__ inline void serve_advance(ServeDev *dev, ServeHost *host, int slot, i
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // every item's writes of the stage
     int next = ph + 1;
     if (ph == PH_GRID && S.bad) {
-        serve_complete(host, slot, gen, SERVE_NONFINITE);
+        serve_complete(host, slot, gen, S.bad);
         return;
     }
     if (ph == PH_KNN && __hip_atomic_load(S.r.count + S.cells + 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {

@@ -39,6 +39,78 @@ __host__ __device__ inline void set_fixed_scale(Grid &g, const double (&ext)[3],
     g.fix_err = sqrt(e2);
 }
 
+// the most cells a frame of n atoms may have: its cell arrays are laid out for
+// no more
+__host__ __device__ constexpr int64_t max_cells(int64_t n) { return 4 * n + 4096; }
+__host__ __device__ inline int64_t grid_cells(const Grid &g) { return (int64_t)g.nc[0] * g.nc[1] * g.nc[2]; }
+
+// Choose the cell grid: cell edge 0.6 x the expected distance of the kn-th
+// neighbour (kn = 14, or 18 for the topological ordering), so that shells
+// 0..2 of cells around an atom (5x5x5 block) usually certify its kn nearest
+// neighbours; at least 3 cells on periodic axes.  The grid affects only
+// speed: the search is certified exact.  Coarser until it has at most
+// max_cells(n); extents that no edge brings there (ratios beyond 10^19, a
+// difference that overflows) leave a grid with more, which the caller has to
+// refuse before anything is indexed with it.
+__host__ __device__ inline Grid make_grid(const double *box, const double *mn, const double *mx, int64_t n, int kn) {
+    Grid g;
+    double ext[3], vol = 1.0;
+    int flat = 0;
+    for (int a = 0; a < 3; a++) {
+        g.periodic[a] = box[a] > 0;
+        ext[a] = g.periodic[a] ? box[a] : fmax(mx[a] - mn[a], 0.0);
+        if (ext[a] > 0) vol *= ext[a];
+        else flat++;
+    }
+    double h;
+    if (flat == 0 && vol > 0) {
+        const double rho = (double)n / vol;
+        h = 0.6 * cbrt((double)kn / (4.1887902047863905 * rho));
+    } else {
+        h = 1.0;
+        for (int a = 0; a < 3; a++) h = fmax(h, ext[a] / 16.0);
+    }
+    for (int iter = 0; iter < 200; iter++) {
+        double cells = 1;
+        for (int a = 0; a < 3; a++) {
+            int nc;
+            if (g.periodic[a]) nc = (int)fmin(floor(ext[a] / h), (double)(1 << 20));
+            else nc = ext[a] > 0 ? (int)fmin(floor(ext[a] / h), (double)(1 << 20)) : 1;
+            if (g.periodic[a] && nc < 3) nc = 3;
+            if (nc < 1) nc = 1;
+            g.nc[a] = nc;
+            cells *= nc;
+        }
+        if (cells <= (double)(1 << 30) && cells <= (double)max_cells(n)) break;
+        h *= 1.25;
+    }
+    double hmax = 0;
+    for (int a = 0; a < 3; a++) {
+        if (g.periodic[a]) {
+            g.L[a] = box[a];
+            g.invL[a] = 1.0 / box[a];
+            g.lo[a] = 0.0;
+            g.h[a] = box[a] / g.nc[a];
+            g.inv_h[a] = g.nc[a] / box[a];
+        } else {
+            g.L[a] = 0.0;
+            g.invL[a] = 0.0;
+            g.lo[a] = mn[a];
+            g.h[a] = ext[a] > 0 ? ext[a] / g.nc[a] : 1.0;
+            g.inv_h[a] = ext[a] > 0 ? g.nc[a] / ext[a] : 1.0;
+        }
+        hmax = fmax(hmax, g.h[a]);
+    }
+    // an extent that is not finite: no cell has an edge, whatever their number
+    if (!(hmax < INFINITY)) g.nc[0] = g.nc[1] = g.nc[2] = 1 << 20;
+    g.margin = 1e-9 * hmax;
+    set_fixed_scale(g, ext, mn, mx);
+    g.canonical = 1;
+    for (int a = 0; a < 3; a++)
+        if (g.periodic[a] && !(mn[a] >= 0.0 && mx[a] < box[a])) g.canonical = 0;
+    return g;
+}
+
 // The grid of a frame whose bounds stay on the device.
 struct GridState {
     Grid g;
@@ -52,7 +124,9 @@ struct GridArg {
     Grid val;
 };
 // values of a frame's box flag: every stage after the one that sets it does nothing
-enum { FRAME_BOX = 1, FRAME_NONFINITE = 2 };
+// (FRAME_GRID: more cells than max_cells; the k-NN kernels run on with FRAME_BOX,
+// which they set themselves, and not with the others)
+enum { FRAME_BOX = 1, FRAME_NONFINITE = 2, FRAME_GRID = 3 };
 
 struct MatchOut {
     int8_t *type;
@@ -149,7 +223,7 @@ constexpr int64_t SERVE_ATOMS_LIGHT = 512;    // atoms per item: bounds, counts,
 constexpr int64_t SERVE_ATOMS = 64;           // atoms per item: k-NN, hulls + match
 constexpr int64_t SERVE_ZERO_CELLS = 16384;   // cells per item: zeroing
 constexpr int64_t SERVE_SCAN_CELLS = 2048;    // cells per item: scan
-enum { SERVE_OK = 0, SERVE_BOX = 1, SERVE_NONFINITE = 2 };
+enum { SERVE_OK = 0, SERVE_BOX = 1, SERVE_NONFINITE = 2, SERVE_GRID = 3 };
 
 // One frame as the host hands it over: inputs, outputs and the frame's
 // device scratch, carved for the largest grid (4n + 4096 cells).
@@ -190,7 +264,7 @@ struct ServeSlot {
     ServeRequest r;
     Grid g;
     int64_t cells;
-    int32_t fast, bad;
+    int32_t fast, bad;  // bad: SERVE_* of a frame that stops at its grid
     unsigned long long next[SERVE_NPH];  // claim counters: generation << 28 | next item
     long long done[SERVE_NPH], nr[SERVE_NPH];
 };
@@ -206,7 +280,7 @@ struct ServeDev {
 inline int64_t serve_bounds_items(int64_t n) { return (n + SERVE_ATOMS_LIGHT - 1) / SERVE_ATOMS_LIGHT; }
 // items of the cell-start scan over cells + 1 entries
 inline int64_t scan_items(int64_t cells) { return (cells + 1 + SERVE_SCAN_CELLS - 1) / SERVE_SCAN_CELLS; }
-inline int64_t serve_scan_items(int64_t n) { return scan_items(4 * n + 4096); }
+inline int64_t serve_scan_items(int64_t n) { return scan_items(max_cells(n)); }
 
 // Launch the persistent kernel (grid: what fits on the device at once);
 // its waves exit after idle_ticks of the device wall clock without work,

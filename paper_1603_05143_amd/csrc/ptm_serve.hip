@@ -195,11 +195,10 @@ static ptm_status serve_init(ptm_ctx *ctx) {
 }
 
 // Size class of a frame's scratch: the next power of two (at least 1 MiB)
-// of an upper bound of its bytes that holds for any cell grid make_grid
-// may choose (at most 4n + 4096 cells).
+// of an upper bound of its bytes that holds for any cell grid the frame may
+// have (max_cells).
 static size_t scratch_class(int64_t n, bool topo) {
-    int64_t cells = 4 * n + 4096;
-    size_t need = frame_bytes(n, cells, bounds_blocks(n), topo);
+    size_t need = frame_bytes(n, max_cells(n), bounds_blocks(n), topo);
     size_t c = (size_t)1 << 20;
     while (c < need) c <<= 1;
     return c;
@@ -346,7 +345,7 @@ static ptm_status persistent_submit(ptm_ctx *ctx, const double *positions, const
     // scratch for the largest grid the kernel can choose
     T->footprint = scratch_class(n, false);
     st = take_scratch(ctx, T->footprint, T->scratch);
-    if (st == PTM_OK && !T->scratch.reserve(n, 4 * n + 4096, false, ctx->err)) st = PTM_E_DEVICE;
+    if (st == PTM_OK && !T->scratch.reserve(n, max_cells(n), false, ctx->err)) st = PTM_E_DEVICE;
     if (st != PTM_OK) {
         if (T->scratch.base) ctx->free_scratch.push_back(T->scratch);
         T->scratch = FrameScratch();
@@ -415,6 +414,7 @@ static ptm_status persistent_wait(ptm_ctx *ctx, Ticket *T, int64_t timeout_us) {
     T->complete = true;
     T->box_fail = status == SERVE_BOX;
     T->nonfinite = status == SERVE_NONFINITE;
+    T->grid_fail = status == SERVE_GRID;
     if (status == SERVE_OK && T->stage.active) {
         ptm_status so = stage_out(ctx, &T->stage.host_out, T->job.n, T->job, T->stage, ctx->bounds_stream);
         if (so != PTM_OK) return so;
@@ -527,7 +527,7 @@ ptm_status ptm_submit(ptm_ctx *ctx, const double *positions, const int8_t *speci
         int64_t cells = 1;
         if (st == PTM_OK) {
             T->job.grid = make_grid(box, mn, mx, n_atoms, T->job.topo ? VK : KMAX);
-            cells = (int64_t)T->job.grid.nc[0] * T->job.grid.nc[1] * T->job.grid.nc[2];
+            cells = grid_cells(T->job.grid);
             T->footprint = scratch_class(n_atoms, T->job.topo);
             st = take_scratch(ctx, T->footprint, T->scratch);
             if (st == PTM_OK && !T->scratch.reserve(n_atoms, cells, T->job.topo, ctx->err)) st = PTM_E_DEVICE;
@@ -609,7 +609,7 @@ ptm_status ptm_wait(ptm_ctx *ctx, uint64_t ticket, int64_t timeout_us, ptm_frame
             T->t_complete = now_us();  // the outputs are in host memory only now
         }
     }
-    const bool box_fail = T->box_fail, nonfinite = T->nonfinite;
+    const bool box_fail = T->box_fail, nonfinite = T->nonfinite, grid_fail = T->grid_fail;
     const bool topo = T->job.topo;
     if (stats) {
         stats->submit_time_us = T->t_submit;
@@ -628,6 +628,10 @@ ptm_status ptm_wait(ptm_ctx *ctx, uint64_t ticket, int64_t timeout_us, ptm_frame
     if (nonfinite) {
         ctx->err = "non-finite coordinate";
         return PTM_E_INVALID;
+    }
+    if (grid_fail) {
+        ctx->err = GRID_MESSAGE;
+        return PTM_E_NOMEM;
     }
     return PTM_OK;
 }
