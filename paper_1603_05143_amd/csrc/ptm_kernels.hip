@@ -464,15 +464,12 @@ __device__ inline double min_image(double d, const Grid &g, int a) {
     return d;
 }
 
-__device__ inline void shell_range(const Grid &g, int a, int s, int &lo, int &hi) {
-    if (g.periodic[a]) {
-        int half = (g.nc[a] - 1) / 2;
-        lo = -min(s, half);
-        hi = min(s, g.nc[a] - 1 - half);
-    } else {
-        lo = -s;
-        hi = s;
-    }
+// offsets of the cells up to s away from cell c on axis a (none twice, none
+// outside an open axis, so a block never has more rows than the grid)
+__device__ inline void shell_range(const Grid &g, int a, int c, int s, int &lo, int &hi) {
+    const int half = g.periodic[a] ? (g.nc[a] - 1) / 2 : c;
+    lo = -min(s, half);
+    hi = min(s, g.nc[a] - 1 - half);
 }
 
 // Radius around the atom that the block of cells with offsets [lo, hi] per
@@ -944,9 +941,11 @@ __device__ void knn_exact_atom(KnnWave &S, int64_t p, int64_t n, const Grid &g, 
         u[a] = wrapped(xs[a], g, a);
     }
     int count = 0;
-    for (int s = 2;; s++) {
+    // (blocks grow by a quarter at least: an atom a hundred thousand empty
+    // cells from the others takes some fifty of them)
+    for (int s = 2;; s += 1 + s / 4) {
         int lo[3], hi[3];
-        for (int a = 0; a < 3; a++) shell_range(g, a, s, lo[a], hi[a]);
+        for (int a = 0; a < 3; a++) shell_range(g, a, cc[a], s, lo[a], hi[a]);
         bool all;
         const double reach = block_reach(g, cc, u, lo, hi, all);
         // kept: d^2 < thr, or d^2 <= thr once the list was cut
@@ -959,22 +958,17 @@ __device__ void knn_exact_atom(KnnWave &S, int64_t p, int64_t n, const Grid &g, 
             const int r = r0 + lane;
             if (r < rows) {
                 int cy = cc[1] + lo[1] + r % ey, cz = cc[2] + lo[2] + r / ey;
-                bool in = true;
-                if (g.periodic[1]) cy = (cy % g.nc[1] + g.nc[1]) % g.nc[1];
-                else in = cy >= 0 && cy < g.nc[1];
-                if (g.periodic[2]) cz = (cz % g.nc[2] + g.nc[2]) % g.nc[2];
-                else in = in && cz >= 0 && cz < g.nc[2];
-                if (in) {
-                    const int cyz = cell_row(g, cy, cz) * nx;
-                    const int a0 = cc[0] + lo[0], a1 = cc[0] + hi[0];
-                    const int i0 = max(a0, 0), i1 = min(a1, nx - 1);
-                    qa = start[cyz + i0];
-                    la = start[cyz + i1 + 1] - qa;
-                    if (g.periodic[0] && (a0 < 0 || a1 >= nx)) {
-                        const int w0 = a0 < 0 ? a0 + nx : 0, w1 = a0 < 0 ? nx - 1 : a1 - nx;
-                        qb = start[cyz + w0];
-                        lb = start[cyz + w1 + 1] - qb;
-                    }
+                cy = cy < 0 ? cy + g.nc[1] : (cy >= g.nc[1] ? cy - g.nc[1] : cy);
+                cz = cz < 0 ? cz + g.nc[2] : (cz >= g.nc[2] ? cz - g.nc[2] : cz);
+                const int cyz = cell_row(g, cy, cz) * nx;
+                const int a0 = cc[0] + lo[0], a1 = cc[0] + hi[0];
+                const int i0 = max(a0, 0), i1 = min(a1, nx - 1);
+                qa = start[cyz + i0];
+                la = start[cyz + i1 + 1] - qa;
+                if (a0 < 0 || a1 >= nx) {  // (a periodic axis)
+                    const int w0 = a0 < 0 ? a0 + nx : 0, w1 = a0 < 0 ? nx - 1 : a1 - nx;
+                    qb = start[cyz + w0];
+                    lb = start[cyz + w1 + 1] - qb;
                 }
             }
             int incl = la + lb;
@@ -1049,7 +1043,7 @@ __device__ void knn_exact_atom(KnnWave &S, int64_t p, int64_t n, const Grid &g, 
 }
 
 template <int NK>
-__global__ void __launch_bounds__(256) k_knn_exact(int64_t n, GridArg A, const double *__restrict__ spos,
+__global__ void __launch_bounds__(256, 4) k_knn_exact(int64_t n, GridArg A, const double *__restrict__ spos,
                                                    const int32_t *__restrict__ sid, const int32_t *__restrict__ start,
                                                    int32_t *__restrict__ nbr_id, double *__restrict__ nbr_rel,
                                                    const int32_t *__restrict__ todo,
