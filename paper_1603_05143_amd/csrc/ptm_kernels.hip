@@ -545,7 +545,7 @@ inline int64_t xcd_pad(int64_t nblocks) { return (nblocks + NXCD - 1) / NXCD * N
 // records of every candidate had to come before.  31.7 M atoms: 13.4 ms with
 // FP64 records, 64-bit keys and rows plane after plane; 12.2 with this search;
 // 10.3 with it and the tiled order of rows (cell_row).  0.92 M atoms: 345 ->
-// 285 us.
+// 285 us.  (Both less by 2 to 4 % with the tables below.)
 //
 // A candidate is ranked by one 32-bit key: the upper 21 bits are d^2 on a
 // linear grid (buckets of 1 / (2^21 - 16) of the squared radius the block
@@ -556,34 +556,50 @@ inline int64_t xcd_pad(int64_t nblocks) { return (nblocks + NXCD - 1) / NXCD * N
 // keys that it replaces took two dependent ones per entry, on two registers
 // each.
 //
-// The ranges come first, in loops over rows that are uniform over the wave
+// The ranges come first, in a loop over rows that is uniform over the wave
 // (their offsets are scalars): nine inner rows, their atoms, then the sixteen
 // outer rows and the cells that the Kth distance found so far leaves, and
-// their atoms.  Each lane then walks its own list of ranges, kept in LDS, two
-// atoms per step, so that a wave pays about the per-lane atom count.
+// their atoms.  Each lane then walks its own table of ranges, kept in LDS, two
+// atoms per step, so that a wave pays about the per-lane atom count.  A range
+// of more than 64 atoms takes several entries, and where a lane's table is
+// full the wave searches what it holds, the lane keeps the listed atoms alone
+// (an entry each), and the rows go on: any number of atoms fits.  Where the
+// own row is dense (KNN_DENSE_ROW) the Kth distance is taken after one, five
+// and nine rows, which spares most of the block.
+//
+// The cells follow the mean density, so a particle in a box of 2.5 diameters
+// has 400 atoms in a 5 x 5 x 1 slice of its block.  With one table for the
+// whole search such atoms were left to the exact search, a wave each: 100,000
+// atoms in such a box 4.14 ms, 0.35 with this loop (0.60 with the search on
+// FP64 records); 1,000,000 atoms 39.2 ms, 1.61 (2.43).  At the mean density
+// the atoms at the x edges of the box, whose rows are two ranges, fit as well:
+// k-NN at 0.92 M atoms 372 -> 327 us, at 31.7 M 10.54 -> 10.19 ms.
 //
 // Two atoms whose buckets differ by `apart` or more are in the exact order
 // (the rounding of the coordinates, of d^2 and of the buckets is covered).
 // Where neighbouring entries are closer, the exact (d^2, id) of the entries
 // decides; that covers exact ties inside the list too (the 12 + 6 neighbours
 // of a perfect FCC or HCP crystal end at entry 18).  The atoms left to
-// k_knn_exact are those whose Kth neighbour the block does not certify, whose
-// ties run past the list, or whose ranges do not fit the codes.  Requires
+// k_knn_exact are those whose Kth neighbour the block does not certify or
+// whose ties run past the list.  Requires
 // every periodic axis to have at least 5 cells (no axis wraps onto itself
 // within the block).
 constexpr int KNN_LIST = 19;    // list entries (both neighbour counts)
-constexpr int KNN_RANGES = 30;  // ranges of one atom (a 5-bit code), kept for the decoding
-constexpr int KNN_PENDING = 18; // ranges of one pass: nine rows that may wrap
+constexpr int KNN_RANGES = 31;  // ranges held at a time, for the decoding (a 5-bit code)
 constexpr int KNN_OFF_BITS = 6; // offset within a range
 constexpr int KNN_CODE_BITS = 11;
 constexpr uint32_t KNN_BUCKETS = (1u << (32 - KNN_CODE_BITS)) - 16;
-static_assert(KNN_RANGES << KNN_OFF_BITS <= 1 << KNN_CODE_BITS, "range and offset fit the code");
+static_assert(KNN_RANGES << KNN_OFF_BITS < 1 << KNN_CODE_BITS, "range and offset fit the code; the last means none");
+static_assert(KNN_LIST < KNN_RANGES, "the atoms of the list, a range each, leave room for more");
+// atoms in the five cells of the own row from which the rows are taken in
+// smaller steps (3.6 at the mean density)
+constexpr int KNN_DENSE_ROW = 24;
 
-// W lanes: 138 bytes each (35,328 per block of 256: four blocks per CU)
+// W lanes: 155 bytes each (39,680 per block of 256: four blocks per CU)
 template <int W>
 struct KnnRanges {
-    uint32_t q0[KNN_RANGES][W];   // first atom
-    uint8_t cnt[KNN_PENDING][W];  // atoms
+    uint32_t q0[KNN_RANGES][W];  // first atom
+    uint8_t cnt[KNN_RANGES][W];  // atoms
 };
 
 // the coordinates of sorted atom q's record (12 bytes: the id, unused, would
@@ -659,31 +675,38 @@ __device__ inline bool knn_fast_atom(KnnRanges<W> &S, int t, int64_t p, int64_t 
     uint32_t key[KNN_LIST];
 #pragma unroll
     for (int m = 0; m < KNN_LIST; m++) key[m] = ~0u;
-    int nrange = 0;         // ranges kept so far
-    bool overflow = false;  // a range or offset that does not fit the codes
+    int nrange = 0, taken = 0;  // ranges held, those whose atoms are in the list
     float cap = (float)rcap2 * 1.000001f;  // squared radius still to search
+    uint32_t r0 = 0, r1 = 0, w0 = 0, w1 = 0;  // what is left of the row: its part here, its part across the box edge
     // (dy + 2) + 5 (dz + 2) of the 25 rows by increasing dy^2 + dz^2, 5 bits each
     const uint64_t rows_lo = 0x013952440D13B56Cull;  // rows 0..11
     const uint64_t rows_hi = 0x0250171D4334BCB6ull;  // rows 12..23
-#pragma unroll 1
-    for (int pass = 0; pass < 2; pass++) {
-        const int r0 = pass ? 9 : 0, r1 = pass ? 25 : 9;
-        const int base = nrange;
-        int npend = 0;
-        auto add = [&](int c0, int c1) {
-            const int32_t q0 = start[c0], cnt = start[c1 + 1] - q0;
-            if (cnt <= 0) return;
-            if (cnt >= (1 << KNN_OFF_BITS) || nrange == KNN_RANGES || npend == KNN_PENDING) {
-                overflow = true;
-                return;
+    int row = 0, stage = 9;  // the same in every lane: the next row, the row at which this stage ends
+    bool more_rows = true;
+    do {
+        for (;;) {
+            // one range of the row per turn
+            if (r0 < r1 && nrange < KNN_RANGES) {
+                const uint32_t cnt = min(r1 - r0, 1u << KNN_OFF_BITS);
+                S.q0[nrange][t] = r0;
+                S.cnt[nrange][t] = (uint8_t)cnt;
+                nrange++;
+                r0 += cnt;
+                if (r0 == r1) {
+                    r0 = w0;
+                    r1 = w1;
+                    w0 = w1;
+                }
             }
-            S.q0[nrange++][t] = (uint32_t)q0;
-            S.cnt[npend++][t] = (uint8_t)cnt;
-        };
-        for (int r = r0; r < r1; r++) {
-            const int code = r < 12 ? (int)((rows_lo >> (5 * r)) & 31)
-                                    : (r < 24 ? (int)((rows_hi >> (5 * (r - 12))) & 31) : 24);
+            if (__ballot(r0 < r1)) {
+                if (__ballot(r0 < r1 && nrange == KNN_RANGES)) break;
+                continue;
+            }
+            if (row == stage) break;
+            const int code = row < 12 ? (int)((rows_lo >> (5 * row)) & 31)
+                                      : (row < 24 ? (int)((rows_hi >> (5 * (row - 12))) & 31) : 24);
             const int dz = code / 5 - 2, dy = code - 5 * (code / 5) - 2;
+            row++;
             int cy = cc[1] + dy, cz = cc[2] + dz;
             const bool out = (!g.periodic[1] && (cy < 0 || cy >= g.nc[1])) ||
                              (!g.periodic[2] && (cz < 0 || cz >= g.nc[2]));
@@ -692,27 +715,35 @@ __device__ inline bool knn_fast_atom(KnnRanges<W> &S, int t, int64_t p, int64_t 
             const float gy2 = dy == 0 ? 0.0f : sqgap(1, dy > 0 ? (float)dy * h[1] - f[1] : f[1] - (float)(dy + 1) * h[1]);
             const float gz2 = dz == 0 ? 0.0f : sqgap(2, dz > 0 ? (float)dz * h[2] - f[2] : f[2] - (float)(dz + 1) * h[2]);
             const float rem = cap - (gy2 + gz2);
-            if (out || rem < 0) continue;
-            // cells whose x-gap exceeds what is left cannot hold a better neighbour
-            const int a0 = cc[0] - (gx_m1 <= rem) - (gx_m2 <= rem), a1 = cc[0] + (gx_p1 <= rem) + (gx_p2 <= rem);
-            const int cyz = cell_row(g, cy, cz) * nx;
-            add(cyz + max(a0, 0), cyz + min(a1, nx - 1));
-            if (g.periodic[0]) {  // the part across the box edge
-                if (a0 < 0) add(cyz + a0 + nx, cyz + nx - 1);
-                else if (a1 >= nx) add(cyz, cyz + a1 - nx);
+            if (!out && rem >= 0) {
+                // cells whose x-gap exceeds what is left cannot hold a better neighbour
+                const int a0 = cc[0] - (gx_m1 <= rem) - (gx_m2 <= rem), a1 = cc[0] + (gx_p1 <= rem) + (gx_p2 <= rem);
+                const int cyz = cell_row(g, cy, cz) * nx;
+                r0 = (uint32_t)start[cyz + max(a0, 0)];
+                r1 = (uint32_t)start[cyz + min(a1, nx - 1) + 1];
+                if (g.periodic[0] && (a0 < 0 || a1 >= nx)) {  // the part across the box edge
+                    w0 = (uint32_t)start[cyz + (a0 < 0 ? a0 + nx : 0)];
+                    w1 = (uint32_t)start[cyz + (a0 < 0 ? nx : a1 - nx + 1)];
+                    if (r0 == r1) {
+                        r0 = w0;
+                        r1 = w1;
+                        w0 = w1;
+                    }
+                }
             }
+            if (row == 1 && __ballot((int)(r1 - r0) + (int)(w1 - w0) >= KNN_DENSE_ROW)) stage = 1;
         }
         // the atoms of the ranges, two per step; the next step's are loaded
         // before this one's are used
-        int k = 0, q = 0, qend = 0;
+        int q = 0, qend = 0;
         uint32_t code = 0;  // code of atom q less q
         auto fetch = [&](int3v &A, int3v &B, uint32_t &ca, uint32_t &cb) {
-            const bool any = q < qend || k < npend;
-            if (q >= qend && k < npend) {
-                q = (int)S.q0[base + k][t];
-                qend = q + (int)S.cnt[k][t];
-                code = ((uint32_t)(base + k) << KNN_OFF_BITS) - (uint32_t)q;
-                k++;
+            const bool any = q < qend || taken < nrange;
+            if (q >= qend && taken < nrange) {
+                q = (int)S.q0[taken][t];
+                qend = q + (int)S.cnt[taken][t];
+                code = ((uint32_t)taken << KNN_OFF_BITS) - (uint32_t)q;
+                taken++;
             }
             // loads without a branch (the atom itself where there is none),
             // so that they can stay in flight
@@ -761,8 +792,30 @@ __device__ inline bool knn_fast_atom(KnnRanges<W> &S, int t, int64_t p, int64_t 
         }
         // an upper bound of the Kth distance found so far
         cap = fminf(cap, (float)((key[NK - 1] >> KNN_CODE_BITS) + (uint32_t)apart) * ((float)bucket * 1.000001f));
-    }
-    if (overflow) return false;
+        if (r0 < r1) {
+            // the table is full: only the atoms of the list stay in it, a range each
+            uint32_t listed[KNN_LIST];
+#pragma unroll
+            for (int m = 0; m < KNN_LIST; m++) {
+                const uint32_t code = key[m] & ((1u << KNN_CODE_BITS) - 1);
+                listed[m] = key[m] == ~0u ? 0u : S.q0[code >> KNN_OFF_BITS][t] + (code & ((1u << KNN_OFF_BITS) - 1));
+            }
+            nrange = 0;
+#pragma unroll
+            for (int m = 0; m < KNN_LIST; m++)
+                if (key[m] != ~0u) {
+                    S.q0[m][t] = listed[m];
+                    key[m] = (key[m] >> KNN_CODE_BITS << KNN_CODE_BITS) | (uint32_t)m << KNN_OFF_BITS;
+                    nrange = m + 1;
+                }
+            taken = nrange;
+        }
+        more_rows = __ballot(r0 < r1) != 0;
+        if (!more_rows && row == stage) {
+            more_rows = stage < 25;
+            stage = stage == 1 ? 5 : (stage == 5 ? 9 : 25);
+        }
+    } while (more_rows);
 
     auto bk = [&](int m) { return (int)(key[m] >> KNN_CODE_BITS); };
     // entries to put in order: past NK as long as the next one could come before the last

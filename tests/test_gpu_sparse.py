@@ -45,3 +45,48 @@ def test_stray_atoms(oracle_lib, n, kind, topological):
         c.close()
     bad = np.flatnonzero((got != ids[:, :14]).any(1))
     assert bad.size == 0, (len(bad), bad[:5], got[bad[:1]], ids[bad[:1]])
+
+
+def _particle(n, ratio, kind):
+    """A BCC particle of n atoms in a periodic cubic box of ratio diameters."""
+    rng = np.random.default_rng(n)
+    m = int((n / 2) ** (1 / 3)) + 2
+    g = np.stack(np.meshgrid(*[np.arange(-m, m + 1)] * 3, indexing="ij"), -1).reshape(-1, 3).astype(float)
+    p = np.concatenate([g, g + 0.5]) * 2.87
+    p = p[np.argsort((p**2).sum(1), kind="stable")[:n]]
+    d = 2 * np.sqrt((p**2).sum(1).max())
+    p = p + rng.normal(scale=0.06, size=p.shape) + ratio * d / 2
+    box = np.array([ratio * d] * 3)
+    if kind == "edge":  # across the x and y edges of the box
+        p -= [ratio * d / 2, 0.45 * ratio * d, 0]
+    if kind == "gas":  # a tenth of the atoms anywhere in the box
+        p[: n // 10] = rng.random((n // 10, 3)) * box
+    return np.ascontiguousarray(p[rng.permutation(n)]), box
+
+
+@pytest.mark.parametrize("topological", [False, True], ids=["euclidean14", "topological18"])
+@pytest.mark.parametrize("n,ratio,kind", [(18000, 1.7, "plain"), (18000, 2.5, "plain"), (18000, 2.5, "edge"),
+                                          (18000, 2.5, "gas"), (18000, 6.0, "edge"), (17000, 11.0, "plain"),
+                                          (3000, 2.5, "edge"), (3000, 6.0, "plain")])
+def test_particle_in_vacuum(oracle_lib, n, ratio, kind, topological):
+    """Rows of cells that hold many times the mean: ranges of 64 atoms and
+    more, tables of ranges that fill up, rows taken one by one.  In frames
+    that the lane-per-atom search takes it must not leave the dense atoms over
+    (a wave each is tens of times the work)."""
+    import torch
+    pos, box = _particle(n, ratio, kind)
+    print(f"[particle] n={n} ratio={ratio} {kind} topological={topological}", flush=True)
+    ids, _, _, _, box_ok = oracle_lib.neighbours(pos, box, K=18 if topological else 14)
+    assert box_ok
+    c = ptm.Classifier(device=0, topological=topological, flags=ptm.PTM_F_PROFILE)
+    try:
+        dpos = torch.from_numpy(pos).to("cuda:0")
+        got = c.classify(dpos, box, knn=True)["knn"].cpu().numpy()
+        info = ptm.ptm_frame_info(c.ctx)
+    finally:
+        c.close()
+    bad = np.flatnonzero((got != ids[:, :14]).any(1))
+    assert bad.size == 0, (len(bad), bad[:5], got[bad[:1]], ids[bad[:1]])
+    print(info, flush=True)
+    if n > 16384 and kind != "gas" and ratio < 11:
+        assert info["knn_exact"] < 0.05 * n, info
