@@ -934,7 +934,17 @@ __global__ void __launch_bounds__(256, 4) k_knn_fast(int64_t n, GridArg A, const
 // by (d^2, id).  (Private sorted lists per lane merged by K rounds of
 // wave-wide minima took 207 us where this takes 86 on the 0.92 M-atom
 // polycrystal.)
+//
+// A first block that holds far more atoms than at the mean density (90, or 116
+// for 18 neighbours) fills the list many times over, so the radius is first the
+// one that holds three times the neighbours at the block's density (K atoms
+// within it are the same certificate), and where the 3x3x3 block should reach
+// that far it is enough.  The smallest frames take this search alone, and a
+// particle in a vacuum fills its cells: whole frames of 16,000 atoms in a
+// periodic box of 1.5, 2.5 and 6 diameters 483, 800 and 1919 -> 260, 263 and
+// 476 us.
 constexpr int KNN_CAND = 256;  // list entries
+constexpr int KNN_FULL_BLOCK = 256;  // atoms
 constexpr int64_t KNN_WAVE_ATOMS = 16384;  // frames up to this take the wave-per-atom search alone
 struct KnnWave {
     double d2[KNN_CAND];
@@ -996,8 +1006,9 @@ __device__ void knn_exact_atom(KnnWave &S, int64_t p, int64_t n, const Grid &g, 
     int count = 0;
     // (blocks grow by a quarter at least: an atom a hundred thousand empty
     // cells from the others takes some fifty of them)
-    for (int s = 2;; s += 1 + s / 4) {
-        int lo[3], hi[3];
+    bool guess = false, guessed = false;  // (of the wave)
+    for (int s = 2;;) {
+        int lo[3], hi[3], next = s + 1 + s / 4;
         for (int a = 0; a < 3; a++) shell_range(g, a, cc[a], s, lo[a], hi[a]);
         bool all;
         const double reach = block_reach(g, cc, u, lo, hi, all);
@@ -1030,6 +1041,19 @@ __device__ void knn_exact_atom(KnnWave &S, int64_t p, int64_t n, const Grid &g, 
                 if (lane >= d) incl += y;
             }
             const int total = __shfl(incl, 63);
+            if (s == 2 && !guessed && total > KNN_FULL_BLOCK) {
+                guess = guessed = true;
+                if (total > 2 * KNN_FULL_BLOCK) {
+                    next = 1;
+                    break;
+                }
+            }
+            if (guess) {
+                double vol = 1;
+                for (int a = 0; a < 3; a++) vol *= (hi[a] - lo[a] + 1) * g.h[a];
+                const double r = cbrt(vol * (3 * NK) / (4.1887902047863905 * max(total, 1)));
+                thr = fmin(thr, r * r);
+            }
             S.pre[lane] = incl - (la + lb);
             S.qa[lane] = qa;
             S.la[lane] = la;
@@ -1073,7 +1097,12 @@ __device__ void knn_exact_atom(KnnWave &S, int64_t p, int64_t n, const Grid &g, 
             }
             wave_lds_sync();
         }
-        if (count >= NK || all) break;
+        if (next > s) {
+            if (count >= NK || (all && !guess)) break;
+            if (guess) next = 2;  // too short
+            guess = false;
+        }
+        s = next;
     }
     const int cnt = knn_cut<NK>(S, count);
     if (lane == 0 && shell_exceeds_box(g, cnt, NK, cnt == NK ? S.d2[NK - 1] : INFINITY)) atomicOr(box_fail, 1);
