@@ -40,6 +40,14 @@ int ptm_selftest_codes(int k, const int32_t *tris, int ntri, uint64_t *codes, in
  * out for as many, 0 if not: such a frame is refused. */
 int ptm_selftest_grid(const double *box, const double *mn, const double *mx, int64_t n, int kn, int64_t *out);
 
+/* The fixed-point coordinates coord[3] that the neighbour search gives the
+ * point x in that grid: scale[0..2] = steps per unit length, scale[3..5] = cell
+ * edges, scale[6] = the error bound of a difference vector.  Of two points less
+ * than three cells apart along an axis, the 32-bit difference is the minimum
+ * image.  Returns as ptm_selftest_grid. */
+int ptm_selftest_fixed(const double *box, const double *mn, const double *mx, int64_t n, int kn, const double *x,
+                       int32_t *coord, double *scale);
+
 /* Eq. (3) superposition for a fixed correspondence with the library's QCP
  * solver: obs and tpl are [N][3] (N <= 15, not centred / not normalised).
  * Writes rmsd, scale and the quaternion (w,x,y,z) rotating the template

@@ -741,6 +741,18 @@ int ptm_selftest_grid(const double *box, const double *mn, const double *mx, int
     return out[3] <= max_cells(n);
 }
 
+int ptm_selftest_fixed(const double *box, const double *mn, const double *mx, int64_t n, int kn, const double *x,
+                       int32_t *coord, double *scale) {
+    const Grid g = make_grid(box, mn, mx, n, kn);
+    for (int a = 0; a < 3; a++) {
+        coord[a] = fixed_coord(x[a], g, a);
+        scale[a] = g.fix[a];
+        scale[3 + a] = g.h[a];
+    }
+    scale[6] = g.fix_err;
+    return grid_cells(g) <= max_cells(n);
+}
+
 int ptm_selftest_orient(const double *p, const int32_t *r) {
     if (r[0] == r[1] || r[0] == r[2] || r[0] == r[3] || r[1] == r[2] || r[1] == r[3] || r[2] == r[3]) return 0;
     double m = 0;

@@ -63,10 +63,6 @@ __device__ inline int cell_row(const Grid &g, int cy, int cz) {
     return tz * g.nc[1] + ty * wz + (cz - tz) * wy + (cy - ty);
 }
 
-__device__ inline double wrapped(double x, const Grid &g, int d) {
-    return g.periodic[d] ? x - g.L[d] * floor(x * g.invL[d]) : x - g.lo[d];
-}
-
 // the grid a kernel works on: one the host made, or the one on the device
 // (read through the constant address space: the kernel before has written it,
 // and scalar loads keep it out of the vector registers)
@@ -348,13 +344,6 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_scan_cells(const int32_t *__re
         for (int k = 0; k < SCAN_PER; k++)
             if (b + k <= cells) start[b + k] = o[k];
     }
-}
-
-// Coordinate x on the grid's fixed-point scale: 2^32 per periodic box length
-// (so that 32-bit differences wrap to the minimum image by themselves), 2^30
-// per extent of an open axis.
-__device__ inline int32_t fixed_coord(double x, const Grid &g, int d) {
-    return (int32_t)(uint32_t)fmin(fmax(wrapped(x, g, d) * g.fix[d], 0.0), 4294967295.0);
 }
 
 __global__ void k_bin_scatter(const double *__restrict__ pos, int64_t n, GridArg A,
@@ -651,7 +640,7 @@ __device__ inline bool knn_fast_atom(KnnRanges<W> &S, int t, int64_t p, int64_t 
     // roundings: 9 2^-24 of at most 2^21 buckets).  apart = one more than
     // twice that, rounded up.
     const double err = 2.1 * sqrt(rcap2) * g.fix_err / bucket + 1.15;
-    if (!(err < 256.0)) return false;  // a grid so long that its fixed point is too coarse
+    if (!(err < 256.0)) return false;  // coordinates so far from the box that FP64 is too coarse
     const int apart = 2 + (int)(2.0 * err);
     // per-axis steps in units of a bucket's square root
     const double root = 1.0 / sqrt(bucket);

@@ -24,19 +24,38 @@ struct Grid {
     int canonical;    // every periodic coordinate already lies in [0, L)
 };
 
-// Fixed-point scale of the axes: 2^32 steps per periodic box length, 2^30 per
-// extent of an open axis (1 if it has none).  fix_err: what a difference
-// vector is off at most, one step per axis and the rounding of the wrapped
-// coordinates (2^-50 of the largest coordinate mn .. mx).
+// Fixed-point scale of the axes: 2^(32 + k) steps per periodic box length,
+// 2^(30 + k) per extent of an open axis (1 if it has none), 2^k at most an
+// eighth of the axis' cells.  Of a coordinate's steps the lower 32 bits are
+// kept: a whole length is 0 in them, and atoms less than three cells apart are
+// less than 2^31 steps apart, so the 32-bit difference of two such atoms is
+// their minimum image.  Steps of a fixed 2^32 per length would leave an axis of
+// 10^6 cells (4 * 10^5 open) too few for the search, steps of a cell's own size
+// are as fine on any axis.  fix_err: what a difference vector is off at most,
+// one step per axis and the rounding of the wrapped coordinates (2^-50 of the
+// largest coordinate mn .. mx).
 __host__ __device__ inline void set_fixed_scale(Grid &g, const double (&ext)[3], const double *mn,
                                                 const double *mx) {
     double e2 = 0;
     for (int a = 0; a < 3; a++) {
-        g.fix[a] = (g.periodic[a] ? 4294967296.0 : 1073741824.0) / (ext[a] > 0 ? ext[a] : 1.0);
+        int bits = g.periodic[a] ? 32 : 30;
+        for (int c = g.nc[a]; c >= 16; c >>= 1) bits++;
+        g.fix[a] = ldexp(1.0, bits) / (ext[a] > 0 ? ext[a] : 1.0);
         const double e = 1.0 / g.fix[a] + 0x1p-50 * fmax(fabs(mn[a]), fabs(mx[a]));
         e2 += e * e;
     }
     g.fix_err = sqrt(e2);
+}
+
+// coordinate within the box of a periodic axis, or from the origin of an open one
+__host__ __device__ inline double wrapped(double x, const Grid &g, int d) {
+    return g.periodic[d] ? x - g.L[d] * floor(x * g.invL[d]) : x - g.lo[d];
+}
+
+// The lower 32 bits of coordinate x in fixed-point steps (set_fixed_scale).
+__host__ __device__ inline int32_t fixed_coord(double x, const Grid &g, int d) {
+    const double v = fmax(wrapped(x, g, d) * g.fix[d], 0.0);
+    return (int32_t)(uint32_t)fmin(fmax(v - floor(v * 0x1p-32) * 0x1p32, 0.0), 4294967295.0);
 }
 
 // the most cells a frame of n atoms may have: its cell arrays are laid out for
