@@ -88,6 +88,10 @@ int ptm_selftest_strain(int t, int precision, const double *obs, double *P);
 struct ptm_ctx;
 int ptm_selftest_strain_device(struct ptm_ctx *ctx, int t, const double *obs, double *P);
 
+/* Scratch allocations of ptm_classify on this context above bytes fail, as on
+ * a device whose memory is taken.  Returns 0 (PTM_OK) or PTM_E_INVALID. */
+int ptm_selftest_scratch_limit(struct ptm_ctx *ctx, int64_t bytes);
+
 #ifdef __cplusplus
 }
 #endif

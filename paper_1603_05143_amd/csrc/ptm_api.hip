@@ -8,6 +8,7 @@
 // ptm_serve.hip).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -65,8 +66,10 @@ bool FrameScratch::reserve(int64_t n, int64_t cells, bool topo, std::string &err
         if (base) (void)hipFree(base);
         base = nullptr;
         bytes = 0;
-        if (hipMalloc(&base, need) != hipSuccess) {
+        if (need > limit || hipMalloc(&base, need) != hipSuccess) {
             (void)hipGetLastError();
+            base = nullptr;
+            refused = std::min(refused, need);
             err = "device allocation of " + std::to_string(need) + " bytes failed";
             return false;
         }
@@ -307,11 +310,12 @@ ptm_status classify_frame(ptm_ctx *ctx, FrameScratch &S, bool noalloc, const dou
     const bool prof = (ctx->flags & PTM_F_PROFILE) != 0;
     ctx->prof_valid = false;
     // Up to DEVICE_GRID_ATOMS atoms the grid is made on the device and the host
-    // waits once, at the end (stage timing wants the bounds apart, and a
-    // budget may hold the frame's own grid but not the largest one).
-    if (n_atoms <= DEVICE_GRID_ATOMS && !prof &&
-        !(ctx->budget && frame_bytes(n_atoms, max_cells(n_atoms), bounds_blocks(n_atoms), J.topo) > ctx->budget)) {
-        if ((st = reserve(max_cells(n_atoms))) != PTM_OK) return st;
+    // waits once, at the end (stage timing wants the bounds apart; a budget, or
+    // what is left of the device's memory, may hold the frame's own grid but
+    // not the largest one).
+    const size_t largest = frame_bytes(n_atoms, max_cells(n_atoms), bounds_blocks(n_atoms), J.topo);
+    if (n_atoms <= DEVICE_GRID_ATOMS && !prof && !(ctx->budget && largest > ctx->budget) && largest < S.refused &&
+        reserve(max_cells(n_atoms)) == PTM_OK) {
         J.dgrid = ctx->grid_state;
         for (int a = 0; a < 3; a++) J.box[a] = box[a];
         *ctx->pinned = 0;
@@ -334,6 +338,7 @@ ptm_status classify_frame(ptm_ctx *ctx, FrameScratch &S, bool noalloc, const dou
         }
         J.dgrid = nullptr;  // FRAME_GRID: the frame was left alone; refused (or laid out) by its own grid below
     }
+    ctx->err.clear();
     // bounds first (needs scratch for the partials): reserve with a tiny grid
     if ((st = reserve(1)) != PTM_OK) return st;
     double mn[3], mx[3];
@@ -751,6 +756,12 @@ int ptm_selftest_fixed(const double *box, const double *mn, const double *mx, in
     }
     scale[6] = g.fix_err;
     return grid_cells(g) <= max_cells(n);
+}
+
+int ptm_selftest_scratch_limit(ptm_ctx *ctx, int64_t bytes) {
+    if (!ctx || bytes < 0) return PTM_E_INVALID;
+    ctx->main.limit = (size_t)bytes;
+    return PTM_OK;
 }
 
 int ptm_selftest_orient(const double *p, const int32_t *r) {

@@ -28,6 +28,8 @@ struct FrameScratch {
     void *base = nullptr;
     size_t bytes = 0;
     bool pooled = false;  // a serving-pool buffer of a fixed size class
+    size_t refused = SIZE_MAX;  // the smallest allocation that failed so far
+    size_t limit = SIZE_MAX;    // larger ones fail (a self-check's stand-in for a full device)
     int32_t *cell_of = nullptr, *slot_of = nullptr, *sid = nullptr, *count = nullptr, *start = nullptr;
     double *spos = nullptr;  // sorted positions, x y z of each atom together
     int4 *sfix = nullptr;    // sorted fixed-point positions and ids, in the space of ord (written later)
