@@ -1620,13 +1620,15 @@ constexpr int TB = 64;  // threads per block of the topology kernel
 // LDS of one block.  P: the neighbour vectors rounded to FP32 (the input of
 // the predicate filters; every predicate is decided exactly, so both
 // precision forms use this kernel); F: facets; H: the horizon of the current
-// insertion, and between insertions the queue of the facet walk.  20,480
-// bytes: eight blocks per CU.
+// insertion.  All a lane's own words; the queue of the facet walk takes what a
+// hull leaves free.  20,480 bytes: eight blocks per CU.
 struct TopoShared {
     float P[3][KMAX][TB];
     uint32_t F[2 * KMAX - 4][TB];
     uint32_t H[KMAX][TB];
 };
+static_assert(offsetof(TopoShared, H) == offsetof(TopoShared, F) + sizeof(uint32_t) * (2 * KMAX - 4) * TB,
+              "H follows F");
 static_assert(sizeof(TopoShared) == 20480, "eight blocks of the topology kernel per CU");
 
 // facet word: v0 | v1<<4 | v2<<8 | nb0<<12 | nb1<<17 | nb2<<22
@@ -1914,26 +1916,30 @@ __device__ uint64_t lane_facet_code(TopoShared &S, int t, uint64_t (&code)[CODE_
     const int x2 = fvr(w0, i0, 2);
     uint64_t lab = ~0ull ^ 0xFull << (4 * u) ^ 0xEull << (4 * v) ^ 0xDull << (4 * x2);
     uint32_t nl = 3, seen = 1u << f0;
-    // queue of facets to visit, a 16-bit entry and a row of TB each: facet |
-    // start of the entry edge in it << 5
-    typedef uint16_t __attribute__((may_alias)) entry_t;
-    entry_t *queue = reinterpret_cast<entry_t *>(&S.H[0][0]) + t;
-    uint32_t tail = (uint32_t)t * 2;  // byte offset
+    // Queue of facets to visit: facet | start of the entry edge in it << 5.  The
+    // first three (always new) stay in registers, the others, and one that
+    // does not count, take words of the lane's own, a row of TB each: 17 of the
+    // 18 that the 12-point hull leaves free in F and H, 21 of P, which the
+    // 14-point hull, the last, no longer needs.
+    typedef uint32_t __attribute__((may_alias)) entry_t;
+    static_assert(K == 12 || K == 14, "the rows below are free");
+    entry_t *queue = K == 12 ? &S.F[NF][t] : reinterpret_cast<entry_t *>(&S.P[0][0][t]);
+    uint32_t tail = 0;  // byte offset
     auto push = [&](uint32_t g, uint32_t start) {
         const uint32_t fresh = (~seen >> g) & 1;
         // (the next entry overwrites it if it does not count)
-        *reinterpret_cast<entry_t *>(reinterpret_cast<char *>(&S.H[0][0]) + tail) = (entry_t)(g | start << 5);
+        *reinterpret_cast<entry_t *>(reinterpret_cast<char *>(queue) + tail) = g | start << 5;
         seen |= 1u << g;
-        tail = (fresh << 7) + tail;
+        tail = (fresh << 8) + tail;
         return fresh;
     };
-    push(fnr(w0, i0, 1), x2);
-    push(fnr(w0, i0, 2), u);
-    push(fnr(w0, i0, 0), v);
+    const int n0 = fnr(w0, i0, 1), n1 = fnr(w0, i0, 2), n2 = fnr(w0, i0, 0);
+    const uint32_t first3[3] = {(uint32_t)n0 | (uint32_t)x2 << 5, (uint32_t)n1 | u << 5, (uint32_t)n2 | v << 5};
+    seen |= 1u << n0 | 1u << n1 | 1u << n2;
     uint64_t c0 = 0, c1 = 0, bits = 0;
 #pragma unroll
     for (int k = 0; k < NF - 1; k++) {
-        const uint32_t e = queue[k * TB];
+        const uint32_t e = k < 3 ? first3[k] : queue[(k - 3) * TB];
         const uint32_t start = e >> 5;
         const uint32_t gw = S.F[e & 0x1F][t];  // (rows from 24 lie in H: in range for any entry)
         const int i = fpos(gw, start), c = fvr(gw, i, 2);
