@@ -382,7 +382,7 @@ ptm_status classify_frame(ptm_ctx *ctx, FrameScratch &S, bool noalloc, const dou
         PTM_HIP(ctx, hipMemcpy(left, S.count + cells + 1, 8, hipMemcpyDeviceToHost));
         PTM_HIP(ctx, hipMemcpy(&pairs, job_counter(S.count, cells), 8, hipMemcpyDeviceToHost));
         ctx->prof_info[PTM_INFO_CELLS] = cells;
-        ctx->prof_info[PTM_INFO_KNN_EXACT] = knn_fast_applies(J.grid) ? left[0] : n_atoms;
+        ctx->prof_info[PTM_INFO_KNN_EXACT] = knn_fast_applies(n_atoms, J.grid) ? left[0] : n_atoms;
         ctx->prof_info[PTM_INFO_PAIRS] = (int64_t)pairs;
         ctx->prof_info[PTM_INFO_DECIDE_FULL] = left[1];
     }

@@ -3500,7 +3500,8 @@ static int match_atoms_per_wave(int64_t n) {
     while (apw < 64 && n > (int64_t)apw * 1024) apw *= 2;
     return apw;
 }
-bool knn_fast_applies(const Grid &g) {
+bool knn_fast_applies(int64_t n, const Grid &g) {
+    if (n <= KNN_WAVE_ATOMS) return false;
     for (int a = 0; a < 3; a++)
         if (g.periodic[a] && g.nc[a] < 5) return false;
     return true;
@@ -3512,7 +3513,7 @@ static void launch_knn_nk(int64_t n, const GridArg &A, const double *spos, const
     int64_t blocks = (n + 255) / 256;
     // up to KNN_WAVE_ATOMS atoms, a wave each: the chip holds 4096 such waves,
     // and one takes a fraction of the time of a lane's walk through its block
-    if (n > KNN_WAVE_ATOMS && (A.dev || knn_fast_applies(A.val))) {
+    if (A.dev ? n > KNN_WAVE_ATOMS : knn_fast_applies(n, A.val)) {
         hipLaunchKernelGGL(k_knn_fast<NK>, dim3((unsigned)xcd_pad(blocks)), dim3(256), 0, st, n, A, spos, sfix,
                            start, nbr_id, nbr_rel, todo, todo_count, box_fail);
         // the atoms left over are few; at most 1024 blocks of four waves stride over them

@@ -187,7 +187,8 @@ void launch_bin_scatter(const double *pos, int64_t n, const GridArg &A, const in
                         const int32_t *box_fail, hipStream_t st);
 // k-NN: fast block search, then the exact shell search for the atoms it
 // leaves in todo (n entries) / *todo_count (zeroed by the caller).
-bool knn_fast_applies(const Grid &g);
+// (knn_fast_applies: whether the block search runs at all)
+bool knn_fast_applies(int64_t n, const Grid &g);
 // nk = 14 (Euclidean ordering) or VK = 18 (input of the topological
 // ordering) nearest neighbours, rank-major [nk][n] / [nk][3][n].  *box_fail
 // (zeroed by the caller) is set when the frame has a periodic axis and some

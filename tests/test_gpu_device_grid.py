@@ -84,3 +84,24 @@ def test_errors_write_nothing(n, what):
         assert st == ptm.PTM_OK
     finally:
         c.close()
+
+
+@pytest.mark.parametrize("n,side,all_exact", [(300, None, True), (16384, None, True), (16385, None, False),
+                                              (17000, 10.3, True)])
+def test_work_counts_name_the_search(n, side, all_exact):
+    """knn_exact of the work counts: every atom where the wave-per-atom search
+    runs alone (small frames, a periodic axis of fewer than five cells),
+    otherwise what the other one leaves."""
+    import torch
+    pos, box = _frame(n, "open" if n < 1000 else "periodic")
+    if side:  # thin in z
+        wide = (n / 0.08 / side) ** 0.5
+        pos, box = np.random.default_rng(n).random((n, 3)) * [wide, wide, side], np.array([wide, wide, side])
+    c = ptm.Classifier(device=0, flags=ptm.PTM_F_PROFILE)
+    try:
+        c.classify(torch.from_numpy(np.ascontiguousarray(pos)).to("cuda:0"), box)
+        info = ptm.ptm_frame_info(c.ctx)
+    finally:
+        c.close()
+    print(f"[info] n={n} {info}", flush=True)
+    assert (info["knn_exact"] == n) == all_exact and info["knn_exact"] <= n
