@@ -993,11 +993,11 @@ __device__ void knn_exact_atom(KnnWave &S, int64_t p, int64_t n, const Grid &g, 
         u[a] = wrapped(xs[a], g, a);
     }
     int count = 0;
-    // (blocks grow by a quarter at least: an atom a hundred thousand empty
-    // cells from the others takes some fifty of them)
+    // (blocks grow by a cell, later by a quarter: an atom a hundred thousand
+    // empty cells from the others takes some fifty of them)
     bool guess = false, guessed = false;  // (of the wave)
     for (int s = 2;;) {
-        int lo[3], hi[3], next = s + 1 + s / 4;
+        int lo[3], hi[3], next = s + 1 + (s < 6 ? 0 : s / 4);
         for (int a = 0; a < 3; a++) shell_range(g, a, cc[a], s, lo[a], hi[a]);
         bool all;
         const double reach = block_reach(g, cc, u, lo, hi, all);
@@ -1029,7 +1029,7 @@ __device__ void knn_exact_atom(KnnWave &S, int64_t p, int64_t n, const Grid &g, 
                 const int y = __shfl_up(incl, d);
                 if (lane >= d) incl += y;
             }
-            const int total = __shfl(incl, 63);
+            const int total = __builtin_amdgcn_readlane(incl, 63);
             if (s == 2 && !guessed && total > KNN_FULL_BLOCK) {
                 guess = guessed = true;
                 if (total > 2 * KNN_FULL_BLOCK) {
@@ -1038,10 +1038,11 @@ __device__ void knn_exact_atom(KnnWave &S, int64_t p, int64_t n, const Grid &g, 
                 }
             }
             if (guess) {
-                double vol = 1;
-                for (int a = 0; a < 3; a++) vol *= (hi[a] - lo[a] + 1) * g.h[a];
-                const double r = cbrt(vol * (3 * NK) / (4.1887902047863905 * max(total, 1)));
-                thr = fmin(thr, r * r);
+                // the volume of 3 K atoms, in cells, to the power 2/3 (any radius is
+                // right, so FP32 will do)
+                const float vol = (float)((hi[0] - lo[0] + 1) * rows * (3 * NK)) / (4.19f * (float)max(total, 1));
+                const double h = fmin(fmin(g.h[0], g.h[1]), g.h[2]);
+                thr = fmin(thr, h * h * (double)__builtin_amdgcn_exp2f(__builtin_amdgcn_logf(vol) * (2.0f / 3.0f)));
             }
             S.pre[lane] = incl - (la + lb);
             S.qa[lane] = qa;
