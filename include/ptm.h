@@ -39,10 +39,11 @@ typedef struct ptm_ctx ptm_ctx; /* opaque: device tables, scratch, stream */
 typedef enum {
     PTM_OK = 0,
     PTM_E_INVALID = 1,   /* bad argument: NULL pointer, n < 0, bad box, NaN/Inf coordinate */
-    PTM_E_NOMEM = 2,     /* device allocation failed or HBM budget exceeded */
+    PTM_E_NOMEM = 2,     /* device allocation failed, HBM budget exceeded, or extents that leave no cell
+                            grid of a size that fits (ratios beyond 10^19, differences that overflow) */
     PTM_E_DEVICE = 3,    /* HIP runtime error (message in ptm_last_error) */
     PTM_E_BOX = 4,       /* periodic box too short for the neighbour shell (see ptm_classify) */
-    PTM_E_TOO_LARGE = 5, /* n > PTM_MAX_ATOMS */
+    PTM_E_TOO_LARGE = 5, /* n > PTM_MAX_ATOMS; ptm_classify_noalloc: more than its scratch holds */
     PTM_E_BUSY = 6,      /* serving queue full */
     PTM_E_TIMEOUT = 7    /* ptm_wait timed out; the ticket stays valid */
 } ptm_status;
@@ -222,8 +223,9 @@ ptm_status ptm_submit(ptm_ctx *ctx, const double *positions, const int8_t *speci
 /* Wait for a ticket (timeout_us < 0: forever; 0: poll).  PTM_E_TIMEOUT if
  * not yet complete (the ticket stays valid); PTM_E_INVALID for an unknown
  * ticket; PTM_E_BOX when the frame's periodic box is too short (as for
- * ptm_classify: no output is written, the ticket is consumed).  stats may be
- * NULL. */
+ * ptm_classify: no output is written, the ticket is consumed); with
+ * PTM_F_PERSISTENT also PTM_E_NOMEM for extents that leave no cell grid
+ * (ptm_submit reports those otherwise).  stats may be NULL. */
 ptm_status ptm_wait(ptm_ctx *ctx, uint64_t ticket, int64_t timeout_us, ptm_frame_stats *stats);
 
 /* Destroy a context (waits for in-flight tickets).  NULL is a no-op. */
@@ -238,7 +240,10 @@ const char *ptm_last_error(const ptm_ctx *ctx);
 /* Device time in milliseconds of each pipeline stage of the most recent
  * ptm_classify on a context created with PTM_F_PROFILE, measured with HIP
  * events on the stream the kernels run on: ms[PTM_STAGE_*] for
- * min(n, PTM_NSTAGES) entries (0 for a stage that did not run).
+ * min(n, PTM_NSTAGES) entries (0 for a stage that did not run).  So that the
+ * bounds are a stage of their own, such a context always makes the cell grid
+ * on the host; without the flag, frames up to 2,000,000 atoms make it on the
+ * device, with fewer launches and one wait less.  Results are the same.
  * PTM_E_INVALID if the context was not created with PTM_F_PROFILE. */
 ptm_status ptm_stage_times(const ptm_ctx *ctx, double *ms, int n);
 

@@ -1,7 +1,12 @@
 // ptm_kernels.hip -- HIP kernels of the PTM classification pass for gfx950.
 //
 // Pipeline for one frame (Polyhedral Template Matching, arXiv:1603.05143):
-//   k_bounds          finite check + bounding box (open axes)
+//   k_setup_small     frames up to 4,096 atoms: all of the following up to the
+//                     sorted copy, in one block
+//   k_bounds_grid     up to 2 M atoms: finite check, bounding box, cleared
+//                     counters and the cell grid
+//   k_bounds          beyond, or with stage timing: finite check + bounding box
+//                     (open axes); the host makes the grid
 //   k_bin_count       cell id + per-cell counter (counting sort, pass 1)
 //   (scan)            exclusive prefix sum of the counters
 //   k_bin_scatter     sorted copy of the positions, x y z of an atom together
@@ -525,9 +530,9 @@ inline int64_t xcd_pad(int64_t nblocks) { return (nblocks + NXCD - 1) / NXCD * N
 // x-rows nearest-first (a row of cells is one contiguous range of the sorted
 // atoms, two if it wraps).
 //
-// What bounds it: vector instructions (busy 73 % of the time on a 0.92 M-atom
-// frame), and in frames beyond the caches the latency of its loads (47 % busy
-// at 31.7 M atoms).  Candidates are read as 16-byte records of fixed-point
+// What bounds it: vector issue (0.68 of the slots on a 0.92 M-atom frame) and
+// the latency of its loads, more so in frames beyond the caches (0.58 of the
+// slots at 31.7 M atoms).  Candidates are read as 16-byte records of fixed-point
 // coordinates, whose 32-bit differences are minimum images without any shift
 // and which are converted to FP32 (half the cost of an FP64 operation); FP64
 // positions are read for the neighbours found only, where 24-byte FP64
@@ -2716,7 +2721,8 @@ __device__ inline void load_templates(MatchShared &M, const TablesView &T) {
 //
 // What bounds it (FP64, 31.7 M atoms, three candidates an atom): of some
 // 95,000 cycles of a wave, 31,000 go to the superpositions and 20,000 to the
-// finish, both near the issue rate of two waves per SIMD, 13,000 to the fold,
+// finish, both chains of dependent instructions that two waves per SIMD leave
+// uncovered (0.38 of the issue slots are used), 13,000 to the fold,
 // 12,000 to the first read of the points.  When every job and the finish read
 // the points for themselves, rank after rank, a wave waited for each: lanes
 // that share an atom hit on each other's outstanding misses, and the waves of
