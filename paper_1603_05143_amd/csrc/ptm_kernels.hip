@@ -556,10 +556,10 @@ inline int64_t xcd_pad(int64_t nblocks) { return (nblocks + NXCD - 1) / NXCD * N
 // their atoms.  Each lane then walks its own table of ranges, kept in LDS, two
 // atoms per step, so that a wave pays about the per-lane atom count.  A range
 // of more than 64 atoms takes several entries, and where a lane's table is
-// full the wave searches what it holds, the lane keeps the listed atoms alone
-// (an entry each), and the rows go on: any number of atoms fits.  Where the
-// own row is dense (KNN_DENSE_ROW) the Kth distance is taken after one, five
-// and nine rows, which spares most of the block.
+// full the wave searches what it holds, the lane frees every entry that the
+// list does not name (12 at least), and the rows go on: any number of atoms
+// fits.  Where the own row is dense (KNN_DENSE_ROW) the Kth distance is taken
+// after one, five and nine rows, which spares most of the block.
 //
 // The cells follow the mean density, so a particle in a box of 2.5 diameters
 // has 400 atoms in a 5 x 5 x 1 slice of its block.  With one table for the
@@ -567,7 +567,8 @@ inline int64_t xcd_pad(int64_t nblocks) { return (nblocks + NXCD - 1) / NXCD * N
 // atoms in such a box 4.14 ms, 0.35 with this loop (0.60 with the search on
 // FP64 records); 1,000,000 atoms 39.2 ms, 1.61 (2.43).  At the mean density
 // the atoms at the x edges of the box, whose rows are two ranges, fit as well:
-// k-NN at 0.92 M atoms 372 -> 327 us, at 31.7 M 10.54 -> 10.19 ms.
+// k-NN at 0.92 M atoms 372 -> 304 us, at 31.7 M 10.54 -> 9.90 ms (with the
+// exact order's loads below).
 //
 // Two atoms whose buckets differ by `apart` or more are in the exact order
 // (the rounding of the coordinates, of d^2 and of the buckets is covered).
@@ -584,7 +585,7 @@ constexpr int KNN_OFF_BITS = 6; // offset within a range
 constexpr int KNN_CODE_BITS = 11;
 constexpr uint32_t KNN_BUCKETS = (1u << (32 - KNN_CODE_BITS)) - 16;
 static_assert(KNN_RANGES << KNN_OFF_BITS < 1 << KNN_CODE_BITS, "range and offset fit the code; the last means none");
-static_assert(KNN_LIST < KNN_RANGES, "the atoms of the list, a range each, leave room for more");
+static_assert(KNN_LIST < KNN_RANGES && KNN_RANGES < 32, "the list names fewer entries than there are; 31 means none");
 // atoms in the five cells of the own row from which the rows are taken in
 // smaller steps (3.6 at the mean density)
 constexpr int KNN_DENSE_ROW = 24;
@@ -669,7 +670,7 @@ __device__ inline bool knn_fast_atom(KnnRanges<W> &S, int t, int64_t p, int64_t 
     uint32_t key[KNN_LIST];
 #pragma unroll
     for (int m = 0; m < KNN_LIST; m++) key[m] = ~0u;
-    int nrange = 0, taken = 0;  // ranges held, those whose atoms are in the list
+    uint32_t unused = (1u << KNN_RANGES) - 1;  // entries of the table that are free
     float cap = (float)rcap2 * 1.000001f;  // squared radius still to search
     uint32_t r0 = 0, r1 = 0, w0 = 0, w1 = 0;  // what is left of the row: its part here, its part across the box edge
     // (dy + 2) + 5 (dz + 2) of the 25 rows by increasing dy^2 + dz^2, 5 bits each
@@ -678,13 +679,15 @@ __device__ inline bool knn_fast_atom(KnnRanges<W> &S, int t, int64_t p, int64_t 
     int row = 0, stage = 9;  // the same in every lane: the next row, the row at which this stage ends
     bool more_rows = true;
     do {
+        uint32_t pending = unused;  // entries to search: those that are taken below
         for (;;) {
             // one range of the row per turn
-            if (r0 < r1 && nrange < KNN_RANGES) {
+            if (r0 < r1 && unused) {
                 const uint32_t cnt = min(r1 - r0, 1u << KNN_OFF_BITS);
-                S.q0[nrange][t] = r0;
-                S.cnt[nrange][t] = (uint8_t)cnt;
-                nrange++;
+                const int e = __builtin_ctz(unused);
+                S.q0[e][t] = r0;
+                S.cnt[e][t] = (uint8_t)cnt;
+                unused &= unused - 1;
                 r0 += cnt;
                 if (r0 == r1) {
                     r0 = w0;
@@ -693,7 +696,7 @@ __device__ inline bool knn_fast_atom(KnnRanges<W> &S, int t, int64_t p, int64_t 
                 }
             }
             if (__ballot(r0 < r1)) {
-                if (__ballot(r0 < r1 && nrange == KNN_RANGES)) break;
+                if (__ballot(r0 < r1 && !unused)) break;
                 continue;
             }
             if (row == stage) break;
@@ -727,17 +730,19 @@ __device__ inline bool knn_fast_atom(KnnRanges<W> &S, int t, int64_t p, int64_t 
             }
             if (row == 1 && __ballot((int)(r1 - r0) + (int)(w1 - w0) >= KNN_DENSE_ROW)) stage = 1;
         }
+        pending &= ~unused;
         // the atoms of the ranges, two per step; the next step's are loaded
         // before this one's are used
         int q = 0, qend = 0;
         uint32_t code = 0;  // code of atom q less q
         auto fetch = [&](int3v &A, int3v &B, uint32_t &ca, uint32_t &cb) {
-            const bool any = q < qend || taken < nrange;
-            if (q >= qend && taken < nrange) {
-                q = (int)S.q0[taken][t];
-                qend = q + (int)S.cnt[taken][t];
-                code = ((uint32_t)taken << KNN_OFF_BITS) - (uint32_t)q;
-                taken++;
+            const bool any = q < qend || pending;
+            if (q >= qend && pending) {
+                const int e = __builtin_ctz(pending);
+                pending &= pending - 1;
+                q = (int)S.q0[e][t];
+                qend = q + (int)S.cnt[e][t];
+                code = ((uint32_t)e << KNN_OFF_BITS) - (uint32_t)q;
             }
             // loads without a branch (the atom itself where there is none),
             // so that they can stay in flight
@@ -787,22 +792,12 @@ __device__ inline bool knn_fast_atom(KnnRanges<W> &S, int t, int64_t p, int64_t 
         // an upper bound of the Kth distance found so far
         cap = fminf(cap, (float)((key[NK - 1] >> KNN_CODE_BITS) + (uint32_t)apart) * ((float)bucket * 1.000001f));
         if (r0 < r1) {
-            // the table is full: only the atoms of the list stay in it, a range each
-            uint32_t listed[KNN_LIST];
+            // the table is full: the entries that the list names stay (an empty
+            // place of the list names one past the last)
+            uint32_t named = 0;
 #pragma unroll
-            for (int m = 0; m < KNN_LIST; m++) {
-                const uint32_t code = key[m] & ((1u << KNN_CODE_BITS) - 1);
-                listed[m] = key[m] == ~0u ? 0u : S.q0[code >> KNN_OFF_BITS][t] + (code & ((1u << KNN_OFF_BITS) - 1));
-            }
-            nrange = 0;
-#pragma unroll
-            for (int m = 0; m < KNN_LIST; m++)
-                if (key[m] != ~0u) {
-                    S.q0[m][t] = listed[m];
-                    key[m] = (key[m] >> KNN_CODE_BITS << KNN_CODE_BITS) | (uint32_t)m << KNN_OFF_BITS;
-                    nrange = m + 1;
-                }
-            taken = nrange;
+            for (int m = 0; m < KNN_LIST; m++) named |= 1u << (key[m] >> KNN_OFF_BITS & 31);
+            unused = ~named & ((1u << KNN_RANGES) - 1);
         }
         more_rows = __ballot(r0 < r1) != 0;
         if (!more_rows && row == stage) {
@@ -836,17 +831,32 @@ __device__ inline bool knn_fast_atom(KnnRanges<W> &S, int t, int64_t p, int64_t 
         // until none is left to make
         double ed[KNN_LIST];
         int32_t ej[KNN_LIST];
+        // (four entries' loads in flight at a time, which the registers hold;
+        // entries past cnt read atom 0.  One after the other, 116 bytes a lane
+        // were spilled and a frame without noise waited for each: 78 -> 73 us at
+        // 100 k atoms, 271 -> 251 us at 0.92 M)
+        constexpr int GROUP = 4;
 #pragma unroll
-        for (int m = 0; m < KNN_LIST; m++) {
-            ed[m] = INFINITY;
-            ej[m] = 0x7fffffff;
-            if (m < cnt) {
-                const int64_t q = kq[m];
-                const double dx = min_image(spos[3 * q] - xi, g, 0), dy = min_image(spos[3 * q + 1] - yi, g, 1);
-                const double dz = min_image(spos[3 * q + 2] - zi, g, 2);
-                ed[m] = (dx * dx + dy * dy) + dz * dz;
-                ej[m] = sfix[q].w;
-            }
+        for (int m0 = 0; m0 < KNN_LIST; m0 += GROUP) {
+            double v[GROUP][3];
+            int32_t id[GROUP];
+#pragma unroll
+            for (int k = 0; k < GROUP; k++)
+                if (m0 + k < KNN_LIST) {
+                    const int64_t q = kq[m0 + k];
+                    for (int d = 0; d < 3; d++) v[k][d] = spos[3 * q + d];
+                    id[k] = sfix[q].w;
+                }
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int k = 0; k < GROUP; k++)
+                if (m0 + k < KNN_LIST) {
+                    const int m = m0 + k;
+                    const double dx = min_image(v[k][0] - xi, g, 0), dy = min_image(v[k][1] - yi, g, 1);
+                    const double dz = min_image(v[k][2] - zi, g, 2);
+                    ed[m] = m < cnt ? (dx * dx + dy * dy) + dz * dz : INFINITY;
+                    ej[m] = m < cnt ? id[k] : 0x7fffffff;
+                }
         }
         bool moved;
         do {
