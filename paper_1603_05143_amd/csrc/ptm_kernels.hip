@@ -530,8 +530,8 @@ inline int64_t xcd_pad(int64_t nblocks) { return (nblocks + NXCD - 1) / NXCD * N
 // x-rows nearest-first (a row of cells is one contiguous range of the sorted
 // atoms, two if it wraps).
 //
-// What bounds it: vector issue (0.68 of the slots on a 0.92 M-atom frame) and
-// the latency of its loads, more so in frames beyond the caches (0.58 of the
+// What bounds it: vector issue (0.74 of the slots on a 0.92 M-atom frame) and
+// the latency of its loads, more so in frames beyond the caches (0.61 of the
 // slots at 31.7 M atoms).  Candidates are read as 16-byte records of fixed-point
 // coordinates, whose 32-bit differences are minimum images without any shift
 // and which are converted to FP32 (half the cost of an FP64 operation); FP64
